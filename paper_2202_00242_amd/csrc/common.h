@@ -98,6 +98,9 @@ struct RelPose {
   float Rs[9], ts[3];   // T_s
   float Rti[9], tti[3]; // T_t^-1
   int skip;             // the source's bounding box misses the map's voxels: no inlier possible
+  // FP32 lookup (batches): voxel coordinates relative to the map's box, s = Af mu + sf. When every
+  // |fract(s) - 1/2| <= thr, floor(s) is the exact (FP64) voxel; thr < 0: never.
+  float Af[9], sf[3], thr;
 };
 
 // One factor of a batch as the persistent kernel sees it.

@@ -90,6 +90,17 @@ __host__ __device__ inline unsigned brick_of(unsigned dx, unsigned dy, unsigned 
                                              unsigned gbz) {
   return ((dx >> 2) * gby + (dy >> 2)) * gbz + (dz >> 1);
 }
+// a * b + c for a, b < 2^24 in one full-rate instruction (the compiler cannot see the bound and
+// takes the 64-bit multiply-add).
+__device__ inline unsigned mad24(unsigned a, unsigned b, unsigned c) {
+  unsigned r;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+  return r;
+}
+// bit_in_brick with rubbish above bit 4 (shifts and bit-field extracts take their amounts mod 32).
+__device__ inline unsigned bit_in_brick_mod32(unsigned dx, unsigned dy, unsigned dz) {
+  return (((dx << 2) | (dy & 3u)) << 1) | (dz & 1u);
+}
 __host__ __device__ inline unsigned bit_in_brick(unsigned dx, unsigned dy, unsigned dz) {
   return ((dx & 3u) << 3) | ((dy & 3u) << 1) | (dz & 1u);
 }
@@ -150,14 +161,32 @@ __device__ inline int floor_sat_i32_f32(float s) {
   return k;
 }
 
+// floor(s) as an int32 in one instruction (saturating; NaN gives 0).
+__device__ inline int floor_i32_f32(float s) {
+  int k;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(k) : "v"(s));
+  return k;
+}
+
 // ------------------------------------------------------------------ fused covariance inverse
+
+// 1 / x for a determinant: the hardware estimate and three Newton steps, the compiler's division
+// without the scaling for operands near the ends of the range (7 operations instead of 11, the
+// same bits). Sums and products of FP32 covariances keep det within 10^-140 .. 10^120, where no
+// step over- or underflows.
+__device__ inline double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
 
 // Omega = (Cv + R C R^T)^-1, formed in FP64 whatever the precision of the rest of the point's
 // arithmetic: with plane-like covariances the fused covariance has a smallest eigenvalue ~1e-3
 // of its entries, and forming or inverting it in FP32 would lose about that factor of accuracy
 // in the surface-normal direction (FP64 vector arithmetic runs at the FP32 rate on this GPU).
-// Adjugate inverse with Sylvester's criterion; o = (xx, xy, xz, yy, yz, zz). False when the
-// fused covariance is not positive definite or not finite.
+// Adjugate inverse with Sylvester's criterion; o = (xx, xy, xz, yy, yz, zz). False (o: products with
+// zero) when the fused covariance is not positive definite or not finite.
 template <typename T>
 __device__ inline bool fused_inverse(const double* R, const double* cv, const float* c, T o[6]) {
   const double c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3], c4 = c[4], c5 = c[5];
@@ -185,15 +214,15 @@ __device__ inline bool fused_inverse(const double* R, const double* cv, const fl
   const double A22 = s00 * s11 - s01 * s01;
   const double det = s00 * A00 + s01 * A01 + s02 * A02;
   // Sylvester's criterion: leading principal minors s00, A22 and det all positive
-  if (!(s00 > 0.0) || !(A22 > 0.0) || !(det > 0.0) || !isfinite(det)) return false;
-  const double inv = 1.0 / det;
+  const bool ok = s00 > 0.0 && A22 > 0.0 && det > 0.0 && isfinite(det);
+  const double inv = ok ? reciprocal(det) : 0.0;  // no branch: the callers' sums stay in place
   o[0] = (T)(A00 * inv);
   o[1] = (T)(A01 * inv);
   o[2] = (T)(A02 * inv);
   o[3] = (T)(A11 * inv);
   o[4] = (T)(A12 * inv);
   o[5] = (T)(A22 * inv);
-  return true;
+  return ok;
 }
 
 // ------------------------------------------------------------------ accumulators
@@ -222,7 +251,7 @@ struct AccF32 {
   }
   __device__ void add(int i, float x) { v[i] += x; }
   __device__ void add(int i, double x) { v[i] += (float)x; }
-  __device__ double get(int i) const { return (double)v[i]; }
+  __device__ float get(int i) const { return v[i]; }
 };
 
 // Kahan-compensated FP32 running sums (Kahan 1965): c carries the low-order part lost by the
@@ -252,26 +281,39 @@ struct AccKahan {
 //   27     e   = sum d^T Omega d
 enum : int { kHrr = 0, kHrt = 6, kHtt = 15, kBr = 21, kBt = 24, kE = 27 };
 
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// x . y and a b - c d with the roundings written out: the compiler's own contraction picks another
+// product to round whenever the code around it changes, which moves FP32 sums by ~1e-9.
+template <typename T>
+__device__ __forceinline__ T dot3(T x0, T y0, T x1, T y1, T x2, T y2) {
+  return fma_of(x2, y2, fma_of(x1, y1, x0 * y0));
+}
+template <typename T>
+__device__ __forceinline__ T det2(T a, T b, T c, T d) {
+  return fma_of(a, b, -(c * d));
+}
+
 // Adds one inlier's contribution (q, d in the target frame, Omega = o).
 template <bool LIN, typename T, class Acc>
 __device__ inline void add_point_terms(const T q[3], const T d[3], const T o[6], Acc& acc) {
-  const T u0 = o[0] * d[0] + o[1] * d[1] + o[2] * d[2];
-  const T u1 = o[1] * d[0] + o[3] * d[1] + o[4] * d[2];
-  const T u2 = o[2] * d[0] + o[4] * d[1] + o[5] * d[2];
-  acc.add(kE, d[0] * u0 + d[1] * u1 + d[2] * u2);
+  const T u0 = dot3(o[0], d[0], o[1], d[1], o[2], d[2]);
+  const T u1 = dot3(o[1], d[0], o[3], d[1], o[4], d[2]);
+  const T u2 = dot3(o[2], d[0], o[4], d[1], o[5], d[2]);
+  acc.add(kE, dot3(d[1], u1, d[0], u0, d[2], u2));
   if constexpr (LIN) {
     const T q0 = q[0], q1 = q[1], q2 = q[2];
     // M = [q]x Omega (= H_rt), column j = q x Omega[:, j]
-    const T m00 = q1 * o[2] - q2 * o[1], m10 = q2 * o[0] - q0 * o[2], m20 = q0 * o[1] - q1 * o[0];
-    const T m01 = q1 * o[4] - q2 * o[3], m11 = q2 * o[1] - q0 * o[4], m21 = q0 * o[3] - q1 * o[1];
-    const T m02 = q1 * o[5] - q2 * o[4], m12 = q2 * o[2] - q0 * o[5], m22 = q0 * o[4] - q1 * o[2];
+    const T m00 = det2(q1, o[2], q2, o[1]), m10 = det2(q2, o[0], q0, o[2]), m20 = det2(q0, o[1], q1, o[0]);
+    const T m01 = det2(q1, o[4], q2, o[3]), m11 = fma_of(-q0, o[4], q2 * o[1]), m21 = det2(q0, o[3], q1, o[1]);
+    const T m02 = det2(q1, o[5], q2, o[4]), m12 = det2(q2, o[2], q0, o[5]), m22 = det2(q0, o[4], q1, o[2]);
     // H_rr = [q]x^T Omega [q]x = -M [q]x
-    acc.add(kHrr + 0, m02 * q1 - m01 * q2);
-    acc.add(kHrr + 1, m00 * q2 - m02 * q0);
-    acc.add(kHrr + 2, m01 * q0 - m00 * q1);
-    acc.add(kHrr + 3, m10 * q2 - m12 * q0);
-    acc.add(kHrr + 4, m11 * q0 - m10 * q1);
-    acc.add(kHrr + 5, m21 * q0 - m20 * q1);
+    acc.add(kHrr + 0, det2(m02, q1, m01, q2));
+    acc.add(kHrr + 1, det2(m00, q2, m02, q0));
+    acc.add(kHrr + 2, det2(m01, q0, m00, q1));
+    acc.add(kHrr + 3, det2(m10, q2, m12, q0));
+    acc.add(kHrr + 4, det2(m11, q0, m10, q1));
+    acc.add(kHrr + 5, det2(m21, q0, m20, q1));
     acc.add(kHrt + 0, m00);
     acc.add(kHrt + 1, m01);
     acc.add(kHrt + 2, m02);
@@ -283,9 +325,9 @@ __device__ inline void add_point_terms(const T q[3], const T d[3], const T o[6],
     acc.add(kHrt + 8, m22);
 #pragma unroll
     for (int i = 0; i < 6; ++i) acc.add(kHtt + i, o[i]);
-    acc.add(kBr + 0, q1 * u2 - q2 * u1);
-    acc.add(kBr + 1, q2 * u0 - q0 * u2);
-    acc.add(kBr + 2, q0 * u1 - q1 * u0);
+    acc.add(kBr + 0, det2(q1, u2, q2, u1));
+    acc.add(kBr + 1, det2(q2, u0, q0, u2));
+    acc.add(kBr + 2, det2(q0, u1, q1, u0));
     acc.add(kBt + 0, u0);
     acc.add(kBt + 1, u1);
     acc.add(kBt + 2, u2);
@@ -323,19 +365,58 @@ __device__ inline void block_sum_store(double (&v)[NV], double* __restrict__ out
   __syncthreads();
 }
 
+// The two halves of the reduce-scatter's exchange in one instruction per register: after it `a`
+// holds what the lower lanes keep and the upper lanes receive, `b` the rest, so a + b is every
+// lane's kept value plus its partner's copy. HALF 32: lane masks 32, HALF 16: lane masks 16.
+template <int HALF>
+__device__ inline void swap_halves(unsigned& a, unsigned& b) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 r;
+  if constexpr (HALF == 32)
+    r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  else
+    r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r.x;
+  b = r.y;
+}
+
+template <int HALF>
+__device__ inline double exchange_add(double lo, double hi) {
+  unsigned a0 = (unsigned)__double2loint(lo), a1 = (unsigned)__double2hiint(lo);
+  unsigned b0 = (unsigned)__double2loint(hi), b1 = (unsigned)__double2hiint(hi);
+  swap_halves<HALF>(a0, b0);
+  swap_halves<HALF>(a1, b1);
+  return __hiloint2double((int)a1, (int)a0) + __hiloint2double((int)b1, (int)b0);
+}
+
+// FP32 lane sums taken to FP64 by the first exchange: the halves move as floats.
+template <int HALF>
+__device__ inline double exchange_add(float lo, float hi) {
+  unsigned a = __float_as_uint(lo), b = __float_as_uint(hi);
+  swap_halves<HALF>(a, b);
+  return (double)__uint_as_float(a) + (double)__uint_as_float(b);
+}
+
 // Same result shape for up to 32 values with a reduce-scatter butterfly: at the step with
 // lane mask m (32, 16, 8, 4, 2) a lane keeps half of its values (the upper half if its m-bit
 // is set) and adds the partner's copy of that half, so the values left to exchange halve at
-// every step (32 double shuffles in all instead of 6 per value). Lanes 2k and 2k+1 end with
-// the wave total of value k.
-template <int BLOCK, int NV>
-__device__ inline void block_sum_store_rs(double (&v)[32], double* __restrict__ out) {
+// every step. Lanes 2k and 2k+1 end with the wave total of value k. v: the lane's 32 values,
+// FP32 or FP64 (the sums are FP64 either way). The two wide steps swap register halves between
+// lanes (v_permlane32/16_swap: one instruction per register where a shuffle with its select took
+// four; a tile's reduction was 0.11 of the global batch's vector instructions).
+template <int BLOCK, int NV, typename T>
+__device__ inline void block_sum_store_rs(const T (&v)[32], double* __restrict__ out) {
   static_assert(NV <= 32, "at most 32 values");
   constexpr int W = BLOCK / 64;
   __shared__ double sh[W][32];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double s16[16], s[8];
 #pragma unroll
-  for (int step = 0; step < 5; ++step) {
+  for (int j = 0; j < 16; ++j) s16[j] = exchange_add<32>(v[j], v[j + 16]);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) s[j] = exchange_add<16>(s16[j], s16[j + 8]);
+#pragma unroll
+  for (int step = 2; step < 5; ++step) {
     const int m = 32 >> step;
     const int half = 16 >> step;
     const bool upper = (lane & m) != 0;
@@ -344,21 +425,21 @@ __device__ inline void block_sum_store_rs(double (&v)[32], double* __restrict__ 
     const long long up = upper ? -1LL : 0LL;
 #pragma unroll
     for (int j = 0; j < half; ++j) {
-      const long long lo_bits = __double_as_longlong(v[j]);
-      const long long hi_bits = __double_as_longlong(v[j + half]);
+      const long long lo_bits = __double_as_longlong(s[j]);
+      const long long hi_bits = __double_as_longlong(s[j + half]);
       const double send = __longlong_as_double((lo_bits & up) | (hi_bits & ~up));
       const double keep = __longlong_as_double((hi_bits & up) | (lo_bits & ~up));
-      v[j] = keep + __shfl_xor(send, m, 64);
+      s[j] = keep + __shfl_xor(send, m, 64);
     }
   }
-  v[0] += __shfl_xor(v[0], 1, 64);
-  if ((lane & 1) == 0) sh[w][lane >> 1] = v[0];
+  s[0] += __shfl_xor(s[0], 1, 64);
+  if ((lane & 1) == 0) sh[w][lane >> 1] = s[0];
   __syncthreads();
   if (threadIdx.x < NV) {
-    double s = sh[0][threadIdx.x];
+    double r = sh[0][threadIdx.x];
 #pragma unroll
-    for (int k = 1; k < W; ++k) s += sh[k][threadIdx.x];
-    out[threadIdx.x] = s;
+    for (int k = 1; k < W; ++k) r += sh[k][threadIdx.x];
+    out[threadIdx.x] = r;
   }
   __syncthreads();
 }

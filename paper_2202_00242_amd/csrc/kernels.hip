@@ -67,40 +67,38 @@ namespace {
 
 // ------------------------------------------------------------------ phase A: voxel lookup
 
+// The FP32 world-coordinate form (precision baseline): the point to world and into the target
+// frame, both in FP32.
+__device__ inline void naive_point(const RelPose& T, float x, float y, float z, float q[3]) {
+  const float w0 = T.Rs[0] * x + T.Rs[1] * y + T.Rs[2] * z + T.ts[0];
+  const float w1 = T.Rs[3] * x + T.Rs[4] * y + T.Rs[5] * z + T.ts[1];
+  const float w2 = T.Rs[6] * x + T.Rs[7] * y + T.Rs[8] * z + T.ts[2];
+  q[0] = T.Rti[0] * w0 + T.Rti[1] * w1 + T.Rti[2] * w2 + T.tti[0];
+  q[1] = T.Rti[3] * w0 + T.Rti[4] * w1 + T.Rti[5] * w2 + T.tti[1];
+  q[2] = T.Rti[6] * w0 + T.Rti[7] * w1 + T.Rti[8] * w2 + T.tti[2];
+}
+
 // Voxel coordinates of one source point in the target frame, branch-free (saturated, see
-// floor_sat_i32), and the transformed point: q, or q / res when res is a power of two (the
-// caller scales it back). Returns false when the transformed point is not finite.
+// floor_sat_i32). Returns false when the transformed point is not finite.
 template <int PREC, bool DIV>
 __device__ inline bool point_key(const MapView& m, const RelPose& T, float x, float y, float z,
-                                 int k[3], double q[3]) {
+                                 int k[3]) {
   if constexpr (PREC == kNaiveWorld) {
-    // world point in FP32, then into the target frame in FP32
-    const float w0 = T.Rs[0] * x + T.Rs[1] * y + T.Rs[2] * z + T.ts[0];
-    const float w1 = T.Rs[3] * x + T.Rs[4] * y + T.Rs[5] * z + T.ts[1];
-    const float w2 = T.Rs[6] * x + T.Rs[7] * y + T.Rs[8] * z + T.ts[2];
-    const float q0 = T.Rti[0] * w0 + T.Rti[1] * w1 + T.Rti[2] * w2 + T.tti[0];
-    const float q1 = T.Rti[3] * w0 + T.Rti[4] * w1 + T.Rti[5] * w2 + T.tti[1];
-    const float q2 = T.Rti[6] * w0 + T.Rti[7] * w1 + T.Rti[8] * w2 + T.tti[2];
+    float q[3];
+    naive_point(T, x, y, z, q);
     const float ir = (float)m.inv_res;
-    k[0] = floor_sat_i32_f32(q0 * ir);
-    k[1] = floor_sat_i32_f32(q1 * ir);
-    k[2] = floor_sat_i32_f32(q2 * ir);
-    q[0] = q0;
-    q[1] = q1;
-    q[2] = q2;
-    return isfinite(q0 + q1 + q2);
+    for (int a = 0; a < 3; ++a) k[a] = floor_sat_i32_f32(q[a] * ir);
+    return isfinite(q[0] + q[1] + q[2]);
   } else {
+    double q[3];
     if constexpr (DIV) {
       transform_exact(T.R, T.t, x, y, z, q);
       for (int a = 0; a < 3; ++a) k[a] = floor_sat_i32(q[a] / m.res);
-      return isfinite(q[0] + q[1] + q[2]);
-    } else {
-      // q / res exactly (power-of-two res); returned scaled, the inlier phase multiplies by
-      // res (exact again)
+    } else {  // q / res exactly (power-of-two res)
       transform_exact(T.Rk, T.tk, x, y, z, q);
       for (int a = 0; a < 3; ++a) k[a] = floor_sat_i32(q[a]);
-      return isfinite(q[0] + q[1] + q[2]);
     }
+    return isfinite(q[0] + q[1] + q[2]);
   }
 }
 
@@ -151,58 +149,94 @@ struct Chunk {
   }
 };
 
-// One queued inlier: its transformed point (FP64, target frame), voxel record, point index.
+// One queued inlier: its position (the inlier phase transforms it again in FP64: 18 operations
+// for the points that hit instead of 24 more bytes of LDS for each), voxel record, point index.
 struct alignas(16) QueueEntry {
-  double q0, q1, q2;
+  float x, y, z;
   int rec;
-  int point;
+};
+struct Queue {
+  QueueEntry* e;
+  int* point;
 };
 
 // Phase A of a wave-chunk: lane l resolves the points base + u*64 + l, u < U (positions in
 // c), with all their lookups in flight together. Hits are appended (in (u, lane) order) to the
-// wave's queue: transformed point, voxel record index (MapView::rec) and point index; cnt
+// wave's queue: position, voxel record index (MapView::rec) and point index; cnt
 // stays wave-uniform. corr receives voxel ids.
 // The next chunk's positions (nxt, at next_base) are loaded here, after this chunk's lookups
 // are issued: vector-memory counters retire in issue order, so loads issued earlier would have
 // to complete before the lookups could be consumed.
-template <int PREC, bool DIV, int LAYOUT, int U, bool GRAD = false>
+//
+// FAST (batches): the voxel comes from an FP32 transform in voxel units relative to the map's box
+// (9 FMA, RelPose::Af/sf), and is the definition's FP64 voxel whenever no coordinate lies within
+// the transform's error bound of a voxel face (RelPose::thr, from the source's bounding box); a
+// chunk row with a point that close (about 1 in 1,000 points at 0.5 m and 100 m) computes those
+// points' voxels in FP64. VALU issue bounds this phase: the FP64 key alone is 33 of its 63
+// instructions per point, the FP32 one is 20 (FP64 issues at the unpacked FP32 rate here, but the
+// definition's order allows no FMA).
+template <int PREC, bool DIV, int LAYOUT, int U, bool FAST, bool GRAD = false>
 __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U>& c,
                                Chunk<U>& nxt, const Planes& P, int next_base, int base, int end,
-                               int lane, QueueEntry* qe, int& cnt, int* __restrict__ corr,
+                               int lane, const Queue& qe, int& cnt, int* __restrict__ corr,
                                unsigned& fl, float* __restrict__ gz = nullptr) {
   const float* x = c.x;
   const float* y = c.y;
   const float* z = c.z;
-  bool valid[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) valid[u] = base + u * 64 + lane < end;
   unsigned slot[U], klo[U], khi[U];
   int st[U], id[U];  // st: 0 probing, 1 hit, 2 miss
-  double q[U][3];    // transformed point (target frame)
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     id[u] = -1;
-    int k[3];
-    const bool finite = point_key<PREC, DIV>(m, T, x[u], y[u], z[u], k, q[u]);
-    if (valid[u] && !finite) fl |= kFlagNonFinite;
-    const unsigned dx = (unsigned)k[0] - (unsigned)m.lo[0];
-    const unsigned dy = (unsigned)k[1] - (unsigned)m.lo[1];
-    const unsigned dz = (unsigned)k[2] - (unsigned)m.lo[2];
+    const bool valid = base + u * 64 + lane < end;
+    unsigned dx, dy, dz;  // voxel relative to the map's box
+    bool inbox;
+    auto exact = [&]() {
+      int k[3];
+      bool finite;
+      if constexpr (FAST) {  // rare: no code of its own per key arithmetic
+        finite = m.pow2 ? point_key<PREC, false>(m, T, x[u], y[u], z[u], k)
+                        : point_key<PREC, true>(m, T, x[u], y[u], z[u], k);
+      } else {
+        finite = point_key<PREC, DIV>(m, T, x[u], y[u], z[u], k);
+      }
+      if (valid && !finite) fl |= kFlagNonFinite;
+      dx = finite ? (unsigned)k[0] - (unsigned)m.lo[0] : ~0u;
+      dy = (unsigned)k[1] - (unsigned)m.lo[1];
+      dz = (unsigned)k[2] - (unsigned)m.lo[2];
+    };
+    if constexpr (FAST) {
+      float s[3], f[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        s[a] = fmaf(T.Af[3 * a], x[u],
+                    fmaf(T.Af[3 * a + 1], y[u], fmaf(T.Af[3 * a + 2], z[u], T.sf[a])));
+        f[a] = fabsf(__builtin_amdgcn_fractf(s[a]) - 0.5f);
+      }
+      dx = (unsigned)floor_i32_f32(s[0]);
+      dy = (unsigned)floor_i32_f32(s[1]);
+      dz = (unsigned)floor_i32_f32(s[2]);
+      // a NaN coordinate fails the comparison (the box of such a cloud is infinite: thr < 0)
+      const bool sure = fmaxf(fmaxf(f[0], f[1]), f[2]) <= T.thr;
+      if (__ballot(!sure) != 0ull) {
+        if (!sure) exact();
+      }
+    } else {
+      exact();
+    }
     // outside the map's voxel bounding box (or out of range, or not finite): a miss
-    const bool inbox = valid[u] && finite && dx < (unsigned)m.ext[0] &&
-                       dy < (unsigned)m.ext[1] && dz < (unsigned)m.ext[2];
+    inbox = valid && dx < (unsigned)m.ext[0] && dy < (unsigned)m.ext[1] && dz < (unsigned)m.ext[2];
     if constexpr (LAYOUT == kLayoutGrid) {
       // 24-bit multiplies: a grid has fewer than 2^24 bricks
-      slot[u] = __umul24(__umul24(dx >> 2, (unsigned)m.gby) + (dy >> 2), (unsigned)m.gbz) +
-                (dz >> 1);
-      klo[u] = bit_in_brick(dx, dy, dz);
+      slot[u] = mad24(mad24(dx >> 2, (unsigned)m.gby, dy >> 2), (unsigned)m.gbz, dz >> 1);
+      klo[u] = bit_in_brick_mod32(dx, dy, dz);
       khi[u] = 0;
     } else if constexpr (LAYOUT == kLayoutHash32) {
       klo[u] = (dx << (m.by + m.bz)) | (dy << m.bz) | dz;
       khi[u] = 0;
       slot[u] = hash32(klo[u]) & m.mask;
     } else {
-      const long long pk = pack_key(k[0], k[1], k[2]);
+      const long long pk = pack_key((int)dx + m.lo[0], (int)dy + m.lo[1], (int)dz + m.lo[2]);
       klo[u] = (unsigned)pk;
       khi[u] = (unsigned)((unsigned long long)pk >> 32);
       slot[u] = hash64(pk) & m.mask;
@@ -223,10 +257,9 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
     nxt.load(P, next_base, lane);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const unsigned hit = (br[u].x >> klo[u]) & 1u;
-      const int pos = (int)br[u].y + __popc(br[u].x & ((1u << klo[u]) - 1u));
-      id[u] = hit ? pos : -1;
-      st[u] = 2 - (int)hit;
+      const unsigned hit = __builtin_amdgcn_ubfe(br[u].x, klo[u], 1);
+      id[u] = (int)br[u].y + __popc(__builtin_amdgcn_ubfe(br[u].x, 0, klo[u]));
+      st[u] = hit != 0u ? 1 : 2;
     }
   } else {
     nxt.load(P, next_base, lane);
@@ -271,7 +304,7 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
   if (corr) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (valid[u]) {
+      if (base + u * 64 + lane < end) {
         int v = -1;
         if (st[u] == 1) v = (LAYOUT == kLayoutGrid) ? gbl(m.rec_id)[id[u]] : id[u];
         gblw(corr)[base + u * 64 + lane] = v;
@@ -280,7 +313,7 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
   if constexpr (GRAD) {  // a point without a voxel has no gradient
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (valid[u] && st[u] != 1) {
+      if (base + u * 64 + lane < end && st[u] != 1) {
         const gptr<float> g = gblw(gz) + 3 * (size_t)(unsigned)(base + u * 64 + lane);
         g[0] = 0.0f;
         g[1] = 0.0f;
@@ -294,8 +327,10 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
     if (h) {
       const int pos = cnt + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mk >> 32),
                                                           __builtin_amdgcn_mbcnt_lo((unsigned)mk, 0u));
-      if constexpr (PREC != kCountOnly)
-        qe[pos] = QueueEntry{q[u][0], q[u][1], q[u][2], id[u], base + u * 64 + lane};
+      if constexpr (PREC != kCountOnly) {
+        qe.e[pos] = QueueEntry{x[u], y[u], z[u], id[u]};
+        qe.point[pos] = base + u * 64 + lane;
+      }
     }
     cnt += __popcll(mk);
   }
@@ -311,27 +346,25 @@ using RealOf = typename std::conditional<PREC == kMathFp64, double, float>::type
 template <int PREC, bool LIN, bool AOS, class Acc>
 __device__ inline void inlier_terms(const MapView& m, const RelPose& T,
                                     const float* __restrict__ cov, int n, QueueEntry e,
-                                    double qscale, Acc& acc, int& nin, unsigned& fl) {
+                                    int point, Acc& acc, int& nin, unsigned& fl) {
   using Real = RealOf<PREC>;
   float c[6];
   if constexpr (AOS) {  // interleaved [n][6] (24 bytes): three 8-byte loads
-    const float2* c2 = gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)e.point;
+    const float2* c2 = gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)point;
     const float2 c01 = c2[0], c23 = c2[1], c45 = c2[2];
     c[0] = c01.x, c[1] = c01.y, c[2] = c23.x, c[3] = c23.y, c[4] = c45.x, c[5] = c45.y;
   } else {  // the caller's planes [6][n]
 #pragma unroll
-    for (int a = 0; a < 6; ++a) c[a] = gbl(cov + (size_t)a * n)[(unsigned)e.point];
+    for (int a = 0; a < 6; ++a) c[a] = gbl(cov + (size_t)a * n)[(unsigned)point];
   }
   const VoxelData vd = gbl(m.rec)[(unsigned)e.rec];
-  // queued as q / res when res is a power of two (qscale = res, exact) else q (qscale = 1)
-  const double q[3] = {e.q0 * qscale, e.q1 * qscale, e.q2 * qscale};
   Real qq[3], d[3];
-  if constexpr (PREC == kNaiveWorld) {  // q holds the FP32 world-path point
-    for (int a = 0; a < 3; ++a) {
-      qq[a] = (float)q[a];
-      d[a] = (float)vd.mean[a] - qq[a];
-    }
+  if constexpr (PREC == kNaiveWorld) {
+    naive_point(T, e.x, e.y, e.z, qq);
+    for (int a = 0; a < 3; ++a) d[a] = (float)vd.mean[a] - qq[a];
   } else {
+    double q[3];
+    transform_exact(T.R, T.t, e.x, e.y, e.z, q);
     for (int a = 0; a < 3; ++a) {
       qq[a] = (Real)q[a];
       d[a] = (Real)(vd.mean[a] - q[a]);
@@ -339,12 +372,9 @@ __device__ inline void inlier_terms(const MapView& m, const RelPose& T,
   }
   Real o[6];
   const bool ok = fused_inverse<Real>(T.R, vd.cov, c, o);
-  if (!ok) {
-    fl |= kFlagNonFinite;
-    return;
-  }
+  fl |= ok ? 0u : (unsigned)kFlagNonFinite;
   add_point_terms<LIN>(qq, d, o, acc);
-  ++nin;
+  nin += ok ? 1 : 0;
 }
 
 // Gradient terms of one inlier (the backward of Eq. (2) with its correspondence held):
@@ -361,22 +391,20 @@ struct GradAcc {
 
 template <int PREC>
 __device__ inline void inlier_grad(const MapView& m, const RelPose& T,
-                                   const float* __restrict__ xyz, const float* __restrict__ cov,
-                                   int n, QueueEntry e, double qscale, GradAcc& acc, int& nin,
-                                   unsigned& fl, float* __restrict__ gz) {
+                                   const float* __restrict__ cov, QueueEntry e, int point,
+                                   GradAcc& acc, int& nin, unsigned& fl,
+                                   float* __restrict__ gz) {
   using Real = RealOf<PREC>;
   float c[6];
-  const float2* c2 = gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)e.point;
+  const float2* c2 = gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)point;
   const float2 c01 = c2[0], c23 = c2[1], c45 = c2[2];
   c[0] = c01.x, c[1] = c01.y, c[2] = c23.x, c[3] = c23.y, c[4] = c45.x, c[5] = c45.y;
-  const float mx = gbl(xyz)[(unsigned)e.point];
-  const float my = gbl(xyz + (size_t)n)[(unsigned)e.point];
-  const float mz = gbl(xyz + 2 * (size_t)n)[(unsigned)e.point];
   const VoxelData vd = gbl(m.rec)[(unsigned)e.rec];
-  const double q[3] = {e.q0 * qscale, e.q1 * qscale, e.q2 * qscale};
+  double q[3];
+  transform_exact(T.R, T.t, e.x, e.y, e.z, q);
   Real d[3];
   for (int a = 0; a < 3; ++a) d[a] = (Real)(vd.mean[a] - q[a]);
-  const gptr<float> g = gblw(gz) + 3 * (size_t)(unsigned)e.point;
+  const gptr<float> g = gblw(gz) + 3 * (size_t)(unsigned)point;
   Real o[6];
   if (!fused_inverse<Real>(T.R, vd.cov, c, o)) {
     fl |= kFlagNonFinite;
@@ -388,18 +416,18 @@ __device__ inline void inlier_grad(const MapView& m, const RelPose& T,
   Real R[9];
 #pragma unroll
   for (int i = 0; i < 9; ++i) R[i] = (Real)T.R[i];
-  const Real u0 = o[0] * d[0] + o[1] * d[1] + o[2] * d[2];
-  const Real u1 = o[1] * d[0] + o[3] * d[1] + o[4] * d[2];
-  const Real u2 = o[2] * d[0] + o[4] * d[1] + o[5] * d[2];
-  const Real w0 = R[0] * u0 + R[3] * u1 + R[6] * u2;
-  const Real w1 = R[1] * u0 + R[4] * u1 + R[7] * u2;
-  const Real w2 = R[2] * u0 + R[5] * u1 + R[8] * u2;
-  const Real a0 = (Real)mx + (c[0] * w0 + c[1] * w1 + c[2] * w2);
-  const Real a1 = (Real)my + (c[1] * w0 + c[3] * w1 + c[4] * w2);
-  const Real a2 = (Real)mz + (c[2] * w0 + c[4] * w1 + c[5] * w2);
-  acc.v[0] += 2.0 * (double)(w1 * a2 - w2 * a1);
-  acc.v[1] += 2.0 * (double)(w2 * a0 - w0 * a2);
-  acc.v[2] += 2.0 * (double)(w0 * a1 - w1 * a0);
+  const Real u0 = dot3(o[0], d[0], o[1], d[1], o[2], d[2]);
+  const Real u1 = dot3(o[1], d[0], o[3], d[1], o[4], d[2]);
+  const Real u2 = dot3(o[2], d[0], o[4], d[1], o[5], d[2]);
+  const Real w0 = dot3(R[3], u1, R[0], u0, R[6], u2);
+  const Real w1 = dot3(R[4], u1, R[1], u0, R[7], u2);
+  const Real w2 = dot3(R[5], u1, R[2], u0, R[8], u2);
+  const Real a0 = (Real)e.x + dot3((Real)c[1], w1, (Real)c[0], w0, (Real)c[2], w2);
+  const Real a1 = (Real)e.y + dot3((Real)c[3], w1, (Real)c[1], w0, (Real)c[4], w2);
+  const Real a2 = (Real)e.z + dot3((Real)c[4], w1, (Real)c[2], w0, (Real)c[5], w2);
+  acc.v[0] += 2.0 * (double)det2(w1, a2, w2, a1);
+  acc.v[1] += 2.0 * (double)det2(w2, a0, w0, a2);
+  acc.v[2] += 2.0 * (double)det2(w0, a1, w1, a0);
   acc.v[3] -= 2.0 * (double)w0;
   acc.v[4] -= 2.0 * (double)w1;
   acc.v[5] -= 2.0 * (double)w2;
@@ -411,14 +439,13 @@ __device__ inline void inlier_grad(const MapView& m, const RelPose& T,
 
 // Phase B of one queued inlier: linearization / evaluation terms, or gradient terms.
 template <int PREC, bool LIN, bool AOS, bool GRAD, class Acc>
-__device__ inline void phase_b(const MapView& m, const RelPose& T, const float* __restrict__ xyz,
-                               const float* __restrict__ cov, int n, QueueEntry e,
-                               double qscale, Acc& acc, int& nin, unsigned& fl,
+__device__ inline void phase_b(const MapView& m, const RelPose& T, const float* __restrict__ cov,
+                               int n, const Queue& qe, int i, Acc& acc, int& nin, unsigned& fl,
                                float* __restrict__ gz) {
   if constexpr (GRAD)
-    inlier_grad<PREC>(m, T, xyz, cov, n, e, qscale, acc, nin, fl, gz);
+    inlier_grad<PREC>(m, T, cov, qe.e[i], qe.point[i], acc, nin, fl, gz);
   else
-    inlier_terms<PREC, LIN, AOS>(m, T, cov, n, e, qscale, acc, nin, fl);
+    inlier_terms<PREC, LIN, AOS>(m, T, cov, n, qe.e[i], qe.point[i], acc, nin, fl);
 }
 
 // ------------------------------------------------------------------ one tile
@@ -445,19 +472,19 @@ template <int PREC, bool LIN, int BLOCK, int U, bool DIV, int LAYOUT, bool AOS, 
 __device__ inline void tile_body(const MapView& m, const RelPose& T,
                                  const float* __restrict__ xyz, const float* __restrict__ cov,
                                  int n, int start, int end, int* __restrict__ corr, Acc& acc,
-                                 int& nin, unsigned& fl, QueueEntry* qe,
+                                 int& nin, unsigned& fl, const Queue& qe,
                                  float* __restrict__ gz) {
+  constexpr bool FAST = AOS && PREC != kNaiveWorld;  // only a batch has the error bound
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const Planes P = make_planes(xyz, n);
-  const double qscale = (DIV || PREC == kNaiveWorld) ? 1.0 : m.res;
   int cnt = 0;
   // positions double-buffered: chunk c + 1 is loaded while chunk c is resolved
   Chunk<U> cur;
   cur.load(P, start + w * 64 * U, lane);
   for (int base = start + w * 64 * U; base < end; base += BLOCK * U) {
     Chunk<U> nxt;
-    resolve<PREC, DIV, LAYOUT, U, GRAD>(m, T, cur, nxt, P, base + BLOCK * U, base, end, lane,
-                                        qe, cnt, corr, fl, gz);
+    resolve<PREC, DIV, LAYOUT, U, FAST, GRAD>(m, T, cur, nxt, P, base + BLOCK * U, base, end,
+                                              lane, qe, cnt, corr, fl, gz);
     cur = nxt;
     if constexpr (PREC == kCountOnly) {  // overlap: count the hits, no inlier phase
       if (lane == 0) nin += cnt;
@@ -468,20 +495,19 @@ __device__ inline void tile_body(const MapView& m, const RelPose& T,
       wave_sync();
       int head = 0;
       for (; cnt - head >= 64; head += 64)
-        phase_b<PREC, LIN, AOS, GRAD>(m, T, xyz, cov, n, qe[head + lane], qscale, acc, nin, fl,
-                                      gz);
+        phase_b<PREC, LIN, AOS, GRAD>(m, T, cov, n, qe, head + lane, acc, nin, fl, gz);
       const int rem = cnt - head;
       // move the tail to the front (through registers: every lane reads before any writes)
       const int src = min(head + lane, cnt - 1);
-      const double e0 = qe[src].q0, e1 = qe[src].q1, e2 = qe[src].q2;
-      const int er = qe[src].rec, ep = qe[src].point;
+      const float ex = qe.e[src].x, ey = qe.e[src].y, ez = qe.e[src].z;
+      const int er = qe.e[src].rec, ep = qe.point[src];
       wave_sync();
       if (lane < rem) {
-        qe[lane].q0 = e0;
-        qe[lane].q1 = e1;
-        qe[lane].q2 = e2;
-        qe[lane].rec = er;
-        qe[lane].point = ep;
+        qe.e[lane].x = ex;
+        qe.e[lane].y = ey;
+        qe.e[lane].z = ez;
+        qe.e[lane].rec = er;
+        qe.point[lane] = ep;
       }
       cnt = rem;
       wave_sync();
@@ -489,8 +515,7 @@ __device__ inline void tile_body(const MapView& m, const RelPose& T,
   }
   wave_sync();
   if constexpr (PREC != kCountOnly)
-    if (lane < cnt)
-      phase_b<PREC, LIN, AOS, GRAD>(m, T, xyz, cov, n, qe[lane], qscale, acc, nin, fl, gz);
+    if (lane < cnt) phase_b<PREC, LIN, AOS, GRAD>(m, T, cov, n, qe, lane, acc, nin, fl, gz);
   wave_sync();
 }
 
@@ -502,23 +527,32 @@ __device__ inline void process_tile(const MapView& m, const RelPose& T,
                                     const float* __restrict__ cov, int n, int start, int end,
                                     int* __restrict__ corr, double* __restrict__ partial,
                                     unsigned* flags, float* __restrict__ gz = nullptr) {
-  __shared__ QueueEntry s_qe[BLOCK / 64][queue_cap<U>()];
+  constexpr int kQueue = PREC == kCountOnly ? 1 : queue_cap<U>();
+  __shared__ QueueEntry s_qe[BLOCK / 64][kQueue];
+  __shared__ int s_qp[BLOCK / 64][kQueue];
   const int w = threadIdx.x >> 6;
   typename std::conditional<GRAD, GradAcc, typename AccOf<PREC>::type>::type acc;
   acc.zero();
   int nin = 0;
   unsigned fl = 0;
-  QueueEntry* qe = s_qe[w];
-  // uniform per tile: lookup structure and key arithmetic (multiply when res is a power of 2)
-#define VGICP_TILE(DIV, LAYOUT)                                                         \
-  tile_body<PREC, LIN, BLOCK, U, DIV, LAYOUT, AOS, GRAD>(m, T, xyz, cov, n, start, end, corr, \
-                                                         acc, nin, fl, qe, gz)
+  const Queue qe{s_qe[w], s_qp[w]};
+  // uniform per tile: lookup structure and, without the FP32 lookup, key arithmetic (a multiply
+  // when res is a power of 2)
+#define VGICP_TILE(LAYOUT)                                                              \
+  do {                                                                                  \
+    if ((AOS && PREC != kNaiveWorld) || m.pow2)                                         \
+      tile_body<PREC, LIN, BLOCK, U, false, LAYOUT, AOS, GRAD>(m, T, xyz, cov, n, start, end, \
+                                                               corr, acc, nin, fl, qe, gz);   \
+    else                                                                                \
+      tile_body<PREC, LIN, BLOCK, U, true, LAYOUT, AOS, GRAD>(m, T, xyz, cov, n, start, end,  \
+                                                              corr, acc, nin, fl, qe, gz);    \
+  } while (0)
   if (m.bricks) {
-    if (m.pow2) VGICP_TILE(false, kLayoutGrid); else VGICP_TILE(true, kLayoutGrid);
+    VGICP_TILE(kLayoutGrid);
   } else if (m.slots32) {
-    if (m.pow2) VGICP_TILE(false, kLayoutHash32); else VGICP_TILE(true, kLayoutHash32);
+    VGICP_TILE(kLayoutHash32);
   } else {
-    if (m.pow2) VGICP_TILE(false, kLayoutHash64); else VGICP_TILE(true, kLayoutHash64);
+    VGICP_TILE(kLayoutHash64);
   }
 #undef VGICP_TILE
   if constexpr (GRAD) {
@@ -528,15 +562,17 @@ __device__ inline void process_tile(const MapView& m, const RelPose& T,
     v[6] = (double)nin;
     block_sum_store<BLOCK, 7>(v, partial);
   } else if constexpr (LIN) {
-    double v[32];
+    // the lane sums' own type (a lane's inlier count is exact in either)
+    using Lane = decltype(acc.get(0));
+    Lane v[32];
 #pragma unroll
     for (int i = 0; i < kNumAcc; ++i) v[i] = acc.get(i);
-    v[kNumAcc] = (double)nin;
+    v[kNumAcc] = (Lane)nin;
 #pragma unroll
-    for (int i = kPartialStride; i < 32; ++i) v[i] = 0.0;
+    for (int i = kPartialStride; i < 32; ++i) v[i] = 0;
     block_sum_store_rs<BLOCK, kPartialStride>(v, partial);
   } else {
-    double v[2] = {acc.get(kE), (double)nin};
+    double v[2] = {(double)acc.get(kE), (double)nin};
     block_sum_store<BLOCK, 2>(v, partial + kE);
   }
   if (fl) atomicOr(flags, fl);
@@ -711,18 +747,18 @@ __global__ __launch_bounds__(BLOCK) void backward_tile_kernel(
       }
       continue;
     }
-    const Real u0 = o[0] * d0 + o[1] * d1 + o[2] * d2;
-    const Real u1 = o[1] * d0 + o[3] * d1 + o[4] * d2;
-    const Real u2 = o[2] * d0 + o[4] * d1 + o[5] * d2;
-    const Real w0 = R[0] * u0 + R[3] * u1 + R[6] * u2;
-    const Real w1 = R[1] * u0 + R[4] * u1 + R[7] * u2;
-    const Real w2 = R[2] * u0 + R[5] * u1 + R[8] * u2;
-    const Real a0 = (Real)x + (c[0] * w0 + c[1] * w1 + c[2] * w2);
-    const Real a1 = (Real)y + (c[1] * w0 + c[3] * w1 + c[4] * w2);
-    const Real a2 = (Real)z + (c[2] * w0 + c[4] * w1 + c[5] * w2);
-    acc[0] += 2.0 * (double)(w1 * a2 - w2 * a1);
-    acc[1] += 2.0 * (double)(w2 * a0 - w0 * a2);
-    acc[2] += 2.0 * (double)(w0 * a1 - w1 * a0);
+    const Real u0 = dot3(o[1], d1, o[0], d0, o[2], d2);
+    const Real u1 = dot3(o[3], d1, o[1], d0, o[4], d2);
+    const Real u2 = dot3(o[4], d1, o[2], d0, o[5], d2);
+    const Real w0 = dot3(R[3], u1, R[0], u0, R[6], u2);
+    const Real w1 = dot3(R[4], u1, R[1], u0, R[7], u2);
+    const Real w2 = dot3(R[5], u1, R[2], u0, R[8], u2);
+    const Real a0 = (Real)x + dot3((Real)c[1], w1, (Real)c[0], w0, (Real)c[2], w2);
+    const Real a1 = (Real)y + dot3((Real)c[3], w1, (Real)c[1], w0, (Real)c[4], w2);
+    const Real a2 = (Real)z + dot3((Real)c[4], w1, (Real)c[2], w0, (Real)c[5], w2);
+    acc[0] += 2.0 * (double)det2(w1, a2, w2, a1);
+    acc[1] += 2.0 * (double)det2(w2, a0, w0, a2);
+    acc[2] += 2.0 * (double)det2(w0, a1, w1, a0);
     acc[3] -= 2.0 * (double)w0;
     acc[4] -= 2.0 * (double)w1;
     acc[5] -= 2.0 * (double)w2;
@@ -782,6 +818,28 @@ __global__ void backward_finalize_kernel(const double* __restrict__ partials, in
 
 // ------------------------------------------------------------------ batches
 
+// The FP32 lookup transform and its error bound. With u = 2^-24, A = R / res, s' = t / res - lo and
+// M = sum_j |A_j| max|mu_j| + |s'|: rounding A and s' moves s by at most u M, the three FMAs by
+// u M (1 + 3 u) each, so s is within 4.01 u M of the real value; the definition's FP64 value is
+// within 2^-49 of the magnitudes it sums. 6 u M leaves a third to spare.
+__device__ inline void fast_lookup(const MapView& m, const float* bx, RelPose& o) {
+  double worst = 0.0;
+  for (int r = 0; r < 3; ++r) {
+    const double tk = o.t[r] * m.inv_res, s = tk - (double)m.lo[r];
+    double M = fabs(s);
+    for (int c = 0; c < 3; ++c) {
+      const double A = o.R[3 * r + c] * m.inv_res;
+      M += fabs(A) * fmax(fabs((double)bx[c]), fabs((double)bx[3 + c]));
+      o.Af[3 * r + c] = (float)A;
+    }
+    o.sf[r] = (float)s;
+    const double eps = 0x1p-24 * 6.0 * M + 0x1p-48 * (M + fabs(tk) + fabs((double)m.lo[r]));
+    worst = eps > worst || !(eps >= 0.0) ? eps : worst;  // keeps a NaN
+    if (!(worst >= 0.0)) break;
+  }
+  o.thr = worst < 0.25 ? (float)(0.5 - worst - 0x1p-23) : -1.0f;
+}
+
 // Per factor: the relative pose, and whether the source's bounding box (its local frame, the
 // eight corners moved by T_ts in FP64 and widened by a margin far above the rounding of any
 // point's transform) misses the voxel box of the map: then no point can fall in a voxel and the
@@ -800,6 +858,7 @@ __global__ void batch_prep_kernel(const FactorView* __restrict__ F, int nF,
                    F[f].map.inv_res, o);
   if (allow_skip && boxes) {
     const float* bx = boxes + 6LL * F[f].source_cloud;
+    fast_lookup(F[f].map, bx, o);
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     bool finite = true;
     for (int c = 0; c < 8; ++c) {
