@@ -598,7 +598,6 @@ struct vgicp_batch_s {
   int device = 0;
   int F = 0, P = 0;
   std::vector<FactorView> hf;       // host copy (tile_base/ntiles follow the schedule)
-  std::vector<int> target_of;       // map index per factor
   std::vector<vgicp_cloud> clouds;  // the caller's clouds (source of the batch's copies)
   std::vector<int64_t> cov6_offset; // per cloud: first point in the copies
   std::vector<double> cloud_cell;   // per cloud: cell of its spatial order (finest target res)
@@ -629,7 +628,7 @@ struct vgicp_batch_s {
   double *d_lm_A = nullptr, *d_lm_diag = nullptr, *d_lm_x = nullptr, *d_lm_dinv = nullptr;
   double *d_lm_Hc = nullptr, *d_lm_bc = nullptr, *d_lm_cand = nullptr, *d_lm_lambda = nullptr;
   int *d_lm_pos = nullptr, *d_lm_accept = nullptr;
-  vgicp_schedule sched{256, 8192, 2, 4};
+  vgicp_schedule sched{256, 8192, 4, 4};  // 4 blocks of 4 waves: the batch kernel's 16 waves per CU
   FactorView* d_factors = nullptr;
   RelPose* d_rel = nullptr;
   WorkItem* d_items = nullptr;
@@ -691,9 +690,13 @@ bool valid_schedule(const vgicp_schedule& s) {
          s.blocks_per_cu <= 16 && (s.lookahead == 2 || s.lookahead == 4 || s.lookahead == 8);
 }
 
-// Splits every factor into tiles and orders the work: factors are grouped by target map, the
-// groups are dealt to the XCD queues by decreasing size onto the least-loaded queue (LPT), and
-// inside a queue the tiles of a group are consecutive.
+// Splits every factor into tiles and orders the work: factors are grouped by source cloud (its
+// positions and covariances, the larger part of a factor's traffic, then stay in one XCD's L2 while
+// its factors run; grouped by target map the global batch took 1,318 us instead of 1,269 and the
+// overlap matrix 1,499 instead of 1,467), a group above 1/32 of the batch is cut into pieces (one
+// scan against many maps would otherwise lie in a single queue), the groups are dealt to the XCD
+// queues by decreasing size onto the least-loaded queue (LPT), and inside a queue the tiles of a
+// group are consecutive.
 vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
   const int tile = sc.tile;
   std::vector<int> ntiles(b->F), base(b->F);
@@ -706,13 +709,21 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
     base[f] = (int)total;
     total += nt;
   }
-  std::map<int, std::vector<int>> groups;
-  for (int f = 0; f < b->F; ++f) groups[b->target_of[f]].push_back(f);
-  std::vector<std::pair<int64_t, int>> gsz;
-  for (auto& kv : groups) {
-    int64_t pts = 0;
-    for (int f : kv.second) pts += b->hf[f].n;
-    gsz.push_back({pts, kv.first});
+  std::vector<int> by_source(b->F);
+  for (int f = 0; f < b->F; ++f) by_source[f] = f;
+  std::stable_sort(by_source.begin(), by_source.end(),
+                   [&](int p, int q) { return b->hf[p].source_cloud < b->hf[q].source_cloud; });
+  const int64_t most = b->total_points / (4 * kNumXcd);
+  std::vector<std::vector<int>> groups;
+  std::vector<std::pair<int64_t, int>> gsz;  // points, group
+  for (int f : by_source) {
+    if (groups.empty() || b->hf[groups.back().back()].source_cloud != b->hf[f].source_cloud ||
+        gsz.back().first + b->hf[f].n > most) {
+      gsz.push_back({0, (int)groups.size()});
+      groups.emplace_back();
+    }
+    groups.back().push_back(f);
+    gsz.back().first += b->hf[f].n;
   }
   std::stable_sort(gsz.begin(), gsz.end(),
                    [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& c) {
@@ -748,7 +759,7 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
       return hip_fail(e, "hipMalloc (work items)");
     b->items_cap = items.size();
   }
-  const size_t np = (size_t)std::max<int64_t>(total, 1) * kPartialStride;
+  const size_t np = (size_t)std::max<int64_t>(total, 1) * (size_t)(sc.block / 64) * kPartialStride;
   if (np > b->partials_cap) {
     (void)hipFree(b->d_partials);
     b->d_partials = nullptr;
@@ -764,7 +775,8 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
     return hip_fail(e, "upload schedule");
   b->total_tiles = (int)total;
   const int cus = device_cu_count(b->device);
-  b->grid = ((cus * sc.blocks_per_cu + kNumXcd - 1) / kNumXcd) * kNumXcd;
+  const int blocks = cus * sc.blocks_per_cu * (sc.block / 256);
+  b->grid = ((blocks + kNumXcd - 1) / kNumXcd) * kNumXcd;
   b->sched = sc;
   b->drop_graphs();
   return VGICP_OK;
@@ -784,6 +796,8 @@ BatchLaunch make_launch(vgicp_batch b, const double* poses, int precision, bool 
   L.flags = device_flags(b->device);
   L.F = b->F;
   L.grid = b->grid;
+  L.cus = std::max(device_cu_count(b->device), kNumXcd);
+  L.total_tiles = b->total_tiles;
   L.block = b->sched.block;
   L.tile = b->sched.tile;
   L.lookahead = b->sched.lookahead;
@@ -933,7 +947,6 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
   b->F = n_factors;
   b->P = n_poses;
   b->hf.resize(n_factors);
-  b->target_of.resize(n_factors);
   b->clouds.assign(clouds, clouds + n_clouds);
   b->cov6_offset.resize(n_clouds);
   int64_t cov6_points = 0;
@@ -976,14 +989,13 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
     v.gbase = b->gpts_total;
     b->gpts_total += v.n;
     b->hf[f] = v;
-    b->target_of[f] = fc.target_map;
     b->total_points += v.n;
   }
   const size_t F1 = (size_t)std::max(n_factors, 1);
   if ((e = hipMalloc(&b->d_factors, F1 * sizeof(FactorView))) ||
       (e = hipMalloc(&b->d_rel, F1 * sizeof(RelPose))) ||
       (e = hipMalloc(&b->d_seg, (kNumXcd + 1) * sizeof(int))) ||
-      (e = hipMalloc(&b->d_heads, kNumXcd * sizeof(unsigned long long)))) {
+      (e = hipMalloc(&b->d_heads, kNumXcd * kHeadStride * sizeof(unsigned long long)))) {
     vgicp_batch_destroy(b);
     return hip_fail(e, "hipMalloc (batch)");
   }

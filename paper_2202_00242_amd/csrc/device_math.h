@@ -404,12 +404,9 @@ __device__ inline double exchange_add(float lo, float hi) {
 // FP32 or FP64 (the sums are FP64 either way). The two wide steps swap register halves between
 // lanes (v_permlane32/16_swap: one instruction per register where a shuffle with its select took
 // four; a tile's reduction was 0.11 of the global batch's vector instructions).
-template <int BLOCK, int NV, typename T>
-__device__ inline void block_sum_store_rs(const T (&v)[32], double* __restrict__ out) {
-  static_assert(NV <= 32, "at most 32 values");
-  constexpr int W = BLOCK / 64;
-  __shared__ double sh[W][32];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+template <typename T>
+__device__ inline double wave_sum_rs(const T (&v)[32]) {
+  const int lane = threadIdx.x & 63;
   double s16[16], s[8];
 #pragma unroll
   for (int j = 0; j < 16; ++j) s16[j] = exchange_add<32>(v[j], v[j + 16]);
@@ -432,8 +429,17 @@ __device__ inline void block_sum_store_rs(const T (&v)[32], double* __restrict__
       s[j] = keep + __shfl_xor(send, m, 64);
     }
   }
-  s[0] += __shfl_xor(s[0], 1, 64);
-  if ((lane & 1) == 0) sh[w][lane >> 1] = s[0];
+  return s[0] + __shfl_xor(s[0], 1, 64);
+}
+
+template <int BLOCK, int NV, typename T>
+__device__ inline void block_sum_store_rs(const T (&v)[32], double* __restrict__ out) {
+  static_assert(NV <= 32, "at most 32 values");
+  constexpr int W = BLOCK / 64;
+  __shared__ double sh[W][32];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const double s = wave_sum_rs(v);
+  if ((lane & 1) == 0) sh[w][lane >> 1] = s;
   __syncthreads();
   if (threadIdx.x < NV) {
     double r = sh[0][threadIdx.x];
@@ -442,6 +448,18 @@ __device__ inline void block_sum_store_rs(const T (&v)[32], double* __restrict__
     out[threadIdx.x] = r;
   }
   __syncthreads();
+}
+
+// The wave's totals of a few values, one shuffle pass each (block_sum_store's order), from lane 0.
+template <int NV>
+__device__ inline void wave_sum_store(const double (&v)[NV], double* __restrict__ out) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    double x = v[i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    if ((threadIdx.x & 63) == 0) out[i] = x;
+  }
 }
 
 // ------------------------------------------------------------------ per-factor expansion

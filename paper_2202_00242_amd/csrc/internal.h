@@ -165,11 +165,13 @@ struct BatchLaunch {
   const double* poses;       // [P][12]
   const WorkItem* items;     // schedule order, per-XCD segments
   const int* seg;            // [kNumXcd + 1]
-  unsigned long long* heads; // [kNumXcd] items taken: from the head (low 32 bits), from the tail (high)
-  double* partials;          // [total tiles][kPartialStride], canonical order
+  unsigned long long* heads; // [kNumXcd] (kHeadStride apart) wave items taken: from the head (low 32 bits), from the tail (high)
+  double* partials;          // [total tiles][block / 64][kPartialStride], canonical order
   unsigned* flags;
   int F;
-  int grid;
+  int grid;                  // 256-thread blocks of the persistent kernel, a multiple of kNumXcd
+  int cus;                   // compute units (>= kNumXcd)
+  int total_tiles;
   int block;
   int tile;
   int lookahead;

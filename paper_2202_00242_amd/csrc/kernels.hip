@@ -463,34 +463,36 @@ struct AccOf<kMathFp64> {
   using type = AccF64;
 };
 
-// Each wave takes chunks of 64 * U points of the tile (chunk c of wave w starts at
-// start + (c * BLOCK/64 + w) * 64 * U), resolves them (phase A) and, whenever at
-// least 64 inliers are queued, runs them with all 64 lanes busy (phase B). The queue tail is
-// flushed at the end of the tile.
-template <int PREC, bool LIN, int BLOCK, int U, bool DIV, int LAYOUT, bool AOS, bool GRAD,
-          class Acc>
-__device__ inline void tile_body(const MapView& m, const RelPose& T,
+// One wave's part of a tile: chunks of `chunk` points (a multiple of 64 U) every `step` points from
+// `base` to `end`, in rows of 64 U points. A row is resolved (phase A) and, whenever at least 64
+// inliers are queued, they run with all 64 lanes busy (phase B); the queue tail is flushed at the
+// end. The k-th inlier of the wave's sequence goes to lane k mod 64, so a lane's sum depends on
+// (base, chunk, step) only, not on U.
+template <int PREC, bool LIN, int U, bool DIV, int LAYOUT, bool AOS, bool GRAD, class Acc>
+__device__ inline void wave_body(const MapView& m, const RelPose& T,
                                  const float* __restrict__ xyz, const float* __restrict__ cov,
-                                 int n, int start, int end, int* __restrict__ corr, Acc& acc,
-                                 int& nin, unsigned& fl, const Queue& qe,
-                                 float* __restrict__ gz) {
+                                 int n, int base, int end, int chunk, int step,
+                                 int* __restrict__ corr, Acc& acc, int& nin, unsigned& fl,
+                                 const Queue& qe, float* __restrict__ gz) {
   constexpr bool FAST = AOS && PREC != kNaiveWorld;  // only a batch has the error bound
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const Planes P = make_planes(xyz, n);
-  int cnt = 0;
-  // positions double-buffered: chunk c + 1 is loaded while chunk c is resolved
+  int cnt = 0, h = 0;
+  // positions double-buffered: the next row is loaded while this one is resolved
   Chunk<U> cur;
-  cur.load(P, start + w * 64 * U, lane);
-  for (int base = start + w * 64 * U; base < end; base += BLOCK * U) {
-    Chunk<U> nxt;
-    resolve<PREC, DIV, LAYOUT, U, FAST, GRAD>(m, T, cur, nxt, P, base + BLOCK * U, base, end,
-                                              lane, qe, cnt, corr, fl, gz);
-    cur = nxt;
-    if constexpr (PREC == kCountOnly) {  // overlap: count the hits, no inlier phase
-      if (lane == 0) nin += cnt;
-      cnt = 0;
-      continue;
+  cur.load(P, base, lane);
+  while (base < end) {
+    int next = base + 64 * U;
+    h += 64 * U;
+    if (h >= chunk) {
+      h = 0;
+      next += step - chunk;
     }
+    Chunk<U> nxt;
+    resolve<PREC, DIV, LAYOUT, U, FAST, GRAD>(m, T, cur, nxt, P, next, base, end, lane, qe, cnt,
+                                              corr, fl, gz);
+    cur = nxt;
+    base = next;
     if (cnt >= 64) {
       wave_sync();
       int head = 0;
@@ -514,63 +516,58 @@ __device__ inline void tile_body(const MapView& m, const RelPose& T,
     }
   }
   wave_sync();
-  if constexpr (PREC != kCountOnly)
-    if (lane < cnt) phase_b<PREC, LIN, AOS, GRAD>(m, T, cov, n, qe, lane, acc, nin, fl, gz);
+  if (lane < cnt) phase_b<PREC, LIN, AOS, GRAD>(m, T, cov, n, qe, lane, acc, nin, fl, gz);
   wave_sync();
 }
 
-// One tile [start, end) of a factor's source; writes the tile's partial sums (kPartialStride
-// doubles: the 28 sums then the inlier count; evaluate writes only e and the count).
-template <int PREC, bool LIN, int BLOCK, int U, bool AOS, bool GRAD = false>
+// The lane's values in the order of the partial sums (the lane sums' own type: a lane's inlier
+// count is exact in either).
+template <class Acc>
+__device__ inline auto lane_values(const Acc& acc, int nin) {
+  using Lane = decltype(acc.get(0));
+  struct Values {
+    Lane v[32];
+  } r;
+#pragma unroll
+  for (int i = 0; i < kNumAcc; ++i) r.v[i] = acc.get(i);
+  r.v[kNumAcc] = (Lane)nin;
+#pragma unroll
+  for (int i = kPartialStride; i < 32; ++i) r.v[i] = 0;
+  return r;
+}
+
+// One tile [start, end) of a single factor's source, by one block; writes the tile's partial sums
+// (kPartialStride doubles: the 28 sums then the inlier count; evaluate writes only e and the count).
+template <int PREC, bool LIN, int BLOCK, int U>
 __device__ inline void process_tile(const MapView& m, const RelPose& T,
                                     const float* __restrict__ xyz,
                                     const float* __restrict__ cov, int n, int start, int end,
                                     int* __restrict__ corr, double* __restrict__ partial,
-                                    unsigned* flags, float* __restrict__ gz = nullptr) {
-  constexpr int kQueue = PREC == kCountOnly ? 1 : queue_cap<U>();
-  __shared__ QueueEntry s_qe[BLOCK / 64][kQueue];
-  __shared__ int s_qp[BLOCK / 64][kQueue];
+                                    unsigned* flags) {
+  __shared__ QueueEntry s_qe[BLOCK / 64][queue_cap<U>()];
+  __shared__ int s_qp[BLOCK / 64][queue_cap<U>()];
   const int w = threadIdx.x >> 6;
-  typename std::conditional<GRAD, GradAcc, typename AccOf<PREC>::type>::type acc;
+  typename AccOf<PREC>::type acc;
   acc.zero();
   int nin = 0;
   unsigned fl = 0;
   const Queue qe{s_qe[w], s_qp[w]};
-  // uniform per tile: lookup structure and, without the FP32 lookup, key arithmetic (a multiply
-  // when res is a power of 2)
-#define VGICP_TILE(LAYOUT)                                                              \
-  do {                                                                                  \
-    if ((AOS && PREC != kNaiveWorld) || m.pow2)                                         \
-      tile_body<PREC, LIN, BLOCK, U, false, LAYOUT, AOS, GRAD>(m, T, xyz, cov, n, start, end, \
-                                                               corr, acc, nin, fl, qe, gz);   \
-    else                                                                                \
-      tile_body<PREC, LIN, BLOCK, U, true, LAYOUT, AOS, GRAD>(m, T, xyz, cov, n, start, end,  \
-                                                              corr, acc, nin, fl, qe, gz);    \
-  } while (0)
+  // uniform: lookup structure and key arithmetic (a multiply when res is a power of 2)
+#define VGICP_TILE(DIV, LAYOUT)                                                               \
+  wave_body<PREC, LIN, U, DIV, LAYOUT, false, false>(m, T, xyz, cov, n, start + w * 64 * U, end, \
+                                                     64 * U, BLOCK * U, corr, acc, nin, fl, qe, \
+                                                     nullptr)
   if (m.bricks) {
-    VGICP_TILE(kLayoutGrid);
+    if (m.pow2) VGICP_TILE(false, kLayoutGrid); else VGICP_TILE(true, kLayoutGrid);
   } else if (m.slots32) {
-    VGICP_TILE(kLayoutHash32);
+    if (m.pow2) VGICP_TILE(false, kLayoutHash32); else VGICP_TILE(true, kLayoutHash32);
   } else {
-    VGICP_TILE(kLayoutHash64);
+    if (m.pow2) VGICP_TILE(false, kLayoutHash64); else VGICP_TILE(true, kLayoutHash64);
   }
 #undef VGICP_TILE
-  if constexpr (GRAD) {
-    double v[7];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) v[i] = acc.v[i];
-    v[6] = (double)nin;
-    block_sum_store<BLOCK, 7>(v, partial);
-  } else if constexpr (LIN) {
-    // the lane sums' own type (a lane's inlier count is exact in either)
-    using Lane = decltype(acc.get(0));
-    Lane v[32];
-#pragma unroll
-    for (int i = 0; i < kNumAcc; ++i) v[i] = acc.get(i);
-    v[kNumAcc] = (Lane)nin;
-#pragma unroll
-    for (int i = kPartialStride; i < 32; ++i) v[i] = 0;
-    block_sum_store_rs<BLOCK, kPartialStride>(v, partial);
+  if constexpr (LIN) {
+    const auto r = lane_values(acc, nin);
+    block_sum_store_rs<BLOCK, kPartialStride>(r.v, partial);
   } else {
     double v[2] = {(double)acc.get(kE), (double)nin};
     block_sum_store<BLOCK, 2>(v, partial + kE);
@@ -659,7 +656,7 @@ __global__ __launch_bounds__(BLOCK) void plain_tile_kernel(MapView m, RelPose T,
                                                            unsigned* flags) {
   const int start = blockIdx.x * tile;
   const int end = (int)min((long long)start + tile, n);
-  process_tile<PREC, LIN, BLOCK, 4, false>(m, T, xyz, cov, (int)n, start, end, corr,
+  process_tile<PREC, LIN, BLOCK, 4>(m, T, xyz, cov, (int)n, start, end, corr,
                                     partials + (size_t)blockIdx.x * kPartialStride, flags);
 }
 
@@ -851,7 +848,7 @@ __global__ void batch_prep_kernel(const FactorView* __restrict__ F, int nF,
                                   RelPose* __restrict__ rel, unsigned long long* __restrict__ heads) {
 #pragma clang fp contract(off)
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f < kNumXcd) heads[f] = 0ull;
+  if (f < kNumXcd) heads[f * kHeadStride] = 0ull;
   if (f >= nF) return;
   RelPose& o = rel[f];
   compute_rel_pose(poses + 12LL * F[f].target_pose, poses + 12LL * F[f].source_pose,
@@ -886,69 +883,241 @@ __global__ void batch_prep_kernel(const FactorView* __restrict__ F, int nF,
   }
 }
 
-// Persistent kernel: block b serves the queue of XCD (b mod 8) first (blocks are dealt to the
-// XCDs round-robin, and each queue holds the work of whole target groups, so an XCD's L2 sees
-// few voxel tables at a time), then helps the other queues. The owner's blocks take a queue's
-// items from its head and helpers from its tail, so a helper works on the queue's last target
-// groups, which the owner has not reached, rather than pulling the owner's current target into
-// a second L2. One 64-bit counter per queue holds both counts: an atomic add returns how many
-// items were taken before it from either end, so every item is taken exactly once and every
-// block leaves once all queues are drained.
-// Occupancy target per lookahead (waves per SIMD): the register budget of 512 / waves.
-template <int U>
-constexpr int waves_for_lookahead() {
-  return U <= 2 ? 4 : (U <= 4 ? 3 : 2);
+// How a batch's work is cut: `tile` points of a factor per work item, shared by `waves` wave items
+// (wave w of a tile takes the chunks of `chunk` points at w * chunk + k * waves * chunk, as the
+// waves of one block of the schedule's size would).
+struct BatchCut {
+  int tile, chunk, waves, wave_shift;
+};
+
+// Persistent kernel, a wave item at a time: each wave takes its own items and writes its own
+// partial sums, so nothing waits at a barrier (with a block per tile, its reduction, the wait for
+// the slowest wave and the next item's dependent loads cost 4.4 us per tile: 0.16 of the global
+// batch's time). Block b serves the queue of XCD (b mod 8) first (blocks are dealt to the XCDs
+// round-robin, and each queue holds the work of whole groups of factors, so an XCD's L2 sees few
+// clouds and maps at a time). The first kStaticShare of a queue is dealt to its waves in turn
+// without any atomic; the rest is taken dynamically, by the queue's own waves from the head and
+// by helpers from the tail. Same-address atomics are served one every ~15 ns here (20,000 of them
+// on one line bounded the batch before), so the counters lie on lines of their own, the next item is
+// asked for before the current one is worked on, and a block asks a drained queue once. One
+// 64-bit counter per queue holds both ends' counts: an atomic add returns how many items were
+// taken before it from either end, so every item is taken exactly once and every wave leaves once
+// all queues are drained.
+// (Dealing 0.3 of a queue measured best on the global batch, 1,242 us; all dynamic 1,257, 0.5 1,252,
+// 0.9 1,466: inliers, and so costs, differ between items.)
+constexpr float kStaticShare = 0.3f;
+
+// Waves per SIMD the registers are kept to: 4 (128 registers) where the lane sums are 28 floats, 3
+// where they are 56 words.
+template <int PREC>
+constexpr int waves_for() {
+  return PREC == kAccKahan || PREC == kMathFp64 ? 3 : 4;
 }
 
-template <int PREC, bool LIN, int BLOCK, int U, bool GRAD = false>
-__global__ __launch_bounds__(BLOCK)
-__attribute__((amdgpu_waves_per_eu(waves_for_lookahead<U>()))) void batch_kernel(const FactorView* __restrict__ F,
-                                                      const RelPose* __restrict__ rel,
-                                                      const WorkItem* __restrict__ items,
-                                                      const int* __restrict__ seg,
-                                                      unsigned long long* __restrict__ heads,
-                                                      int tile,
-                                                      double* __restrict__ partials,
-                                                      unsigned* flags,
-                                                      float* __restrict__ gpts = nullptr) {
-  __shared__ int s_item;
+template <int PREC, bool LIN, bool GRAD = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for<PREC>()))) void
+batch_kernel(const FactorView* __restrict__ F, const RelPose* __restrict__ rel,
+             const WorkItem* __restrict__ items, const int* __restrict__ seg,
+             unsigned long long* __restrict__ heads, BatchCut cut,
+             double* __restrict__ partials, unsigned* flags, float* __restrict__ gpts = nullptr) {
+  constexpr int U = 2;
+  __shared__ QueueEntry s_qe[4][queue_cap<U>()];
+  __shared__ int s_qp[4][queue_cap<U>()];
+  __shared__ unsigned s_drained;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (threadIdx.x == 0) s_drained = 0u;
+  __syncthreads();
+  const Queue qe{s_qe[wv], s_qp[wv]};
   const int xcd = blockIdx.x & (kNumXcd - 1);
-  for (int qi = 0; qi < kNumXcd; ++qi) {
+  const int nw = (int)(gridDim.x / kNumXcd) * 4;           // waves of this queue
+  const int rank = (int)(blockIdx.x / kNumXcd) * 4 + wv;
+  const int own = (seg[xcd + 1] - seg[xcd]) << cut.wave_shift;
+  const int rounds = (int)(kStaticShare * (float)own) / nw;  // items dealt to every wave
+  unsigned fl = 0;
+  int round = 0, qi = 0;
+  bool asked = false;
+  unsigned long long old = 0ull;  // lane 0: the counter before this wave's addition
+  for (;;) {
     const int x = (xcd + qi) & (kNumXcd - 1);
-    const int base = seg[x];
-    const int count = seg[x + 1] - base;
+    const int count = (seg[x + 1] - seg[x]) << cut.wave_shift;
+    // the part of queue x that its own waves do not take in turn starts here
+    const int first = ((int)(kStaticShare * (float)count) / nw) * nw;
     const unsigned long long inc = qi == 0 ? 1ull : (1ull << 32);
-    for (;;) {
-      if (threadIdx.x == 0) {
-        const unsigned long long old = atomicAdd(&heads[x], inc);
-        const long long from_head = (long long)(old & 0xffffffffull), from_tail = (long long)(old >> 32);
-        s_item = from_head + from_tail < count ? (qi == 0 ? (int)from_head : count - 1 - (int)from_tail)
-                                               : -1;
+    int idx;
+    if (round < rounds) {
+      idx = round * nw + rank;
+      ++round;
+    } else {
+      if (!asked) {
+        if (__builtin_amdgcn_readfirstlane((int)((s_drained >> x) & 1u))) {
+          if (++qi == kNumXcd) break;
+          continue;
+        }
+        if (lane == 0) old = atomicAdd(&heads[x * kHeadStride], inc);
       }
-      __syncthreads();
-      // the item index is the same for the whole block: keep it (and what it selects) scalar
-      const int it = __builtin_amdgcn_readfirstlane(s_item);
-      __syncthreads();
-      if (it < 0) break;
-      const int wf = __builtin_amdgcn_readfirstlane(items[base + it].factor);
-      const int wt = __builtin_amdgcn_readfirstlane(items[base + it].tile);
-      if (__builtin_amdgcn_readfirstlane(rel[wf].skip)) continue;  // the finalize writes zeros
-      const FactorView& f = F[wf];
-      const int start = wt * tile;
-      const int end = (int)min((long long)start + tile, f.n);
-      process_tile<PREC, LIN, BLOCK, U, true, GRAD>(
-          f.map, rel[wf], f.xyz, f.cov6, (int)f.n, start, end, nullptr,
-          partials + (size_t)(f.tile_base + wt) * kPartialStride, flags,
-          GRAD ? gpts + 3 * (size_t)f.gbase : nullptr);
+      asked = false;
+      const int from_head = __builtin_amdgcn_readfirstlane((int)(unsigned)old);
+      const int from_tail = __builtin_amdgcn_readfirstlane((int)(unsigned)(old >> 32));
+      if ((long long)from_head + from_tail >= (long long)(count - first)) {
+        if (lane == 0) atomicOr(&s_drained, 1u << x);
+        if (++qi == kNumXcd) break;
+        continue;
+      }
+      idx = qi == 0 ? first + from_head : count - 1 - from_tail;
     }
+    if (round >= rounds) {  // ask for the next item now
+      if (lane == 0) old = atomicAdd(&heads[x * kHeadStride], inc);
+      asked = true;
+    }
+    const int it = seg[x] + (idx >> cut.wave_shift), w = idx & (cut.waves - 1);
+    const int wf = __builtin_amdgcn_readfirstlane(items[it].factor);
+    const int wt = __builtin_amdgcn_readfirstlane(items[it].tile);
+    const RelPose& T = rel[wf];
+    if (__builtin_amdgcn_readfirstlane(T.skip)) continue;  // the finalize writes zeros
+    const FactorView& f = F[wf];
+    const MapView& m = f.map;
+    const int start = wt * cut.tile;
+    const int end = (int)min((long long)start + cut.tile, f.n);
+    double* partial = partials + ((size_t)(f.tile_base + wt) * cut.waves + w) * kPartialStride;
+    typename std::conditional<GRAD, GradAcc, typename AccOf<PREC>::type>::type acc;
+    acc.zero();
+    int nin = 0;
+    float* gz = GRAD ? gpts + 3 * (size_t)f.gbase : nullptr;
+#define VGICP_WAVE(LAYOUT)                                                                      \
+  wave_body<PREC, LIN, U, false, LAYOUT, true, GRAD>(m, T, f.xyz, f.cov6, (int)f.n,               \
+                                                   start + w * cut.chunk, end, cut.chunk,       \
+                                                   cut.waves * cut.chunk, nullptr, acc, nin, fl, \
+                                                   qe, gz)
+    if (m.bricks)
+      VGICP_WAVE(kLayoutGrid);
+    else if (m.slots32)
+      VGICP_WAVE(kLayoutHash32);
+    else
+      VGICP_WAVE(kLayoutHash64);
+#undef VGICP_WAVE
+    if constexpr (GRAD) {
+      double v[7];
+#pragma unroll
+      for (int i = 0; i < 6; ++i) v[i] = acc.v[i];
+      v[6] = (double)nin;
+      wave_sum_store<7>(v, partial);
+    } else if constexpr (LIN) {
+      const auto r = lane_values(acc, nin);
+      const double v = wave_sum_rs(r.v);
+      if ((lane & 1) == 0 && (lane >> 1) < kPartialStride) partial[lane >> 1] = v;
+    } else {
+      double v[2] = {(double)acc.get(kE), (double)nin};
+      wave_sum_store<2>(v, partial + kE);
+    }
+  }
+  if (fl) atomicOr(flags, fl);
+}
+
+// Overlap counts: every point's voxel, nothing else. The counts are whole numbers, so the cut is
+// free: a wave takes a tile's share of 1 / waves in one piece, the items are dealt to the waves in
+// turn (their cost is even: no counter is shared), 64 items' skip flags are read at once, and the
+// few registers leave 8 waves per SIMD.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void batch_count_kernel(
+    const FactorView* __restrict__ F, const RelPose* __restrict__ rel,
+    const WorkItem* __restrict__ items, const int* __restrict__ seg, BatchCut cut,
+    int* __restrict__ counts, unsigned* flags) {
+  constexpr int U = 2;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int xcd = blockIdx.x & (kNumXcd - 1);
+  const int nw = (int)(gridDim.x / kNumXcd) * 4;
+  const int rank = (int)(blockIdx.x / kNumXcd) * 4 + wv;
+  const int first = seg[xcd], own = (seg[xcd + 1] - first) << cut.wave_shift;
+  const int share = cut.tile >> cut.wave_shift;
+  unsigned fl = 0;
+  for (int at = rank; at < own; at += 64 * nw) {
+    // lane l looks at item at + l * nw
+    const long long mine = (long long)at + (long long)lane * nw;
+    const bool live = mine < own && rel[items[first + (int)(mine >> cut.wave_shift)].factor].skip == 0;
+    for (unsigned long long todo = __ballot(live); todo != 0ull; todo &= todo - 1ull) {
+      const int idx = at + __builtin_ctzll(todo) * nw;
+      const int it = first + (idx >> cut.wave_shift), w = idx & (cut.waves - 1);
+      const int wf = __builtin_amdgcn_readfirstlane(items[it].factor);
+      const int wt = __builtin_amdgcn_readfirstlane(items[it].tile);
+      const RelPose& T = rel[wf];
+      const FactorView& f = F[wf];
+      const MapView& m = f.map;
+      const Planes P = make_planes(f.xyz, (int)f.n);
+      const int lo = wt * cut.tile + w * share;
+      const int end = (int)min((long long)lo + share, f.n);
+      int cnt = 0;
+      Chunk<U> cur;
+      cur.load(P, lo, lane);
+      for (int base = lo; base < end; base += 64 * U) {
+        Chunk<U> nxt;
+        const Queue none{nullptr, nullptr};
+#define VGICP_COUNT(LAYOUT)                                                                     \
+  resolve<kCountOnly, false, LAYOUT, U, true>(m, T, cur, nxt, P, base + 64 * U, base, end, lane, \
+                                              none, cnt, nullptr, fl)
+        if (m.bricks)
+          VGICP_COUNT(kLayoutGrid);
+        else if (m.slots32)
+          VGICP_COUNT(kLayoutHash32);
+        else
+          VGICP_COUNT(kLayoutHash64);
+#undef VGICP_COUNT
+        cur = nxt;
+      }
+      if (lane == 0) counts[(size_t)(f.tile_base + wt) * cut.waves + w] = cnt;
+    }
+  }
+  if (fl) atomicOr(flags, fl);
+}
+
+// Inliers and overlap rate of every factor: one wave adds a factor's counts.
+__global__ __launch_bounds__(256) void batch_count_finalize_kernel(
+    const FactorView* __restrict__ F, const RelPose* __restrict__ rel, int nF, int waves,
+    const int* __restrict__ counts, double* __restrict__ rates, long long* __restrict__ inliers) {
+  const int f = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (f >= nF) return;
+  const int n = rel[f].skip ? 0 : F[f].ntiles * waves;
+  const int* c = counts + (size_t)F[f].tile_base * waves;
+  int a = 0;  // at most 2^30 points
+  for (int i = lane; i < n; i += 64) a += c[i];
+  for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+  if (lane == 0) {
+    rates[f] = F[f].n > 0 ? (double)a / (double)F[f].n : 0.0;
+    inliers[f] = a;
   }
 }
 
-// RATE (count-only mode): err receives the overlap rate inliers / n instead of the cost.
-template <bool LIN, bool RATE>
+// A factor's tiles in order, each the sum of its waves in order.
+__device__ inline double sum_tiles(const double* __restrict__ partials, long long base, int nt,
+                                   int waves, int i) {
+  const double* p = partials + base * waves * kPartialStride + i;
+  double a = 0.0;
+  for (int t = 0; t < nt; ++t, p += (long long)waves * kPartialStride) {
+    double s = 0.0;
+    if (waves == 8) {  // eight loads in flight
+      double v[8];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v[w] = p[w * kPartialStride];
+      s = v[0];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) s += v[w];
+    } else {
+      double v[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[w] = p[w * kPartialStride];
+      s = v[0];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) s += v[w];
+    }
+    a += s;
+  }
+  return a;
+}
+
+template <bool LIN>
 __global__ __launch_bounds__(64) void batch_finalize_kernel(const FactorView* __restrict__ F,
                                       const RelPose* __restrict__ rel,
-                                      const double* __restrict__ partials,
+                                      const double* __restrict__ partials, int waves,
                                       double* __restrict__ H, double* __restrict__ b,
                                       double* __restrict__ err, long long* __restrict__ inliers) {
   __shared__ double s[kPartialStride];
@@ -956,17 +1125,10 @@ __global__ __launch_bounds__(64) void batch_finalize_kernel(const FactorView* __
   const int f = blockIdx.x;
   const int i = threadIdx.x;
   const int base = F[f].tile_base, nt = rel[f].skip ? 0 : F[f].ntiles;
-  if (i < kPartialStride && (LIN || i >= kE)) {
-    double a = 0.0;
-    for (int t = 0; t < nt; ++t) a += partials[(long long)(base + t) * kPartialStride + i];
-    s[i] = a;
-  }
+  if (i < kPartialStride && (LIN || i >= kE)) s[i] = sum_tiles(partials, base, nt, waves, i);
   __syncthreads();
   if (i == 0) {
-    if constexpr (RATE)
-      err[f] = F[f].n > 0 ? s[kNumAcc] / (double)F[f].n : 0.0;
-    else
-      err[f] = s[kE];
+    err[f] = s[kE];
     inliers[f] = (long long)s[kNumAcc];
   }
   if constexpr (LIN) expand_shared(s, rel[f], F[f].binary, H + 144LL * f, 12, b + 12LL * f, i, ew);
@@ -979,18 +1141,14 @@ __global__ __launch_bounds__(64) void batch_finalize_kernel(const FactorView* __
 // gf[f] = [source | target] (the target half is zero for a unary factor).
 __global__ void batch_grad_finalize_kernel(const FactorView* __restrict__ F,
                                            const RelPose* __restrict__ rel,
-                                           const double* __restrict__ partials,
+                                           const double* __restrict__ partials, int waves,
                                            const double* __restrict__ grad_err,
                                            double* __restrict__ gf) {
   __shared__ double s[6];
   const int f = blockIdx.x;
   const int i = threadIdx.x;
   const int base = F[f].tile_base, nt = rel[f].skip ? 0 : F[f].ntiles;
-  if (i < 6) {
-    double a = 0.0;
-    for (int t = 0; t < nt; ++t) a += partials[(long long)(base + t) * kPartialStride + i];
-    s[i] = a * grad_err[f];
-  }
+  if (i < 6) s[i] = sum_tiles(partials, base, nt, waves, i) * grad_err[f];
   __syncthreads();
   if (i < 12) {
     double v = 0.0;
@@ -1078,32 +1236,40 @@ void launch_plain_t(const MapView& m, const RelPose& T, const float* xyz, const 
                                              reinterpret_cast<long long*>(inliers));
 }
 
-template <int PREC, bool LIN, int BLOCK, int U>
-void launch_batch_t(const BatchLaunch& L, hipStream_t s) {
-  batch_prep_kernel<<<(L.F + 255) / 256, 256, 0, s>>>(L.factors, L.F, L.poses, L.boxes,
-                                                      PREC != kNaiveWorld, L.rel, L.heads);
-  batch_kernel<PREC, LIN, BLOCK, U><<<L.grid, BLOCK, 0, s>>>(L.factors, L.rel, L.items, L.seg,
-                                                            L.heads, L.tile, L.partials, L.flags);
-  batch_finalize_kernel<LIN, PREC == kCountOnly><<<L.F, 64, 0, s>>>(
-      L.factors, L.rel, L.partials, L.H, L.b, L.err, reinterpret_cast<long long*>(L.inliers));
+BatchCut cut_of(const BatchLaunch& L) {
+  return {L.tile, 64 * L.lookahead, L.block / 64, L.block == 512 ? 3 : 2};
 }
 
-template <int PREC, bool LIN, int BLOCK>
-void launch_batch_u(const BatchLaunch& L, hipStream_t s) {
-  if (L.lookahead == 8)
-    launch_batch_t<PREC, LIN, BLOCK, 8>(L, s);
-  else if (L.lookahead == 2)
-    launch_batch_t<PREC, LIN, BLOCK, 2>(L, s);
-  else
-    launch_batch_t<PREC, LIN, BLOCK, 4>(L, s);
+// The schedule's grid, but no more blocks than fit the chip together: a wave of a later round would
+// start on its dealt items when everyone else is done (global batch, 6 blocks per CU instead of 4:
+// 1,371 us instead of 1,242).
+template <int PREC>
+int resident(const BatchLaunch& L) {
+  const int need = (L.total_tiles * (L.block / 64) + 3) / 4;  // a wave item per wave at least
+  const int most = std::min(L.grid, L.cus * waves_for<PREC>());
+  return std::max((std::min(need, most) + kNumXcd - 1) / kNumXcd, 1) * kNumXcd;
 }
 
 template <int PREC, bool LIN>
-void launch_batch_b(const BatchLaunch& L, hipStream_t s) {
-  if (L.block == 512)
-    launch_batch_u<PREC, LIN, 512>(L, s);
-  else
-    launch_batch_u<PREC, LIN, 256>(L, s);
+void launch_batch_t(const BatchLaunch& L, hipStream_t s) {
+  const BatchCut cut = cut_of(L);
+  batch_prep_kernel<<<(L.F + 255) / 256, 256, 0, s>>>(L.factors, L.F, L.poses, L.boxes,
+                                                      PREC != kNaiveWorld, L.rel, L.heads);
+  batch_kernel<PREC, LIN><<<resident<PREC>(L), 256, 0, s>>>(L.factors, L.rel, L.items, L.seg, L.heads, cut,
+                                                 L.partials, L.flags);
+  batch_finalize_kernel<LIN><<<L.F, 64, 0, s>>>(L.factors, L.rel, L.partials, cut.waves, L.H, L.b,
+                                                L.err, reinterpret_cast<long long*>(L.inliers));
+}
+
+void launch_batch_count(const BatchLaunch& L, hipStream_t s) {
+  const BatchCut cut = cut_of(L);  // 8 blocks of 4 waves fill a CU's 32 wave slots
+  int* counts = reinterpret_cast<int*>(L.partials);
+  batch_prep_kernel<<<(L.F + 255) / 256, 256, 0, s>>>(L.factors, L.F, L.poses, L.boxes, 1, L.rel,
+                                                      L.heads);
+  batch_count_kernel<<<8 * L.cus / kNumXcd * kNumXcd, 256, 0, s>>>(L.factors, L.rel, L.items, L.seg, cut, counts,
+                                                  L.flags);
+  batch_count_finalize_kernel<<<(L.F + 3) / 4, 256, 0, s>>>(
+      L.factors, L.rel, L.F, cut.waves, counts, L.err, reinterpret_cast<long long*>(L.inliers));
 }
 
 }  // namespace
@@ -1142,14 +1308,15 @@ void launch_backward(const MapView& m, const RelPose& T, const TangentMap& J, co
 }
 
 namespace {
-template <int PREC, int BLOCK, int U>
+template <int PREC>
 void launch_batch_grad_t(const BatchLaunch& L, const BatchGrad& G, hipStream_t s) {
+  const BatchCut cut = cut_of(L);
   batch_prep_kernel<<<(L.F + 255) / 256, 256, 0, s>>>(L.factors, L.F, L.poses, L.boxes, 1,
                                                       L.rel, L.heads);
-  batch_kernel<PREC, false, BLOCK, U, true><<<L.grid, BLOCK, 0, s>>>(
-      L.factors, L.rel, L.items, L.seg, L.heads, L.tile, L.partials, L.flags, G.gpts);
-  batch_grad_finalize_kernel<<<L.F, 64, 0, s>>>(L.factors, L.rel, L.partials, G.grad_err,
-                                                G.gf);
+  batch_kernel<PREC, false, true><<<resident<PREC>(L), 256, 0, s>>>(L.factors, L.rel, L.items, L.seg,
+                                                         L.heads, cut, L.partials, L.flags, G.gpts);
+  batch_grad_finalize_kernel<<<L.F, 64, 0, s>>>(L.factors, L.rel, L.partials, cut.waves,
+                                                G.grad_err, G.gf);
   if (G.P > 0)
     batch_grad_pose_kernel<<<(6 * G.P + 255) / 256, 256, 0, s>>>(G.bptr, G.bcontrib, G.gf, G.P,
                                                                G.grad_poses);
@@ -1161,40 +1328,23 @@ void launch_batch_grad_t(const BatchLaunch& L, const BatchGrad& G, hipStream_t s
   }
 }
 
-template <int PREC, int BLOCK>
-void launch_batch_grad_u(const BatchLaunch& L, const BatchGrad& G, hipStream_t s) {
-  if (L.lookahead == 8)
-    launch_batch_grad_t<PREC, BLOCK, 8>(L, G, s);
-  else if (L.lookahead == 2)
-    launch_batch_grad_t<PREC, BLOCK, 2>(L, G, s);
-  else
-    launch_batch_grad_t<PREC, BLOCK, 4>(L, G, s);
-}
-
-template <int PREC>
-void launch_batch_grad_b(const BatchLaunch& L, const BatchGrad& G, hipStream_t s) {
-  if (L.block == 512)
-    launch_batch_grad_u<PREC, 512>(L, G, s);
-  else
-    launch_batch_grad_u<PREC, 256>(L, G, s);
-}
 }  // namespace
 
 void launch_batched_backward(const BatchLaunch& L, const BatchGrad& G, hipStream_t s) {
   if (L.precision == kMathFp64)
-    launch_batch_grad_b<kMathFp64>(L, G, s);
+    launch_batch_grad_t<kMathFp64>(L, G, s);
   else
-    launch_batch_grad_b<kAccFp64>(L, G, s);
+    launch_batch_grad_t<kAccFp64>(L, G, s);
 }
 
 void launch_batched(const BatchLaunch& L, hipStream_t s) {
 #define VGICP_BATCH(P) \
-  (L.linearize ? launch_batch_b<P, true>(L, s) : launch_batch_b<P, false>(L, s))
+  (L.linearize ? launch_batch_t<P, true>(L, s) : launch_batch_t<P, false>(L, s))
   switch (L.precision) {
     case kAccKahan: VGICP_BATCH(kAccKahan); break;
     case kNaiveWorld: VGICP_BATCH(kNaiveWorld); break;
     case kMathFp64: VGICP_BATCH(kMathFp64); break;
-    case kCountOnly: launch_batch_b<kCountOnly, false>(L, s); break;
+    case kCountOnly: launch_batch_count(L, s); break;
     default: VGICP_BATCH(kAccFp64); break;
   }
 #undef VGICP_BATCH
