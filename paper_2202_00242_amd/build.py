@@ -19,7 +19,7 @@ LIB = os.path.join(HERE, "libvgicp.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["capi.hip", "imu.hip", "kernels.hip", "lm.hip", "preprocess.hip",
            "voxelmap.hip"]
-HEADERS = ["common.h", "device_math.h", "internal.h"]
+HEADERS = ["common.h", "device_math.h", "internal.h", "sort.h"]
 ARCH = os.environ.get("VGICP_OFFLOAD_ARCH", "gfx950")
 
 # Packed FP32 instructions are disabled for the device code (the compiler would otherwise

@@ -93,6 +93,63 @@ int device_cu_count(int device) {
   return d && d->cus > 0 ? d->cus : 256;
 }
 
+hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s) {
+  static std::mutex mu;
+  static std::map<int, hipMemPool_t> pools;  // one per device, for the life of the process
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  hipMemPool_t pool = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = pools.find(dev);
+    if (it == pools.end()) {
+      hipMemPoolProps props{};
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = dev;
+      if ((e = hipMemPoolCreate(&pool, &props)) != hipSuccess) return e;
+      uint64_t keep = kPoolKeep;
+      (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+      it = pools.emplace(dev, pool).first;
+    }
+    pool = it->second;
+  }
+  return hipMallocFromPoolAsync(p, bytes, pool, s);
+}
+
+namespace {
+std::mutex g_host_mutex;
+std::vector<void*>& host_blocks() {  // not destroyed: calls may run while the process ends
+  static auto* v = new std::vector<void*>;
+  return *v;
+}
+}  // namespace
+
+HostBlock::HostBlock() {
+  {
+    std::lock_guard<std::mutex> lk(g_host_mutex);
+    if (!host_blocks().empty()) {
+      p = host_blocks().back();
+      host_blocks().pop_back();
+      return;
+    }
+  }
+  if (hipHostMalloc(&p, kHostBlockBytes, hipHostMallocPortable) != hipSuccess) p = nullptr;
+}
+
+HostBlock::~HostBlock() {
+  if (!p) return;
+  {
+    std::lock_guard<std::mutex> lk(g_host_mutex);
+    if (host_blocks().size() < kHostBlocks) {
+      host_blocks().push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
 vgicp_status flags_to_status(unsigned f) {
   if (f & kFlagNonFinite)
     return fail(VGICP_E_NONFINITE,
@@ -601,8 +658,7 @@ struct vgicp_batch_s {
   std::vector<vgicp_cloud> clouds;  // the caller's clouds (source of the batch's copies)
   std::vector<int64_t> cov6_offset; // per cloud: first point in the copies
   std::vector<double> cloud_cell;   // per cloud: cell of its spatial order (finest target res)
-  std::vector<float> boxes;         // per cloud: bounding box lo, hi (local frame)
-  float* d_boxes = nullptr;
+  float* d_boxes = nullptr;         // per cloud: bounding box lo, hi (local frame)
   float* d_xyz = nullptr;           // every cloud's positions in spatial order, [3][n] each
   float* d_cov6 = nullptr;          // and its covariances, interleaved [n][6]
   int* d_perm = nullptr;            // and its order: spatial index -> the caller's index
@@ -629,13 +685,16 @@ struct vgicp_batch_s {
   double *d_lm_Hc = nullptr, *d_lm_bc = nullptr, *d_lm_cand = nullptr, *d_lm_lambda = nullptr;
   int *d_lm_pos = nullptr, *d_lm_accept = nullptr;
   vgicp_schedule sched{256, 8192, 4, 4};  // 4 blocks of 4 waves: the batch kernel's 16 waves per CU
-  FactorView* d_factors = nullptr;
+  void* arena = nullptr;            // the pool block of the copies, boxes, relative poses, counters
   RelPose* d_rel = nullptr;
-  WorkItem* d_items = nullptr;
-  int* d_seg = nullptr;
   unsigned long long* d_heads = nullptr;
+  char* d_sched = nullptr;          // one upload: the factors, the queue segments, the work items
+  FactorView* d_factors = nullptr;
+  int* d_seg = nullptr;
+  WorkItem* d_items = nullptr;
   double* d_partials = nullptr;
-  size_t items_cap = 0, partials_cap = 0;
+  size_t sched_cap = 0, partials_cap = 0;
+  bool one_shot = false;            // used once: launched directly, no graph
   int total_tiles = 0;
   int grid = 0;
   int64_t total_points = 0;
@@ -752,26 +811,39 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
     b->hf[f].ntiles = ntiles[f];
   }
   hipError_t e;
-  if (items.size() > b->items_cap) {
-    (void)hipFree(b->d_items);
-    b->d_items = nullptr;
-    if ((e = hipMalloc(&b->d_items, std::max<size_t>(items.size(), 1) * sizeof(WorkItem))))
-      return hip_fail(e, "hipMalloc (work items)");
-    b->items_cap = items.size();
-  }
+  // [factors | segments | items] in one block and one copy
+  const size_t o_seg = Arena::up(b->hf.size() * sizeof(FactorView));
+  const size_t o_items = o_seg + Arena::up(seg.size() * sizeof(int));
+  const size_t bytes = o_items + items.size() * sizeof(WorkItem);
   const size_t np = (size_t)std::max<int64_t>(total, 1) * (size_t)(sc.block / 64) * kPartialStride;
-  if (np > b->partials_cap) {
-    (void)hipFree(b->d_partials);
-    b->d_partials = nullptr;
-    if ((e = hipMalloc(&b->d_partials, np * sizeof(double))))
-      return hip_fail(e, "hipMalloc (partials)");
-    b->partials_cap = np;
-  }
-  if ((!items.empty() && (e = hipMemcpy(b->d_items, items.data(), items.size() * sizeof(WorkItem),
-                                         hipMemcpyHostToDevice))) ||
-      (e = hipMemcpy(b->d_seg, seg.data(), seg.size() * sizeof(int), hipMemcpyHostToDevice)) ||
-      (b->F > 0 && (e = hipMemcpy(b->d_factors, b->hf.data(), b->hf.size() * sizeof(FactorView),
-                                  hipMemcpyHostToDevice))))
+  // another schedule may need more: the old blocks' readers are done (set_schedule synchronises)
+  auto grow = [&](void** p, size_t* cap, size_t want) {
+    if (want <= *cap) return hipSuccess;
+    if (*p) (void)hipFreeAsync(*p, nullptr);
+    *p = nullptr;
+    *cap = 0;
+    Arena a;
+    a.need<char>(want);
+    const hipError_t ge = a.get(nullptr, true);
+    if (ge == hipSuccess) {
+      *p = a.base;
+      *cap = want;
+      a.base = nullptr;
+    }
+    return ge;
+  };
+  if ((e = grow(reinterpret_cast<void**>(&b->d_sched), &b->sched_cap, bytes)) ||
+      (e = grow(reinterpret_cast<void**>(&b->d_partials), &b->partials_cap, np * sizeof(double))))
+    return hip_fail(e, "pool allocation (schedule)");
+  b->d_factors = reinterpret_cast<FactorView*>(b->d_sched);
+  b->d_seg = reinterpret_cast<int*>(b->d_sched + o_seg);
+  b->d_items = reinterpret_cast<WorkItem*>(b->d_sched + o_items);
+  std::vector<char> image(bytes);
+  if (b->F > 0) std::memcpy(image.data(), b->hf.data(), b->hf.size() * sizeof(FactorView));
+  std::memcpy(image.data() + o_seg, seg.data(), seg.size() * sizeof(int));
+  if (!items.empty())
+    std::memcpy(image.data() + o_items, items.data(), items.size() * sizeof(WorkItem));
+  if ((e = hipMemcpy(b->d_sched, image.data(), bytes, hipMemcpyHostToDevice)))
     return hip_fail(e, "upload schedule");
   b->total_tiles = (int)total;
   const int cus = device_cu_count(b->device);
@@ -827,6 +899,11 @@ constexpr size_t kMaxGraphs = 16;
 vgicp_status run_batch(vgicp_batch b, const double* poses, int precision, bool lin, double* H,
                        double* bb, double* err, int64_t* inliers, hipStream_t s) {
   if (b->F == 0) return VGICP_OK;
+  if (b->one_shot) {  // a graph's capture and instantiation cost more (100 us) than three launches
+    launch_batched(make_launch(b, poses, precision, lin, H, bb, err, inliers), s);
+    const hipError_t le = hipGetLastError();
+    return le == hipSuccess ? VGICP_OK : hip_fail(le, "batch launch");
+  }
   const std::array<uintptr_t, 8> key = {(uintptr_t)precision, (uintptr_t)lin, (uintptr_t)poses,
                                         (uintptr_t)H, (uintptr_t)bb, (uintptr_t)err,
                                         (uintptr_t)inliers, (uintptr_t)b->grid};
@@ -955,16 +1032,26 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
     cov6_points += clouds[i].n;
   }
   b->cloud_cell.assign(n_clouds, 0.0);
-  if ((e = hipMalloc(&b->d_cov6, (size_t)std::max<int64_t>(cov6_points, 1) * 24)) ||
-      (e = hipMalloc(&b->d_xyz, (size_t)std::max<int64_t>(cov6_points, 1) * 12)) ||
-      (e = hipMalloc(&b->d_perm, (size_t)std::max<int64_t>(cov6_points, 1) * 4)) ||
-      (e = hipMalloc(&b->d_boxes, (size_t)std::max(n_clouds, 1) * 6 * sizeof(float)))) {
-    (void)hipFree(b->d_cov6);
-    (void)hipFree(b->d_xyz);
-    (void)hipFree(b->d_perm);
+  const size_t pts1 = (size_t)std::max<int64_t>(cov6_points, 1), F1 = (size_t)std::max(n_factors, 1);
+  Arena own;
+  own.need<float>(6 * pts1);
+  own.need<float>(3 * pts1);
+  own.need<int>(pts1);
+  own.need<float>(6 * (size_t)std::max(n_clouds, 1));
+  own.need<RelPose>(F1);
+  own.need<unsigned long long>(kNumXcd * kHeadStride);
+  if ((e = own.get(nullptr, true))) {
     delete b;
-    return hip_fail(e, "hipMalloc (cloud copy)");
+    return hip_fail(e, "pool allocation (batch)");
   }
+  b->d_cov6 = own.take<float>(6 * pts1);
+  b->d_xyz = own.take<float>(3 * pts1);
+  b->d_perm = own.take<int>(pts1);
+  b->d_boxes = own.take<float>(6 * (size_t)std::max(n_clouds, 1));
+  b->d_rel = own.take<RelPose>(F1);
+  b->d_heads = own.take<unsigned long long>(kNumXcd * kHeadStride);
+  b->arena = own.base;
+  own.base = nullptr;  // the batch's now
   for (int f = 0; f < n_factors; ++f) {
     const vgicp_factor& fc = factors[f];
     if (fc.target_map < 0 || fc.target_map >= n_maps || fc.source_cloud < 0 ||
@@ -991,14 +1078,6 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
     b->hf[f] = v;
     b->total_points += v.n;
   }
-  const size_t F1 = (size_t)std::max(n_factors, 1);
-  if ((e = hipMalloc(&b->d_factors, F1 * sizeof(FactorView))) ||
-      (e = hipMalloc(&b->d_rel, F1 * sizeof(RelPose))) ||
-      (e = hipMalloc(&b->d_seg, (kNumXcd + 1) * sizeof(int))) ||
-      (e = hipMalloc(&b->d_heads, kNumXcd * kHeadStride * sizeof(unsigned long long)))) {
-    vgicp_batch_destroy(b);
-    return hip_fail(e, "hipMalloc (batch)");
-  }
   vgicp_status st = apply_schedule(b, b->sched);
   if (st == VGICP_OK) st = vgicp_batch_refresh(b, nullptr);
   if (st == VGICP_OK && (e = hipStreamSynchronize(nullptr))) st = hip_fail(e, "batch setup");
@@ -1015,20 +1094,14 @@ VGICP_API vgicp_status vgicp_batch_refresh(vgicp_batch batch, vgicp_stream strea
   hipStream_t s = stream_of(stream);
   vgicp_status st0 = batch_begin(batch, s);
   if (st0 != VGICP_OK) return st0;
-  batch->boxes.assign(6 * std::max<size_t>(batch->clouds.size(), 1), 0.0f);
+  std::vector<SpatialJob> jobs;
   for (size_t i = 0; i < batch->clouds.size(); ++i) {
-    float* box = batch->boxes.data() + 6 * i;
-    if (batch->cloud_cell[i] <= 0.0) continue;  // no factor reads this cloud
     const int64_t o = batch->cov6_offset[i];
-    vgicp_status st = spatial_copy(batch->clouds[i].xyz, batch->clouds[i].cov, batch->clouds[i].n,
-                                   batch->cloud_cell[i], batch->d_xyz + 3 * o,
-                                   batch->d_cov6 + 6 * o, box, batch->d_perm + o, s);
-    if (st != VGICP_OK) return batch_end(batch, s, st);
+    jobs.push_back({batch->clouds[i].xyz, batch->clouds[i].cov, batch->d_xyz + 3 * o,
+                    batch->d_cov6 + 6 * o, batch->d_perm + o, batch->clouds[i].n, 0,
+                    batch->cloud_cell[i]});
   }
-  hipError_t e = hipMemcpy(batch->d_boxes, batch->boxes.data(),
-                           batch->boxes.size() * sizeof(float), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return batch_end(batch, s, hip_fail(e, "upload bounding boxes"));
-  return batch_end(batch, s, VGICP_OK);
+  return batch_end(batch, s, spatial_copies(jobs, batch->d_boxes, s));
 }
 
 VGICP_API vgicp_status vgicp_batch_set_schedule(vgicp_batch batch,
@@ -1589,16 +1662,8 @@ VGICP_API vgicp_status vgicp_batch_destroy(vgicp_batch batch) {
   batch->drop_graphs();
   if (batch->capture_stream) (void)hipStreamDestroy(batch->capture_stream);
   if (batch->done) (void)hipEventDestroy(batch->done);
-  (void)hipFree(batch->d_factors);
-  (void)hipFree(batch->d_boxes);
-  (void)hipFree(batch->d_rel);
-  (void)hipFree(batch->d_items);
-  (void)hipFree(batch->d_seg);
-  (void)hipFree(batch->d_heads);
-  (void)hipFree(batch->d_partials);
-  (void)hipFree(batch->d_cov6);
-  (void)hipFree(batch->d_xyz);
-  (void)hipFree(batch->d_perm);
+  for (void* p : {batch->arena, (void*)batch->d_sched, (void*)batch->d_partials})
+    if (p) (void)hipFreeAsync(p, nullptr);
   for (void* p : {(void*)batch->d_gpts, (void*)batch->d_gf, (void*)batch->d_gbptr,
                   (void*)batch->d_gbcontrib, (void*)batch->d_cptr, (void*)batch->d_cfac,
                   (void*)batch->d_cloud_n, (void*)batch->d_cloud_off, (void*)batch->d_gout})
@@ -1621,6 +1686,7 @@ VGICP_API vgicp_status vgicp_linearize_batched(const vgicp_voxelmap* maps, int32
   vgicp_status st =
       vgicp_batch_create(maps, n_maps, clouds, n_clouds, factors, n_factors, n_poses, &bt);
   if (st != VGICP_OK) return st;
+  bt->one_shot = true;
   st = vgicp_batch_linearize(bt, poses, precision, H, b, err, inliers, stream);
   hipError_t e = hipStreamSynchronize(stream_of(stream));
   vgicp_batch_destroy(bt);

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -27,6 +28,7 @@ struct vgicp_voxelmap_s {
   int64_t nbricks = 0;
   int gby = 0, gbz = 0;
   vgicp::VoxelData* voxb = nullptr;  // [V] records in brick order (grid layout)
+  void* arena = nullptr;             // the device memory of all the arrays here
   int* rec_id = nullptr;             // [V] voxel id of each brick-ordered record
   uint2* slots32 = nullptr;          // [cap] {relative key, id}, when key32
   longlong2* slots64 = nullptr;      // [cap] {packed key, id}, otherwise
@@ -83,6 +85,68 @@ double* device_scratch(int device);
 void relative_pose(const double* Tt, const double* Ts, double* Tts);
 RelPose make_rel_pose(const double* Tt, const double* Ts, double inv_res);
 
+// Device memory of one host call: one block of the library's stream-ordered pool, cut up by take().
+// (hipMalloc per buffer and hipFree, which waits for the device, were half of a sweep's 920 us.) The
+// pool keeps at most kPoolKeep bytes between calls; the block goes back to it on the call's stream,
+// so calls on other streams and threads never see it before this call's work is done.
+constexpr size_t kPoolKeep = 256u << 20;
+hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s);
+struct Arena {
+  hipStream_t s = nullptr;
+  char* base = nullptr;
+  size_t used = 0, size = 0;
+  // Sizes are added up with need() first; get() allocates; take() hands out in any order.
+  static size_t up(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+  template <typename T>
+  void need(size_t count) {
+    size += up(std::max<size_t>(count, 1) * sizeof(T));
+  }
+  // Scratch blocks are powers of two of at least 1 MiB, lasting ones powers of two up to 16 MiB and
+  // multiples of an eighth of one above: calls of other sizes then find the pool's blocks again (a
+  // block that the pool has to map anew costs some 300 us).
+  hipError_t get(hipStream_t stream, bool lasting = false) {
+    s = stream;
+    size_t bytes = 1u << 16;
+    while (bytes < size) bytes <<= 1;
+    if (!lasting)
+      bytes = std::max<size_t>(bytes, 1u << 20);
+    else if (bytes > (16u << 20))
+      bytes = (size + bytes / 16 - 1) / (bytes / 16) * (bytes / 16);
+    return pool_alloc(reinterpret_cast<void**>(&base), bytes, s);
+  }
+  template <typename T>
+  T* take(size_t count) {
+    T* p = reinterpret_cast<T*>(base + used);
+    used += up(std::max<size_t>(count, 1) * sizeof(T));
+    return p;
+  }
+  ~Arena() {
+    if (base) (void)hipFreeAsync(base, s);
+  }
+};
+
+// A pinned host block that a call's kernels write their results to (read after a synchronisation
+// of the stream; copies of a few bytes to pageable memory took 15 to 30 us each). A block belongs to
+// one call at a time; at most kHostBlocks idle ones are kept.
+constexpr size_t kHostBlocks = 16, kHostBlockBytes = 4096;
+struct HostBlock {
+  void* p = nullptr;
+  HostBlock();
+  ~HostBlock();
+  HostBlock(const HostBlock&) = delete;
+  HostBlock& operator=(const HostBlock&) = delete;
+};
+
+// What the map build, the filter and the neighbour search read back. Error words are plain stores
+// of 1 (several writers store the same value).
+struct BuildReport {
+  int lo[3], hi[3];        // integer bounds (voxels, cells)
+  float flo[3], fhi[3];    // coordinate bounds
+  int nonfinite, keyrange, internal, deep;
+  int count;               // voxels / output points
+  int est[64];             // neighbour search: sampled distance exponents
+};
+
 // Device buffers owned by one host call, freed (hipFree synchronises) when it returns.
 struct Scratch {
   std::vector<void*> ptrs;
@@ -99,26 +163,68 @@ struct Scratch {
   }
 };
 
-// Device-wide primitives (voxelmap.hip), enqueued on s. Exclusive scan of n ints (in and out
-// may alias). Stable LSD radix sort of (key, value) pairs on the low `bits` bits of the keys,
-// 8 bits per pass: the sorted pairs end in (*k, *v) - the pointers swap with the temporaries
-// (*kt, *vt) as the passes go. A scatter outside [0, n) sets kFlagInternal in flags.
-hipError_t scan_exclusive(const int* in, int* out, long long n, hipStream_t s, Scratch& sc);
+// Stable LSD radix sort of (key, value) pairs, 8 bits per pass (voxelmap.hip), of one array or of
+// several segments at once (segs: device array; null: one segment of n). Up to kSortMax pairs per
+// segment a pass is two launches: hist holds every tile's digit counts [segment][tile][256] -
+// those of pass 0 written by the kernel that makes the keys (sort_tile_hist in sort.h) - and each tile
+// adds up its predecessors' counts itself. Longer arrays take radix_sort_pairs. A destination outside
+// the segment sets *internal.
+struct SortSeg {
+  long long off;
+  int n;
+  int pad;
+};
+constexpr int kSortTile = 1024;
+constexpr long long kSortMax = 1LL << 18;
+struct SortBuffers {
+  unsigned long long *k, *kt;  // keys and their other buffer (swapped by every pass)
+  int *v, *vt;
+  int* hist;
+};
+inline long long sort_tiles(long long n) { return (n + kSortTile - 1) / kSortTile; }
+inline size_t sort_hist_ints(int nseg, long long max_n) {
+  return (size_t)nseg * (size_t)sort_tiles(max_n) * 256;
+}
+hipError_t sort_passes(SortBuffers& b, const SortSeg* segs, int nseg, long long max_n, int bits,
+                       int* internal, hipStream_t s);
+
+// Device-wide primitives (voxelmap.hip), enqueued on s. Stable LSD radix sort of (key, value) pairs
+// on the low `bits` bits of the keys, any length: the sorted pairs end in (*k, *v) - the pointers swap
+// with the temporaries (*kt, *vt) as the passes go. A scatter outside [0, n) sets *internal.
 hipError_t radix_sort_pairs(unsigned long long** k, int** v, unsigned long long** kt, int** vt,
-                            long long n, int bits, unsigned* flags, hipStream_t s, Scratch& sc);
+                            long long n, int bits, int* internal, hipStream_t s, Scratch& sc);
+
+// Starts of the runs of equal keys of a sorted array (voxelmap.hip): start[r] for run r in order,
+// start[count] = n, and the number of runs in *count_out (pinned or device). tile_counts holds
+// kRunTiles ints.
+constexpr int kRunTiles = 1024;
+hipError_t run_starts(const unsigned long long* key, long long n, int* start, int* tile_counts,
+                      int* count_out, hipStream_t s);
+// Exclusive scan of n ints (in and out may not alias); *total (may be null) receives the sum.
+hipError_t scan_values(const int* in, int* out, long long n, int* tile_counts, int* total,
+                       hipStream_t s);
+// Zeroes `words` ints and, when given, resets the integer bounds (7 ints: 3 minima, 3 maxima, a
+// ticket) and the report.
+void launch_call_init(int* zero, long long words, int* bounds, BuildReport* report,
+                      hipStream_t s);
 
 // Voxel map build (voxelmap.hip).
 vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, double res,
                             int layout, hipStream_t s, vgicp_voxelmap* out);
 void destroy_voxelmap(vgicp_voxelmap m);
-// A cloud in the spatial order of the Morton codes of its cells of size `cell` (stable):
-// positions [3][n] and interleaved covariances [n][6], and its bounding box (host, 6 floats:
-// lo, hi; infinite when a coordinate is not finite, empty when n = 0) (voxelmap.hip).
-// Synchronises s.
-// perm_out (device [n], may be NULL) receives the permutation: spatial index -> original index.
-vgicp_status spatial_copy(const float* xyz, const float* cov, int64_t n, double cell,
-                          float* xyz_out, float* cov6_out, float* box, int* perm_out,
-                          hipStream_t s);
+// Clouds in the spatial order of the Morton codes of their cells of size `cell` (stable):
+// positions [3][n] and interleaved covariances [n][6], the permutation (spatial index -> original
+// index), and the bounding boxes [clouds][6] (lo, hi; infinite when a coordinate is not finite,
+// empty when n = 0), all of a batch's clouds together (voxelmap.hip). Clouds with cell <= 0 are left
+// out (their box is zero). Synchronises s.
+struct SpatialJob {
+  const float *xyz, *cov;
+  float *xyz_out, *cov6_out;
+  int* perm;
+  long long n, off;  // off: first point of the cloud in the job's sort buffers
+  double cell;
+};
+vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipStream_t s);
 
 // Preprocessing (preprocess.hip). downsample and knn synchronise s; the covariance kernel is
 // enqueued only and reports a neighbour index outside [-1, n) through flags.

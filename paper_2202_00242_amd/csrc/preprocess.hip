@@ -13,10 +13,12 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "device_math.h"
 #include "internal.h"
+#include "sort.h"
 
 namespace vgicp {
 namespace {
@@ -34,14 +36,6 @@ int bits_for(long long span) {  // bits to hold values 0..span
   return b;
 }
 
-__global__ void bounds_reset_kernel(int* bounds, unsigned* flags) {
-  if (threadIdx.x < 3) {
-    bounds[threadIdx.x] = INT_MAX;
-    bounds[3 + threadIdx.x] = INT_MIN;
-  }
-  if (threadIdx.x == 0) *flags = 0u;
-}
-
 // ------------------------------------------------------------------ voxel-grid filter
 
 // Cells floor(p / res) per axis in FP64 (a multiply for a power-of-two res, where it is exact),
@@ -51,7 +45,7 @@ __global__ __launch_bounds__(kBlock) void ds_cells_kernel(const float* __restric
                                                           long long n, int pow2, double res,
                                                           double inv_res, int* __restrict__ kc,
                                                           int* __restrict__ bounds,
-                                                          unsigned* __restrict__ flags) {
+                                                          BuildReport* __restrict__ report) {
   int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
   unsigned fl = 0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -68,30 +62,9 @@ __global__ __launch_bounds__(kBlock) void ds_cells_kernel(const float* __restric
       hi[a] = max(hi[a], k);
     }
   }
-  for (int a = 0; a < 3; ++a)
-    for (int off = 32; off > 0; off >>= 1) {
-      lo[a] = min(lo[a], __shfl_xor(lo[a], off, 64));
-      hi[a] = max(hi[a], __shfl_xor(hi[a], off, 64));
-    }
-  // one set of atomics per block: same-address atomics from every wave serialize in L2
-  __shared__ int red[6][kBlock / 64];
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int a = 0; a < 3; ++a) {
-      red[a][w] = lo[a];
-      red[3 + a][w] = hi[a];
-    }
-  if (fl) atomicOr(flags, fl);
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    int v = red[threadIdx.x][0];
-    for (int ww = 1; ww < kBlock / 64; ++ww)
-      v = threadIdx.x < 3 ? min(v, red[threadIdx.x][ww]) : max(v, red[threadIdx.x][ww]);
-    if (threadIdx.x < 3)
-      atomicMin(&bounds[threadIdx.x], v);
-    else
-      atomicMax(&bounds[threadIdx.x], v);
-  }
+  publish_bounds(lo, hi, bounds, report);
+  if (fl & kFlagNonFinite) report->nonfinite = 1;
+  if (fl & kFlagKeyRange) report->keyrange = 1;
 }
 
 // Sort key of a timestamp: its FP32 bits made monotone as unsigned (-0 counted as +0).
@@ -109,45 +82,95 @@ __global__ __launch_bounds__(kBlock) void ds_time_key_kernel(const float* __rest
 }
 
 // Cell key of the point at each position of `order` (identity if null): coordinates relative to
-// the bounds, packed x-major so that key order is (x, y, z) lexicographic order.
+// the bounds, packed x-major so that key order is (x, y, z) lexicographic order. One block per sort
+// tile; hist (may be null): the first pass's digit counts.
 __global__ __launch_bounds__(kBlock) void ds_cell_key_kernel(const int* __restrict__ kc,
                                                              long long n,
                                                              const int* __restrict__ order,
                                                              int lx, int ly, int lz, int sy,
                                                              int sz,
                                                              unsigned long long* __restrict__ key,
-                                                             int* __restrict__ val) {
+                                                             int* __restrict__ val,
+                                                             int* __restrict__ hist) {
+  unsigned digit[kSortTile / kBlock];
+  bool valid[kSortTile / kBlock];
+#pragma unroll
+  for (int q = 0; q < kSortTile / kBlock; ++q) {
+    const long long i = (long long)blockIdx.x * kSortTile + q * kBlock + threadIdx.x;
+    valid[q] = i < n;
+    digit[q] = 0;
+    if (!valid[q]) continue;
+    const long long j = order ? order[i] : i;
+    const unsigned long long k = ((unsigned long long)(kc[j] - lx) << sy) |
+                                 ((unsigned long long)(kc[n + j] - ly) << sz) |
+                                 (unsigned long long)(kc[2 * n + j] - lz);
+    key[i] = k;
+    val[i] = (int)j;
+    digit[q] = (unsigned)k;
+  }
+  if (hist) sort_tile_hist(digit, valid, hist + (size_t)blockIdx.x * 256);
+}
+
+// Time order within the cells: a point's place is the number of its cell's points before it in
+// (timestamp, index) order, counted directly (a cell holds a few points: for a sweep of 53,000
+// points one launch of a few us instead of four passes of a sort by time). A cell of more than
+// kMaxRanked points would cost its square: the call then sorts by time.
+constexpr int kMaxRanked = 4096;
+__global__ __launch_bounds__(kBlock) void ds_time_rank_kernel(
+    const int* __restrict__ val, long long n, const int* __restrict__ start,
+    const int* __restrict__ cells, const float* __restrict__ t, int* __restrict__ order,
+    BuildReport* __restrict__ report) {
+  const int C = *cells;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
-    const long long j = order ? order[i] : i;
-    key[i] = ((unsigned long long)(kc[j] - lx) << sy) |
-             ((unsigned long long)(kc[n + j] - ly) << sz) |
-             (unsigned long long)(kc[2 * n + j] - lz);
-    val[i] = (int)j;
+    int lo = 0, hi = C;  // start[lo] <= i < start[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (start[mid] <= i) lo = mid; else hi = mid;
+    }
+    const int s = start[lo], e = start[lo + 1];
+    const int me = val[i];
+    if (e - s > kMaxRanked) {
+      report->deep = 1;
+      order[i] = me;  // the count pass still runs over it
+      continue;
+    }
+    const float ti = t[me];
+    int rank = 0;
+    for (int j = s; j < e; ++j) {  // positions within a cell are in index order
+      const float tj = t[val[j]];
+      rank += tj < ti || (tj == ti && j < i) ? 1 : 0;
+    }
+    order[s + rank] = me;
   }
 }
 
-// One thread per cell (its first sorted position) walks the cell's points in (time, index)
-// order: the count pass stores the number of voxels at the cell's first position, the emit
-// pass writes every voxel's means at the offsets of the scanned counts.
+// One thread per cell walks the cell's points in (time, index) order: the count pass stores the
+// number of its voxels (0 past the cells), the emit pass writes every voxel's means at the offsets
+// of the scanned counts, unless they exceed the capacity.
 template <bool EMIT>
 __global__ __launch_bounds__(kBlock) void ds_walk_kernel(
-    const unsigned long long* __restrict__ key, const int* __restrict__ val, long long n,
-    const float* __restrict__ xyz, const float* __restrict__ t, double thr,
-    int* __restrict__ vcount, const int* __restrict__ voff, long long m, float* __restrict__ out,
-    float* __restrict__ tout) {
+    const int* __restrict__ val, long long n, const int* __restrict__ start,
+    const int* __restrict__ cells, const float* __restrict__ xyz, const float* __restrict__ t,
+    double thr, int* __restrict__ vcount, const int* __restrict__ voff,
+    const int* __restrict__ total, long long capacity, float* __restrict__ out,
+    float* __restrict__ tout, BuildReport* __restrict__ report) {
 #pragma clang fp contract(off)
+  const int C = *cells;
+  const long long m = EMIT ? *total : 0;
+  if (EMIT && blockIdx.x == 0 && threadIdx.x == 0) report->count = (int)m;
+  if (EMIT && m > capacity) return;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
-    const unsigned long long k0 = key[i];
-    if (i > 0 && key[i - 1] == k0) {
+    if (i >= C) {
       if (!EMIT) vcount[i] = 0;
       continue;
     }
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, st = 0.0;
     int cnt = 0, nv = 0;
     const long long o = EMIT ? voff[i] : 0;
-    for (long long j = i; j < n && key[j] == k0; ++j) {
+    const int e = start[i + 1];
+    for (int j = start[i]; j < e; ++j) {
       const long long p = val[j];
       const double tj = t ? (double)t[p] : 0.0;
       if (t && cnt > 0 && fabs(tj - st / (double)cnt) > thr) {
@@ -161,9 +184,11 @@ __global__ __launch_bounds__(kBlock) void ds_walk_kernel(
         s0 = s1 = s2 = st = 0.0;
         cnt = 0;
       }
-      s0 = s0 + (double)xyz[p];
-      s1 = s1 + (double)xyz[n + p];
-      s2 = s2 + (double)xyz[2 * n + p];
+      if (EMIT) {
+        s0 = s0 + (double)xyz[p];
+        s1 = s1 + (double)xyz[n + p];
+        s2 = s2 + (double)xyz[2 * n + p];
+      }
       st = st + tj;
       ++cnt;
     }
@@ -209,53 +234,40 @@ __device__ inline unsigned cell_hash(unsigned long long k) {  // SplitMix64 fina
   return (unsigned)k;
 }
 
-// Per block: min and max of every axis, and the finiteness check.
+// A float's bits as an int in the floats' order (its own inverse).
+__host__ __device__ inline int ordered_bits(int b) { return b ^ ((b >> 31) & 0x7fffffff); }
+
+// Minimum and maximum of every axis (as ordered bits), and the finiteness check.
 __global__ __launch_bounds__(kBlock) void knn_bounds_kernel(const float* __restrict__ xyz,
-                                                            long long n,
-                                                            float* __restrict__ part,
-                                                            unsigned* __restrict__ flags) {
-  __shared__ float red[6][kBlock / 64];
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  unsigned fl = 0;
+                                                            long long n, int* __restrict__ bounds,
+                                                            BuildReport* __restrict__ report) {
+  int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
+  bool bad = false;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
     for (int a = 0; a < 3; ++a) {
       const float v = xyz[a * n + i];
-      if (!isfinite(v)) fl |= kFlagNonFinite;
-      lo[a] = fminf(lo[a], v);
-      hi[a] = fmaxf(hi[a], v);
+      bad |= !isfinite(v);
+      const int b = ordered_bits(__float_as_int(v));
+      lo[a] = min(lo[a], b);
+      hi[a] = max(hi[a], b);
     }
-  for (int a = 0; a < 3; ++a)
-    for (int off = 32; off > 0; off >>= 1) {
-      lo[a] = fminf(lo[a], __shfl_xor(lo[a], off, 64));
-      hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], off, 64));
-    }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int a = 0; a < 3; ++a) {
-      red[a][w] = lo[a];
-      red[3 + a][w] = hi[a];
-    }
-  if (fl) atomicOr(flags, fl);
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    float v = red[threadIdx.x][0];
-    for (int ww = 1; ww < kBlock / 64; ++ww)
-      v = threadIdx.x < 3 ? fminf(v, red[threadIdx.x][ww]) : fmaxf(v, red[threadIdx.x][ww]);
-    part[blockIdx.x * 6 + threadIdx.x] = v;
-  }
+  publish_bounds(lo, hi, bounds, report);
+  if (bad) report->nonfinite = 1;
 }
 
 // Cell size estimate: for S sampled points (one block each), the binary exponent e of the
 // squared distance at which the count of points reaches k; the k-th neighbour then lies within
 // 2^((e + 1) / 2). est = INT_MAX if the cloud has fewer than k points, INT_MIN for duplicates.
-constexpr int kExpBins = 128;
-__global__ __launch_bounds__(kBlock) void knn_sample_kernel(const float* __restrict__ xyz,
-                                                            long long n, int S, int k,
-                                                            int* __restrict__ est) {
+// Most distances share a few exponents, so every lane of 16 counts in a copy of its own (one copy
+// for all lanes serialized on them: 31 us for 19,000 points).
+constexpr int kExpBins = 128, kExpCopies = 16, kSampleBlock = 512;
+__global__ __launch_bounds__(kSampleBlock) void knn_sample_kernel(const float* __restrict__ xyz,
+                                                                  long long n, int S, int k,
+                                                                  BuildReport* __restrict__ report) {
 #pragma clang fp contract(off)
-  __shared__ int hist[kExpBins];
-  for (int b = threadIdx.x; b < kExpBins; b += blockDim.x) hist[b] = 0;
+  __shared__ int hist[kExpBins][kExpCopies + 1];
+  for (int b = threadIdx.x; b < kExpBins * (kExpCopies + 1); b += blockDim.x) (&hist[0][0])[b] = 0;
   __syncthreads();
   const long long q = (long long)blockIdx.x * n / S;
   const double q0 = xyz[q], q1 = xyz[n + q], q2 = xyz[2 * n + q];
@@ -264,36 +276,53 @@ __global__ __launch_bounds__(kBlock) void knn_sample_kernel(const float* __restr
                  dz = (double)xyz[2 * n + j] - q2;
     const double d2 = (dx * dx + dy * dy) + dz * dz;
     const int b = d2 > 0.0 ? min(max(ilogb(d2), -62), 62) + 64 : 0;
-    atomicAdd(&hist[b], 1);
+    atomicAdd(&hist[b][threadIdx.x & (kExpCopies - 1)], 1);
+  }
+  __syncthreads();
+  if (threadIdx.x < kExpBins) {
+    int c = 0;
+    for (int r = 0; r < kExpCopies; ++r) c += hist[threadIdx.x][r];
+    hist[threadIdx.x][kExpCopies] = c;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     int cum = 0, e = INT_MAX;
     for (int b = 0; b < kExpBins; ++b) {
-      cum += hist[b];
+      cum += hist[b][kExpCopies];
       if (cum >= k) {
         e = b == 0 ? INT_MIN : b - 64;
         break;
       }
     }
-    est[blockIdx.x] = e;
+    report->est[blockIdx.x] = e;
   }
 }
 
-// Morton code of every point's cell (coordinates relative to the cloud's lowest cell).
+// Morton code of every point's cell (coordinates relative to the cloud's lowest cell). One block per
+// sort tile; hist (may be null): the first pass's digit counts.
 __global__ __launch_bounds__(kBlock) void knn_code_kernel(const float* __restrict__ xyz,
                                                           long long n, double inv_h, int lx,
                                                           int ly, int lz,
                                                           unsigned long long* __restrict__ code,
-                                                          int* __restrict__ idx) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
+                                                          int* __restrict__ idx,
+                                                          int* __restrict__ hist) {
+  unsigned digit[kSortTile / kBlock];
+  bool valid[kSortTile / kBlock];
+#pragma unroll
+  for (int q = 0; q < kSortTile / kBlock; ++q) {
+    const long long i = (long long)blockIdx.x * kSortTile + q * kBlock + threadIdx.x;
+    valid[q] = i < n;
+    digit[q] = 0;
+    if (!valid[q]) continue;
     const int cx = (int)floor((double)xyz[i] * inv_h) - lx;
     const int cy = (int)floor((double)xyz[n + i] * inv_h) - ly;
     const int cz = (int)floor((double)xyz[2 * n + i] * inv_h) - lz;
-    code[i] = morton3(cx, cy, cz);
+    const unsigned long long c = morton3(cx, cy, cz);
+    code[i] = c;
     idx[i] = (int)i;
+    digit[q] = (unsigned)c;
   }
+  if (hist) sort_tile_hist(digit, valid, hist + (size_t)blockIdx.x * 256);
 }
 
 // Sorted copy of the positions.
@@ -311,11 +340,20 @@ __global__ __launch_bounds__(kBlock) void knn_gather_kernel(const float* __restr
 // Grid level L has cells 8^L times the finest along each axis; its cell of a point is the
 // finest cell's relative coordinates shifted right by 3L, so its Morton code is the finest code
 // shifted right by 9L and every level's cells are contiguous runs of the one sorted order.
-// Two passes per level: a cell's first position claims a hash slot and stores its start, then
-// its last position finds the slot and stores the count.
+// Two launches for all levels (blockIdx.y): a cell's first position claims a hash slot and stores its
+// start, then its last position finds the slot and stores the count.
+constexpr int kMaxLevels = 8;  // 3 more bits per level: 8 levels cover 2^21 finest cells
+struct LevelTables {
+  CellSlot* slots[kMaxLevels];
+  unsigned mask[kMaxLevels];
+};
+
 __global__ __launch_bounds__(kBlock) void knn_level_head_kernel(
-    long long n, const unsigned long long* __restrict__ code, int shift,
-    CellSlot* __restrict__ slots, unsigned mask, unsigned* __restrict__ flags) {
+    long long n, const unsigned long long* __restrict__ code, LevelTables tab,
+    int* __restrict__ internal) {
+  const int shift = 9 * blockIdx.y;
+  CellSlot* slots = tab.slots[blockIdx.y];
+  const unsigned mask = tab.mask[blockIdx.y];
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
     const unsigned long long c = code[i] >> shift;
@@ -331,13 +369,16 @@ __global__ __launch_bounds__(kBlock) void knn_level_head_kernel(
       }
       s = (s + 1) & mask;
     }
-    if (!placed) atomicOr(flags, kFlagInternal);
+    if (!placed) *internal = 1;
   }
 }
 
 __global__ __launch_bounds__(kBlock) void knn_level_tail_kernel(
-    long long n, const unsigned long long* __restrict__ code, int shift,
-    CellSlot* __restrict__ slots, unsigned mask, unsigned* __restrict__ flags) {
+    long long n, const unsigned long long* __restrict__ code, LevelTables tab,
+    int* __restrict__ internal) {
+  const int shift = 9 * blockIdx.y;
+  CellSlot* slots = tab.slots[blockIdx.y];
+  const unsigned mask = tab.mask[blockIdx.y];
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
     const unsigned long long c = code[i] >> shift;
@@ -352,11 +393,9 @@ __global__ __launch_bounds__(kBlock) void knn_level_tail_kernel(
       }
       s = (s + 1) & mask;
     }
-    if (!found) atomicOr(flags, kFlagInternal);
+    if (!found) *internal = 1;
   }
 }
-
-constexpr int kMaxLevels = 8;  // 3 more bits per level: 8 levels cover 2^21 finest cells
 
 struct KnnGrid {
   const float* xs;         // [3][n] sorted positions
@@ -696,104 +735,148 @@ vgicp_status downsample(const float* xyz, const float* t, int64_t n, double res,
                         hipStream_t s) {
   *n_out = 0;
   if (n == 0) return VGICP_OK;
-  Scratch sc;
-  int *kc = nullptr, *bounds = nullptr, *vA = nullptr, *vB = nullptr, *vcnt = nullptr,
-      *voff = nullptr;
-  unsigned long long *kA = nullptr, *kB = nullptr;
-  unsigned* flags = nullptr;
+  HostBlock hb;
+  if (!hb.p) return fail(VGICP_E_OOM, "pinned host block");
+  BuildReport* report = static_cast<BuildReport*>(hb.p);
+  volatile BuildReport* rep = report;
+  const bool small = n <= kSortMax;
+  const size_t words = small ? sort_hist_ints(1, n) : 0, N = (size_t)n;
+  Arena ar;
+  ar.need<int>(3 * N);
+  ar.need<int>(8);
+  ar.need<int>(words);
+  ar.need<unsigned long long>(N);
+  ar.need<unsigned long long>(N);
+  for (int i = 0; i < 5; ++i) ar.need<int>(N);
+  ar.need<int>(N + 1);
+  ar.need<int>(kRunTiles);
+  ar.need<int>(2);
   hipError_t e;
-  if ((e = sc.alloc(&kc, 3 * (size_t)n)) || (e = sc.alloc(&bounds, 6)) ||
-      (e = sc.alloc(&flags, 1)) || (e = sc.alloc(&kA, (size_t)n)) ||
-      (e = sc.alloc(&kB, (size_t)n)) || (e = sc.alloc(&vA, (size_t)n)) ||
-      (e = sc.alloc(&vB, (size_t)n)) || (e = sc.alloc(&vcnt, (size_t)n)) ||
-      (e = sc.alloc(&voff, (size_t)n)))
-    return hip_fail(e, "hipMalloc (downsample)");
+  if ((e = ar.get(s))) return hip_fail(e, "pool allocation (downsample)");
+  int* kc = ar.take<int>(3 * N);
+  int* bounds = ar.take<int>(8);
+  SortBuffers sb;
+  sb.hist = ar.take<int>(words);
+  sb.k = ar.take<unsigned long long>(N);
+  sb.kt = ar.take<unsigned long long>(N);
+  sb.v = ar.take<int>(N);
+  sb.vt = ar.take<int>(N);
+  int* vcnt = ar.take<int>(N);
+  int* voff = ar.take<int>(N);
+  int* ranked = ar.take<int>(N);
+  int* start = ar.take<int>(N + 1);
+  int* tile_counts = ar.take<int>(kRunTiles);
+  int* totals = ar.take<int>(2);  // cells, voxels
   const bool p2 = pow2_res(res);
-  bounds_reset_kernel<<<1, 64, 0, s>>>(bounds, flags);
+  launch_call_init(nullptr, 0, bounds, report, s);
   ds_cells_kernel<<<std::min(grid_for(n), 128), kBlock, 0, s>>>(xyz, t, n, p2 ? 1 : 0, res, 1.0 / res, kc,
-                                                 bounds, flags);
-  int hb[6];
-  unsigned hf = 0;
-  if ((e = hipGetLastError()) || (e = hipMemcpyAsync(hb, bounds, sizeof(hb), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) ||
-      (e = hipStreamSynchronize(s)))
+                                                 bounds, report);
+  if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
     return hip_fail(e, "downsample cells");
-  if (hf & kFlagNonFinite) return fail(VGICP_E_NONFINITE, "non-finite point or timestamp");
-  if (hf & kFlagKeyRange) return fail(VGICP_E_KEY_RANGE, "cell coordinate out of range");
-  const int bx = bits_for((long long)hb[3] - hb[0]), by = bits_for((long long)hb[4] - hb[1]),
-            bz = bits_for((long long)hb[5] - hb[2]);
-  const int* order = nullptr;
-  if (t) {  // (time, index) order first; the stable cell sort below keeps it within a cell
-    ds_time_key_kernel<<<grid_for(n), kBlock, 0, s>>>(t, n, kA, vA);
-    if ((e = hipGetLastError()) || (e = radix_sort_pairs(&kA, &vA, &kB, &vB, n, 32, flags, s, sc)))
-      return hip_fail(e, "downsample time sort");
-    order = vA;
-  }
-  ds_cell_key_kernel<<<grid_for(n), kBlock, 0, s>>>(kc, n, order, hb[0], hb[1], hb[2], by + bz,
-                                                    bz, kB, vB);
-  std::swap(kA, kB);
-  std::swap(vA, vB);
-  if ((e = hipGetLastError()) ||
-      (e = radix_sort_pairs(&kA, &vA, &kB, &vB, n, bx + by + bz, flags, s, sc)))
-    return hip_fail(e, "downsample cell sort");
+  if (rep->nonfinite) return fail(VGICP_E_NONFINITE, "non-finite point or timestamp");
+  if (rep->keyrange) return fail(VGICP_E_KEY_RANGE, "cell coordinate out of range");
+  const int lo[3] = {rep->lo[0], rep->lo[1], rep->lo[2]};
+  const int bx = bits_for((long long)rep->hi[0] - lo[0]), by = bits_for((long long)rep->hi[1] - lo[1]),
+            bz = bits_for((long long)rep->hi[2] - lo[2]);
   const double thr = d_scan / 10.0;
-  ds_walk_kernel<false><<<grid_for(n), kBlock, 0, s>>>(kA, vA, n, xyz, t, thr, vcnt, nullptr, 0,
-                                                       nullptr, nullptr);
-  if ((e = hipGetLastError()) || (e = scan_exclusive(vcnt, voff, n, s, sc)))
-    return hip_fail(e, "downsample count");
-  int last[2] = {0, 0};
-  if ((e = hipMemcpyAsync(&last[0], voff + n - 1, sizeof(int), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(&last[1], vcnt + n - 1, sizeof(int), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) ||
-      (e = hipStreamSynchronize(s)))
-    return hip_fail(e, "downsample count");
-  if (hf & kFlagInternal) return fail(VGICP_E_HIP, "internal error in the downsample sort");
-  const int64_t m = (int64_t)last[0] + last[1];
+  // the cells' points in (time, index) order: sorted by cell and ranked within the cells, or (long
+  // clouds, or a cell too full to rank) sorted by time first, which the stable cell sort keeps
+  bool by_time = t != nullptr && !small;
+  for (;;) {
+    Scratch sc;
+    const int* order = nullptr;
+    if (by_time) {
+      ds_time_key_kernel<<<grid_for(n), kBlock, 0, s>>>(t, n, sb.k, sb.v);
+      if ((e = hipGetLastError()) ||
+          (e = radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, 32, &report->internal, s, sc)))
+        return hip_fail(e, "downsample time sort");
+      order = sb.v;
+    }
+    const bool passes = small && !by_time;
+    ds_cell_key_kernel<<<(unsigned)sort_tiles(n), kBlock, 0, s>>>(
+        kc, n, order, lo[0], lo[1], lo[2], by + bz, bz, sb.kt, sb.vt, passes ? sb.hist : nullptr);
+    std::swap(sb.k, sb.kt);
+    std::swap(sb.v, sb.vt);
+    e = passes ? sort_passes(sb, nullptr, 1, n, bx + by + bz, &report->internal, s)
+               : radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, bx + by + bz,
+                                  &report->internal, s, sc);
+    if (e) return hip_fail(e, "downsample cell sort");
+    if ((e = run_starts(sb.k, n, start, tile_counts, &totals[0], s)))
+      return hip_fail(e, "downsample cells");
+    const int* val = sb.v;
+    if (t && !by_time) {
+      ds_time_rank_kernel<<<grid_for(n), kBlock, 0, s>>>(sb.v, n, start, &totals[0], t, ranked,
+                                                         report);
+      val = ranked;
+    }
+    ds_walk_kernel<false><<<grid_for(n), kBlock, 0, s>>>(val, n, start, &totals[0], xyz, t, thr,
+                                                         vcnt, nullptr, nullptr, 0, nullptr,
+                                                         nullptr, report);
+    if ((e = hipGetLastError()) || (e = scan_values(vcnt, voff, n, tile_counts, &totals[1], s)))
+      return hip_fail(e, "downsample count");
+    // a cell left unranked has no valid order: nothing is written before that is known
+    if (t && !by_time) {
+      if ((e = hipStreamSynchronize(s))) return hip_fail(e, "downsample count");
+      if (rep->deep) {
+        by_time = true;
+        continue;
+      }
+    }
+    ds_walk_kernel<true><<<grid_for(n), kBlock, 0, s>>>(val, n, start, &totals[0], xyz, t, thr,
+                                                        nullptr, voff, &totals[1], capacity,
+                                                        xyz_out, t ? t_out : nullptr, report);
+    if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
+      return hip_fail(e, "downsample emit");
+    break;
+  }
+  if (rep->internal) return fail(VGICP_E_HIP, "internal error in the downsample sort");
+  const int64_t m = rep->count;
   *n_out = m;
   if (m > capacity) return fail(VGICP_E_CAPACITY, "downsampled cloud exceeds the output capacity");
-  ds_walk_kernel<true><<<grid_for(n), kBlock, 0, s>>>(kA, vA, n, xyz, t, thr, nullptr, voff, m,
-                                                      xyz_out, t ? t_out : nullptr);
-  if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
-    return hip_fail(e, "downsample emit");
   return VGICP_OK;
 }
 
 vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, hipStream_t s) {
   if (n == 0) return VGICP_OK;
-  Scratch sc;
   hipError_t e;
-  const int nb = std::min<int>(grid_for(n), 1024);
-  float* part = nullptr;
-  unsigned* flags = nullptr;
-  if ((e = sc.alloc(&part, (size_t)nb * 6)) || (e = sc.alloc(&flags, 1)))
-    return hip_fail(e, "hipMalloc (knn)");
-  if ((e = hipMemsetAsync(flags, 0, sizeof(unsigned), s))) return hip_fail(e, "hipMemsetAsync");
-  knn_bounds_kernel<<<nb, kBlock, 0, s>>>(xyz, n, part, flags);
+  HostBlock hb;
+  if (!hb.p) return fail(VGICP_E_OOM, "pinned host block");
+  BuildReport* report = static_cast<BuildReport*>(hb.p);
+  volatile BuildReport* rep = report;
+  const bool small = n <= kSortMax;
+  const size_t words = small ? sort_hist_ints(1, n) : 0, N = (size_t)n;
+  Arena ar;
+  ar.need<int>(8);
+  ar.need<int>(words);
+  ar.need<unsigned long long>(N);
+  ar.need<unsigned long long>(N);
+  ar.need<int>(N);
+  ar.need<int>(N);
+  ar.need<float>(3 * N);
+  if ((e = ar.get(s))) return hip_fail(e, "pool allocation (knn)");
+  int* bounds = ar.take<int>(8);
+  SortBuffers sb;
+  sb.hist = ar.take<int>(words);
+  sb.k = ar.take<unsigned long long>(N);
+  sb.kt = ar.take<unsigned long long>(N);
+  sb.v = ar.take<int>(N);
+  sb.vt = ar.take<int>(N);
+  float* xs = ar.take<float>(3 * N);
+  launch_call_init(nullptr, 0, bounds, report, s);
+  knn_bounds_kernel<<<std::min(grid_for(n), 128), kBlock, 0, s>>>(xyz, n, bounds, report);
   // the cell estimate runs beside the bounds (a non-finite cloud is rejected after it)
   const int S = cell > 0.0 ? 0 : (int)std::min<int64_t>(n, 64);
-  int* est = nullptr;
-  if (S > 0) {
-    if ((e = sc.alloc(&est, (size_t)S))) return hip_fail(e, "hipMalloc (knn)");
-    knn_sample_kernel<<<S, kBlock, 0, s>>>(xyz, n, S, k, est);
-  }
-  std::vector<float> hp((size_t)nb * 6);
-  std::vector<int> he(S);
-  unsigned hf = 0;
-  if ((e = hipGetLastError()) ||
-      (e = hipMemcpyAsync(hp.data(), part, hp.size() * sizeof(float), hipMemcpyDeviceToHost, s)) ||
-      (S > 0 && (e = hipMemcpyAsync(he.data(), est, S * sizeof(int), hipMemcpyDeviceToHost, s))) ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) ||
-      (e = hipStreamSynchronize(s)))
-    return hip_fail(e, "knn bounds");
-  if (hf & kFlagNonFinite) return fail(VGICP_E_NONFINITE, "non-finite point");
+  if (S > 0) knn_sample_kernel<<<S, kSampleBlock, 0, s>>>(xyz, n, S, k, report);
+  if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s))) return hip_fail(e, "knn bounds");
+  if (rep->nonfinite) return fail(VGICP_E_NONFINITE, "non-finite point");
   double lo[3], hi[3], maxabs = 0.0;
   for (int a = 0; a < 3; ++a) {
-    lo[a] = hp[a];
-    hi[a] = hp[3 + a];
-    for (int b = 1; b < nb; ++b) {
-      lo[a] = std::min<double>(lo[a], hp[b * 6 + a]);
-      hi[a] = std::max<double>(hi[a], hp[b * 6 + 3 + a]);
-    }
+    const int l = ordered_bits(rep->lo[a]), h = ordered_bits(rep->hi[a]);
+    float f;
+    std::memcpy(&f, &l, 4);
+    lo[a] = f;
+    std::memcpy(&f, &h, 4);
+    hi[a] = f;
     maxabs = std::max(maxabs, std::max(std::fabs(lo[a]), std::fabs(hi[a])));
   }
   int eh = 0;  // cell edge 2^eh
@@ -801,8 +884,10 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
     eh = (int)std::ceil(std::log2(cell));
   } else {
     std::vector<int> r;
-    for (int v : he)
+    for (int i = 0; i < S; ++i) {
+      const int v = rep->est[i];
       if (v != INT_MIN) r.push_back(v == INT_MAX ? 62 : (v + 2) / 2);  // 2^r >= k-th distance
+    }
     if (!r.empty()) {
       std::nth_element(r.begin(), r.begin() + r.size() / 2, r.end());
       eh = r[r.size() / 2];
@@ -822,35 +907,44 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   const int bits = 3 * bits_for(ext_max);
   int levels = 1;
   while (levels < kMaxLevels && (ext_max >> (3 * (levels - 1))) > 0) ++levels;
-  unsigned long long *kA = nullptr, *kB = nullptr;
-  int *vA = nullptr, *vB = nullptr;
-  float* xs = nullptr;
-  if ((e = sc.alloc(&kA, (size_t)n)) || (e = sc.alloc(&kB, (size_t)n)) ||
-      (e = sc.alloc(&vA, (size_t)n)) || (e = sc.alloc(&vB, (size_t)n)) ||
-      (e = sc.alloc(&xs, 3 * (size_t)n)))
-    return hip_fail(e, "hipMalloc (knn)");
-  knn_code_kernel<<<grid_for(n), kBlock, 0, s>>>(xyz, n, inv_h, g.lo[0], g.lo[1], g.lo[2], kA, vA);
-  if ((e = hipGetLastError()) || (e = radix_sort_pairs(&kA, &vA, &kB, &vB, n, bits, flags, s, sc)))
-    return hip_fail(e, "knn sort");
-  knn_gather_kernel<<<grid_for(n), kBlock, 0, s>>>(xyz, n, vA, xs);
+  // one buffer for the cell tables of all levels
+  LevelTables tab{};
+  size_t slots_total = 0, at[kMaxLevels];
   for (int L = 0; L < levels; ++L) {
     // cells on level L: at most n, and at most the product of the level's extents
     long long cells = 1;
     for (int a = 0; a < 3; ++a) cells = std::min<long long>(cells * ((g.ext[a] >> (3 * L)) + 1), n);
     unsigned cap = 1;
     while ((long long)cap < 2 * cells) cap <<= 1;
-    CellSlot* slots = nullptr;
-    if ((e = sc.alloc(&slots, (size_t)cap))) return hip_fail(e, "hipMalloc (knn)");
-    if ((e = hipMemsetAsync(slots, 0xff, (size_t)cap * sizeof(CellSlot), s)))
-      return hip_fail(e, "hipMemsetAsync");
-    knn_level_head_kernel<<<grid_for(n), kBlock, 0, s>>>(n, kA, 9 * L, slots, cap - 1, flags);
-    knn_level_tail_kernel<<<grid_for(n), kBlock, 0, s>>>(n, kA, 9 * L, slots, cap - 1, flags);
-    g.slots[L] = slots;
-    g.mask[L] = cap - 1;
+    tab.mask[L] = cap - 1;
+    at[L] = slots_total;
+    slots_total += cap;
   }
+  Arena at_ar;
+  Scratch sc;
+  at_ar.need<CellSlot>(slots_total);
+  if ((e = at_ar.get(s))) return hip_fail(e, "pool allocation (knn)");
+  CellSlot* slots = at_ar.take<CellSlot>(slots_total);
+  for (int L = 0; L < levels; ++L) {
+    tab.slots[L] = slots + at[L];
+    g.slots[L] = tab.slots[L];
+    g.mask[L] = tab.mask[L];
+  }
+  if ((e = hipMemsetAsync(slots, 0xff, slots_total * sizeof(CellSlot), s)))
+    return hip_fail(e, "hipMemsetAsync");
+  knn_code_kernel<<<(unsigned)sort_tiles(n), kBlock, 0, s>>>(xyz, n, inv_h, g.lo[0], g.lo[1],
+                                                             g.lo[2], sb.k, sb.v,
+                                                             small ? sb.hist : nullptr);
+  e = small ? sort_passes(sb, nullptr, 1, n, bits, &report->internal, s)
+            : radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, bits, &report->internal, s, sc);
+  if (e) return hip_fail(e, "knn sort");
+  knn_gather_kernel<<<grid_for(n), kBlock, 0, s>>>(xyz, n, sb.v, xs);
+  const dim3 lgrid((unsigned)grid_for(n), (unsigned)levels);
+  knn_level_head_kernel<<<lgrid, kBlock, 0, s>>>(n, sb.k, tab, &report->internal);
+  knn_level_tail_kernel<<<lgrid, kBlock, 0, s>>>(n, sb.k, tab, &report->internal);
   g.levels = levels;
   g.xs = xs;
-  g.perm = vA;
+  g.perm = sb.v;
   g.h = h;
   g.inv_h = inv_h;
   g.n = n;
@@ -861,11 +955,8 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
     knn_query_kernel<16><<<qgrid, kBlock, 0, s>>>(g, k, nbr);
   else
     knn_query_kernel<32><<<qgrid, kBlock, 0, s>>>(g, k, nbr);
-  if ((e = hipGetLastError()) ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) ||
-      (e = hipStreamSynchronize(s)))
-    return hip_fail(e, "knn query");
-  if (hf & kFlagInternal) return fail(VGICP_E_HIP, "internal error in the neighbour search");
+  if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s))) return hip_fail(e, "knn query");
+  if (rep->internal) return fail(VGICP_E_HIP, "internal error in the neighbour search");
   return VGICP_OK;
 }
 

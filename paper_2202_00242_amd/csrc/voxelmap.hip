@@ -19,6 +19,7 @@
 
 #include "device_math.h"
 #include "internal.h"
+#include "sort.h"
 
 namespace vgicp {
 namespace {
@@ -36,7 +37,7 @@ __global__ __launch_bounds__(kBlock) void coords_kernel(const float* __restrict_
                                                         long long n, int pow2, double res,
                                                         double inv_res, int* __restrict__ kc,
                                                         int* __restrict__ bounds,
-                                                        unsigned* __restrict__ flags) {
+                                                        BuildReport* __restrict__ report) {
   int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
   unsigned fl = 0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -60,49 +61,52 @@ __global__ __launch_bounds__(kBlock) void coords_kernel(const float* __restrict_
       hi[a] = max(hi[a], __shfl_xor(hi[a], off, 64));
     }
   }
-  // one set of atomics per block: same-address atomics from every wave serialize in L2
-  __shared__ int red[6][kBlock / 64];
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int a = 0; a < 3; ++a) {
-      red[a][w] = lo[a];
-      red[3 + a][w] = hi[a];
-    }
-  if (fl) atomicOr(flags, fl);
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    int v = red[threadIdx.x][0];
-    for (int ww = 1; ww < kBlock / 64; ++ww)
-      v = threadIdx.x < 3 ? min(v, red[threadIdx.x][ww]) : max(v, red[threadIdx.x][ww]);
-    if (threadIdx.x < 3)
-      atomicMin(&bounds[threadIdx.x], v);
-    else
-      atomicMax(&bounds[threadIdx.x], v);
-  }
+  publish_bounds(lo, hi, bounds, report);
+  if (fl & kFlagNonFinite) report->nonfinite = 1;
+  if (fl & kFlagKeyRange) report->keyrange = 1;
 }
 
-__global__ void bounds_init_kernel(int* bounds, unsigned* flags) {
-  if (threadIdx.x < 3) {
-    bounds[threadIdx.x] = INT_MAX;
-    bounds[3 + threadIdx.x] = INT_MIN;
+// Start of a call: zeroed words (digit counts), the integer bounds with their ticket, the report.
+__global__ __launch_bounds__(kBlock) void call_init_kernel(int* __restrict__ zero, long long words,
+                                                           int* __restrict__ bounds,
+                                                           BuildReport* __restrict__ report) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < words;
+       i += (long long)gridDim.x * blockDim.x)
+    zero[i] = 0;
+  if (blockIdx.x == 0) {
+    if (bounds && threadIdx.x < 7)
+      bounds[threadIdx.x] = threadIdx.x < 3 ? INT_MAX : (threadIdx.x < 6 ? INT_MIN : 0);
+    if (report)
+      for (unsigned i = threadIdx.x; i < sizeof(BuildReport) / 4; i += blockDim.x)
+        reinterpret_cast<int*>(report)[i] = 0;
   }
-  if (threadIdx.x == 0) *flags = 0u;
 }
 
 // ------------------------------------------------------------------ step 2: sort keys
 
+// One block per sort tile; hist (may be null): the first pass's digit counts of every tile.
 __global__ __launch_bounds__(kBlock) void sortkey_kernel(const int* __restrict__ kc, long long n,
                                                          int lx, int ly, int lz, int by, int bz,
                                                          unsigned long long* __restrict__ key,
-                                                         int* __restrict__ val) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
+                                                         int* __restrict__ val,
+                                                         int* __restrict__ hist) {
+  unsigned digit[kSortTile / kBlock];
+  bool valid[kSortTile / kBlock];
+#pragma unroll
+  for (int j = 0; j < kSortTile / kBlock; ++j) {
+    const long long i = (long long)blockIdx.x * kSortTile + j * kBlock + threadIdx.x;
+    valid[j] = i < n;
+    digit[j] = 0;
+    if (!valid[j]) continue;
     const unsigned long long x = (unsigned long long)(kc[i] - lx);
     const unsigned long long y = (unsigned long long)(kc[n + i] - ly);
     const unsigned long long z = (unsigned long long)(kc[2 * n + i] - lz);
-    key[i] = (x << (by + bz)) | (y << bz) | z;
+    const unsigned long long k = (x << (by + bz)) | (y << bz) | z;
+    key[i] = k;
     val[i] = (int)i;
+    digit[j] = (unsigned)k;
   }
+  if (hist) sort_tile_hist(digit, valid, hist + (size_t)blockIdx.x * 256);
 }
 
 // ------------------------------------------------------------------ exclusive scan (int)
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(kBlock) void radix_hist_kernel(
 __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(
     const unsigned long long* __restrict__ kin, const int* __restrict__ vin,
     unsigned long long* __restrict__ kout, int* __restrict__ vout, long long n, int shift,
-    const int* __restrict__ offsets, int ntiles, unsigned* __restrict__ flags) {
+    const int* __restrict__ offsets, int ntiles, int* __restrict__ internal) {
   __shared__ int running[256];
   __shared__ int wcount[kBlock / 64][256];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(
         kout[off] = k;
         vout[off] = v;
       } else {
-        atomicOr(flags, kFlagInternal);
+        *internal = 1;
       }
     }
     __syncthreads();
@@ -234,76 +238,269 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(
   }
 }
 
+// One pass of the sort up to kSortMax pairs: block (tile, segment). Its digits' destinations are the
+// digit totals below, the predecessors' counts of the digit, and the rank within the tile (wave
+// ballots over items in order). Adding up the predecessors is at most 256 coalesced rows of 1 KB, and
+// spares the three launches of a scan (113,000 points: five launches and 25 us a pass before, two and
+// 13 us now; counting the next pass's digits here, by atomics on the destination tile's row, took
+// 16); beyond kSortMax the rows outgrow the keys.
+__global__ __launch_bounds__(kBlock) void sort_pass_kernel(
+    const unsigned long long* __restrict__ kin, const int* __restrict__ vin,
+    unsigned long long* __restrict__ kout, int* __restrict__ vout,
+    const SortSeg* __restrict__ segs, int n_one, int shift, int max_tiles,
+    const int* __restrict__ hist, int* __restrict__ internal) {
+  constexpr int J = kSortTile / kBlock;
+  __shared__ int wcnt[kBlock / 64][256];
+  const int seg = blockIdx.y, tile = blockIdx.x;
+  const long long off = segs ? segs[seg].off : 0;
+  const int n = segs ? segs[seg].n : n_one;
+  if (tile * kSortTile >= n) return;
+  const int ntiles = (n + kSortTile - 1) / kSortTile;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  for (int q = 0; q < kBlock / 64; ++q) wcnt[q][t] = 0;
+  // thread t is digit t
+  const int* h = hist + (size_t)seg * max_tiles * 256 + t;
+  int before = 0, all = 0;
+  int r = 0;
+  for (; r < ntiles; r += 32) {  // 32 rows in flight: each comes from beyond this XCD's L2
+    int c[32];
+#pragma unroll
+    for (int q = 0; q < 32; ++q) c[q] = r + q < ntiles ? h[(size_t)(r + q) * 256] : 0;
+#pragma unroll
+    for (int q = 0; q < 32; ++q) {
+      all += c[q];
+      before += r + q < tile ? c[q] : 0;
+    }
+  }
+  int total;
+  const int digit_base = block_prefix_256(all, total) + before;
+  // wave w ranks the items w * 256 .. + 255 of the tile, 64 at a time
+  const unsigned long long lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+  unsigned long long key[J];
+  int val[J], dgt[J], rank[J];
+  bool valid[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int i = tile * kSortTile + w * (kSortTile / 4) + j * 64 + lane;
+    valid[j] = i < n;
+    key[j] = valid[j] ? kin[off + i] : 0ull;
+    val[j] = valid[j] ? vin[off + i] : 0;
+    dgt[j] = (int)((key[j] >> shift) & 255ull);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    unsigned long long peers = __ballot(valid[j]);
+    for (int bit = 0; bit < 8; ++bit) {
+      const bool set = (dgt[j] >> bit) & 1;
+      const unsigned long long m = __ballot(set);
+      peers &= set ? m : ~m;
+    }
+    const int pos = __popcll(peers & lt);
+    rank[j] = pos + (valid[j] ? wcnt[w][dgt[j]] : 0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (valid[j] && pos == 0) wcnt[w][dgt[j]] += __popcll(peers);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  __syncthreads();
+  int run = digit_base;
+  for (int q = 0; q < kBlock / 64; ++q) {
+    const int c = wcnt[q][t];
+    wcnt[q][t] = run;
+    run += c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    if (!valid[j]) continue;
+    const int dst = wcnt[w][dgt[j]] + rank[j];
+    if (dst < 0 || dst >= n) {
+      *internal = 1;
+      continue;
+    }
+    kout[off + dst] = key[j];
+    vout[off + dst] = val[j];
+  }
+}
+
+// Digit counts of every tile for a pass after the first.
+__global__ __launch_bounds__(kBlock) void sort_hist_kernel(
+    const unsigned long long* __restrict__ key, const SortSeg* __restrict__ segs, int n_one,
+    int shift, int max_tiles, int* __restrict__ hist) {
+  const int n = segs ? segs[blockIdx.y].n : n_one;
+  const long long off = segs ? segs[blockIdx.y].off : 0;
+  if ((int)blockIdx.x * kSortTile >= n) return;
+  unsigned digit[kSortTile / kBlock];
+  bool valid[kSortTile / kBlock];
+#pragma unroll
+  for (int j = 0; j < kSortTile / kBlock; ++j) {
+    const int i = blockIdx.x * kSortTile + j * kBlock + threadIdx.x;
+    valid[j] = i < n;
+    digit[j] = valid[j] ? (unsigned)(key[off + i] >> shift) : 0u;
+  }
+  sort_tile_hist(digit, valid, hist + ((size_t)blockIdx.y * max_tiles + blockIdx.x) * 256);
+}
+
+// ------------------------------------------------------------------ scans over at most kRunTiles blocks
+
+// What a scan adds up: the heads of runs of equal keys, an int array, or the voxels of bricks.
+struct RunHeads {
+  const unsigned long long* key;
+  int* start;
+  long long n;
+  __device__ int value(long long i) const { return i == 0 || key[i] != key[i - 1] ? 1 : 0; }
+  __device__ void put(long long i, int base, int v) const {
+    if (v) start[base] = (int)i;
+  }
+  __device__ void end(int total) const { start[total] = (int)n; }
+};
+struct Ints {
+  const int* in;
+  int* out;
+  long long n;
+  __device__ int value(long long i) const { return in[i]; }
+  __device__ void put(long long i, int base, int) const { out[i] = base; }
+  __device__ void end(int) const {}
+};
+struct BrickVoxels {
+  Brick* b;
+  long long n;
+  __device__ int value(long long i) const { return __popc(b[i].mask); }
+  __device__ void put(long long i, int base, int) const { b[i].base = base; }
+  __device__ void end(int) const {}
+};
+
+// Two launches instead of three per level: a block's total, then every block adds up its
+// predecessors' totals (at most kRunTiles, four loads a thread) and walks its items. Block b has the
+// items b * per .. + per - 1 (per: a multiple of 1,024).
+template <class Op>
+__global__ __launch_bounds__(kBlock) void scan_total_kernel(Op op, long long per,
+                                                            int* __restrict__ tile_counts) {
+  const long long first = blockIdx.x * per, end = min(first + per, op.n);
+  int v = 0;
+  for (long long i = first + threadIdx.x; i < end; i += kBlock) v += op.value(i);
+  const int total = block_total_256(v);
+  if (threadIdx.x == 0) tile_counts[blockIdx.x] = total;
+}
+
+template <class Op>
+__global__ __launch_bounds__(kBlock) void scan_put_kernel(Op op, long long per,
+                                                          const int* __restrict__ tile_counts,
+                                                          int* __restrict__ total_out) {
+  int v = 0;
+  for (int t = threadIdx.x; t < (int)blockIdx.x; t += kBlock) v += tile_counts[t];
+  int run = block_total_256(v);
+  const long long first = blockIdx.x * per, end = min(first + per, op.n);
+  for (long long base = first; base < end; base += 1024) {
+    const long long i0 = base + 4 * threadIdx.x;
+    int x[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[j] = i0 + j < end ? op.value(i0 + j) : 0;
+      sum += x[j];
+    }
+    int total;
+    int at = run + block_prefix_256(sum, total);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (i0 + j < end) op.put(i0 + j, at, x[j]);
+      at += x[j];
+    }
+    run += total;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    op.end(run);
+    if (total_out) *total_out = run;
+  }
+}
+
+template <class Op>
+hipError_t scan_with(Op op, int* tile_counts, int* total, hipStream_t s) {
+  const long long units = std::max<long long>((op.n + 1023) / 1024, 1);
+  const long long per = (units + kRunTiles - 1) / kRunTiles * 1024;
+  const unsigned blocks = (unsigned)std::max<long long>((op.n + per - 1) / per, 1);
+  scan_total_kernel<<<blocks, kBlock, 0, s>>>(op, per, tile_counts);
+  scan_put_kernel<<<blocks, kBlock, 0, s>>>(op, per, tile_counts, total);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ steps 4-6
 
-__global__ __launch_bounds__(kBlock) void heads_kernel(const unsigned long long* __restrict__ key,
-                                                       long long n, int* __restrict__ head) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    head[i] = (i == 0 || key[i] != key[i - 1]) ? 1 : 0;
+__device__ inline void voxel_box_coords(long long k, int lo0, int lo1, int lo2, unsigned& dx,
+                                        unsigned& dy, unsigned& dz) {
+  const int m21 = (1 << 21) - 1;
+  dx = (unsigned)((int)((k >> 42) & m21) - (int)kKeyLimit - lo0);
+  dy = (unsigned)((int)((k >> 21) & m21) - (int)kKeyLimit - lo1);
+  dz = (unsigned)((int)(k & m21) - (int)kKeyLimit - lo2);
 }
 
-__global__ __launch_bounds__(kBlock) void seg_start_kernel(const int* __restrict__ head,
-                                                           const int* __restrict__ vid,
-                                                           long long n, int* __restrict__ start,
-                                                           int V, unsigned* __restrict__ flags) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    if (head[i]) {
-      const int v = vid[i];
-      if (v >= 0 && v < V)
-        start[v] = (int)i;
-      else
-        atomicOr(flags, kFlagInternal);
-    }
-  if (blockIdx.x == 0 && threadIdx.x == 0) start[V] = (int)n;
-}
-
-// One thread per voxel: FP64 sums over the members in increasing point index.
+// FP64 sums over a voxel's members in increasing point index: 16 lanes per voxel, one of the 9
+// components each (a thread per voxel held up its wave for the fullest of 64 voxels, 9 gathers a
+// member: 22 us for 24,000 voxels), four members' loads in flight. With bricks the voxel sets its bit
+// in its brick's occupancy mask (cleared before).
 __global__ __launch_bounds__(kBlock) void stats_kernel(
     const float* __restrict__ xyz, const float* __restrict__ cov, long long n,
     const int* __restrict__ kc, const int* __restrict__ order,
     const unsigned long long* __restrict__ skey, const int* __restrict__ start, int V,
     long long* __restrict__ keys, unsigned* __restrict__ rkey, double* __restrict__ mean,
     double* __restrict__ vcov, int* __restrict__ count, VoxelData* __restrict__ vox,
-    unsigned* __restrict__ flags) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    Brick* __restrict__ bricks, int lo0, int lo1, int lo2, int gby, int gbz,
+    int* __restrict__ internal) {
+  const int v = (int)(((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 4);
+  const int c = threadIdx.x & 15;
   if (v >= V) return;
   const int s = start[v], e = start[v + 1];
   if (!(s >= 0 && s < e && e <= n)) {
-    atomicOr(flags, kFlagInternal);
+    *internal = 1;
     return;
   }
-  double m0 = 0.0, m1 = 0.0, m2 = 0.0;
-  double c[6] = {0, 0, 0, 0, 0, 0};
-  for (int k = s; k < e; ++k) {
-    const long long j = order[k];
-    if (j < 0 || j >= n) {
-      atomicOr(flags, kFlagInternal);
-      return;
-    }
-    m0 += (double)xyz[j];
-    m1 += (double)xyz[n + j];
-    m2 += (double)xyz[2 * n + j];
-    for (int a = 0; a < 6; ++a) c[a] += (double)cov[a * n + j];
-  }
   const double cnt = (double)(e - s);
-  const long long j0 = order[s];
-  keys[v] = pack_key(kc[j0], kc[n + j0], kc[2 * n + j0]);
-  rkey[v] = (unsigned)skey[s];
-  VoxelData d;
-  d.mean[0] = m0 / cnt;
-  d.mean[1] = m1 / cnt;
-  d.mean[2] = m2 / cnt;
-  for (int a = 0; a < 6; ++a) d.cov[a] = c[a] / cnt;
-  d.count = e - s;
-  d.pad = 0;
-  vox[v] = d;
-  mean[v] = d.mean[0];
-  mean[(long long)V + v] = d.mean[1];
-  mean[2LL * V + v] = d.mean[2];
-  for (int a = 0; a < 6; ++a) vcov[(long long)a * V + v] = d.cov[a];
-  count[v] = e - s;
+  if (c < 9) {
+    const float* plane = c < 3 ? xyz + (size_t)c * n : cov + (size_t)(c - 3) * n;
+    double sum = 0.0;
+    int k = s;
+    bool bad = false;
+    for (; k + 4 <= e; k += 4) {
+      float x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = order[k + q];
+        bad |= j < 0 || j >= n;
+        x[q] = plane[bad ? 0 : j];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum += (double)x[q];
+    }
+    for (; k < e; ++k) {
+      const int j = order[k];
+      bad |= j < 0 || j >= n;
+      sum += (double)plane[bad ? 0 : j];
+    }
+    if (bad) *internal = 1;
+    const double r = sum / cnt;
+    if (c < 3) {
+      vox[v].mean[c] = r;
+      mean[(long long)c * V + v] = r;
+    } else {
+      vox[v].cov[c - 3] = r;
+      vcov[(long long)(c - 3) * V + v] = r;
+    }
+  } else if (c == 9) {
+    const long long j0 = order[s];
+    const int k0 = kc[j0], k1 = kc[n + j0], k2 = kc[2 * n + j0];
+    const long long key = pack_key(k0, k1, k2);
+    keys[v] = key;
+    rkey[v] = (unsigned)skey[s];
+    vox[v].count = e - s;
+    vox[v].pad = 0;
+    count[v] = e - s;
+    if (bricks) {
+      unsigned dx, dy, dz;
+      voxel_box_coords(key, lo0, lo1, lo2, dx, dy, dz);
+      atomicOr(&bricks[brick_of(dx, dy, dz, (unsigned)gby, (unsigned)gbz)].mask,
+               1u << bit_in_brick(dx, dy, dz));
+    }
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void slots32_init_kernel(uint2* __restrict__ t, long long cap) {
@@ -358,44 +555,7 @@ __global__ __launch_bounds__(kBlock) void insert64_kernel(const long long* __res
   }
 }
 
-// Grid layout, step 1: one thread per voxel sets its bit in its brick's occupancy mask.
-__device__ inline void voxel_box_coords(long long k, int lo0, int lo1, int lo2, unsigned& dx,
-                                        unsigned& dy, unsigned& dz) {
-  const int m21 = (1 << 21) - 1;
-  dx = (unsigned)((int)((k >> 42) & m21) - (int)kKeyLimit - lo0);
-  dy = (unsigned)((int)((k >> 21) & m21) - (int)kKeyLimit - lo1);
-  dz = (unsigned)((int)(k & m21) - (int)kKeyLimit - lo2);
-}
-
-__global__ __launch_bounds__(kBlock) void brick_mark_kernel(const long long* __restrict__ keys,
-                                                            int V, int lo0, int lo1, int lo2,
-                                                            int gby, int gbz,
-                                                            Brick* __restrict__ bricks) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= V) return;
-  unsigned dx, dy, dz;
-  voxel_box_coords(keys[v], lo0, lo1, lo2, dx, dy, dz);
-  atomicOr(&bricks[brick_of(dx, dy, dz, (unsigned)gby, (unsigned)gbz)].mask,
-           1u << bit_in_brick(dx, dy, dz));
-}
-
-// Step 2: occupied voxels per brick (then an exclusive scan gives each brick's base).
-__global__ __launch_bounds__(kBlock) void brick_count_kernel(const Brick* __restrict__ bricks,
-                                                             long long nb, int* __restrict__ cnt) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nb;
-       i += (long long)gridDim.x * blockDim.x)
-    cnt[i] = __popc(bricks[i].mask);
-}
-
-__global__ __launch_bounds__(kBlock) void brick_base_kernel(Brick* __restrict__ bricks,
-                                                            long long nb,
-                                                            const int* __restrict__ base) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nb;
-       i += (long long)gridDim.x * blockDim.x)
-    bricks[i].base = base[i];
-}
-
-// Step 3: one thread per voxel copies its record to its brick-ordered position.
+// Grid layout: one thread per voxel copies its record to its brick-ordered position.
 __global__ __launch_bounds__(kBlock) void brick_place_kernel(
     const long long* __restrict__ keys, int V, int lo0, int lo1, int lo2, int gby, int gbz,
     const Brick* __restrict__ bricks, const VoxelData* __restrict__ vox,
@@ -413,80 +573,136 @@ __global__ __launch_bounds__(kBlock) void brick_place_kernel(
 
 // ------------------------------------------------------------------ spatial order of a cloud
 
-// Morton code of the point's cell (floor(v / cell) per axis, offset by 2^20 and clamped to 21
-// bits; bits interleaved x, y, z from the lowest) and the point index.
-__global__ __launch_bounds__(kBlock) void morton_kernel(const float* __restrict__ xyz, long long n,
-                                                       double inv_cell,
-                                                       unsigned long long* __restrict__ code,
-                                                       int* __restrict__ idx) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    unsigned long long c = 0;
-    for (int a = 0; a < 3; ++a) {
-      double f = floor((double)xyz[a * n + i] * inv_cell) + (double)kKeyLimit;
-      f = fmin(fmax(f, 0.0), (double)(2 * kKeyLimit - 1));  // NaN -> 0
-      const unsigned long long k = (unsigned long long)f;
-      for (int b = 0; b < 21; ++b) c |= ((k >> b) & 1ull) << (3 * b + a);
-    }
-    code[i] = c;
-    idx[i] = (int)i;
-  }
-}
+// What the kernels below read of a SpatialJob.
+struct SpatialSeg {
+  const float *xyz, *cov;
+  float *xyz_out, *cov6_out;
+  int* perm;
+  long long off;
+  double inv_cell;
+  int n, box;  // box: index of the cloud's bounding box
+};
 
-// Per block: min and max of every axis of a cloud, and whether a coordinate is not finite.
-__global__ __launch_bounds__(kBlock) void cloud_bounds_kernel(const float* __restrict__ xyz,
-                                                              long long n,
-                                                              float* __restrict__ part,
-                                                              unsigned* __restrict__ flags) {
-  __shared__ float red[6][kBlock / 64];
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  unsigned fl = 0;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
+// Bounding box of every cloud (grid: blocks x clouds): block minima and maxima, then the cloud's last
+// block to arrive adds them up. A cloud with a coordinate that is not finite gets an infinite box
+// (never skipped, so the kernels report it).
+constexpr int kBoxBlocks = 16;
+__global__ __launch_bounds__(kBlock) void cloud_boxes_kernel(const SpatialSeg* __restrict__ segs,
+                                                             float* __restrict__ part,
+                                                             int* __restrict__ tickets,
+                                                             float* __restrict__ boxes) {
+  __shared__ float red[7][kBlock / 64];
+  __shared__ int s_last;
+  const SpatialSeg g = segs[blockIdx.y];
+  float v[7] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0f};
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < g.n; i += gridDim.x * kBlock)
     for (int a = 0; a < 3; ++a) {
-      const float v = xyz[a * n + i];
-      if (!isfinite(v)) fl |= kFlagNonFinite;
-      lo[a] = fminf(lo[a], v);
-      hi[a] = fmaxf(hi[a], v);
-    }
-  for (int a = 0; a < 3; ++a)
-    for (int off = 32; off > 0; off >>= 1) {
-      lo[a] = fminf(lo[a], __shfl_xor(lo[a], off, 64));
-      hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], off, 64));
+      const float x = g.xyz[(size_t)a * g.n + i];
+      if (!isfinite(x)) v[6] = 1.0f;
+      v[a] = fminf(v[a], x);
+      v[3 + a] = fmaxf(v[3 + a], x);
     }
   const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int a = 0; a < 3; ++a) {
-      red[a][w] = lo[a];
-      red[3 + a][w] = hi[a];
+  for (int a = 0; a < 7; ++a) {
+    for (int off = 32; off > 0; off >>= 1) {
+      const float o = __shfl_xor(v[a], off, 64);
+      v[a] = a < 3 ? fminf(v[a], o) : fmaxf(v[a], o);
     }
-  if (fl) atomicOr(flags, fl);
+    if ((threadIdx.x & 63) == 0) red[a][w] = v[a];
+  }
   __syncthreads();
+  float* mine = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 8;
+  if (threadIdx.x < 7) {
+    float x = red[threadIdx.x][0];
+    for (int q = 1; q < kBlock / 64; ++q)
+      x = threadIdx.x < 3 ? fminf(x, red[threadIdx.x][q]) : fmaxf(x, red[threadIdx.x][q]);
+    __hip_atomic_store(&mine[threadIdx.x], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&tickets[blockIdx.y], 1) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
   if (threadIdx.x < 6) {
-    float v = red[threadIdx.x][0];
-    for (int ww = 1; ww < kBlock / 64; ++ww)
-      v = threadIdx.x < 3 ? fminf(v, red[threadIdx.x][ww]) : fmaxf(v, red[threadIdx.x][ww]);
-    part[blockIdx.x * 6 + threadIdx.x] = v;
+    const float* p = part + (size_t)blockIdx.y * gridDim.x * 8;
+    float x = threadIdx.x < 3 ? INFINITY : -INFINITY, bad = 0.0f;
+    for (unsigned q = 0; q < gridDim.x; ++q) {
+      const float o = __hip_atomic_load(&p[q * 8 + threadIdx.x], __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+      x = threadIdx.x < 3 ? fminf(x, o) : fmaxf(x, o);
+      bad = fmaxf(bad, __hip_atomic_load(&p[q * 8 + 6], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT));
+    }
+    if (bad > 0.0f) x = threadIdx.x < 3 ? -INFINITY : INFINITY;
+    boxes[6 * (size_t)g.box + threadIdx.x] = x;
   }
 }
 
-// Positions [3][n] and interleaved covariances [n][6] in the order perm.
-__global__ __launch_bounds__(kBlock) void gather_cloud_kernel(
-    const float* __restrict__ xyz, const float* __restrict__ cov, long long n,
-    const int* __restrict__ perm, float* __restrict__ xyz_out, float* __restrict__ cov6_out,
-    unsigned* __restrict__ flags) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const long long j = perm[i];
-    if (j < 0 || j >= n) {
-      atomicOr(flags, kFlagInternal);
+// Morton code of a point's cell: per axis u = floor(v / cell) + 2^20 clamped to 21 bits, bits
+// interleaved x, y, z from the lowest. When every cell coordinate of the clouds lies in
+// [-2^b, 2^b), bits 19 .. b of u repeat the complement of bit 20, so the code keeps bit 20 and
+// the low b bits only: the order is the same (two codes that differ above bit b differ first at
+// bit 20), in 3 (b + 1) bits instead of 63.
+__device__ inline unsigned long long spread3_21(unsigned long long x) {
+  x &= 0x1fffffull;
+  x = (x | x << 32) & 0x1f00000000ffffull;
+  x = (x | x << 16) & 0x1f0000ff0000ffull;
+  x = (x | x << 8) & 0x100f00f00f00f00full;
+  x = (x | x << 4) & 0x10c30c30c30c30c3ull;
+  x = (x | x << 2) & 0x1249249249249249ull;
+  return x;
+}
+
+__global__ __launch_bounds__(kBlock) void morton_kernel(const SpatialSeg* __restrict__ segs, int b,
+                                                        unsigned long long* __restrict__ code,
+                                                        int* __restrict__ idx, int max_tiles,
+                                                        int* __restrict__ hist) {
+  const SpatialSeg g = segs[blockIdx.y];
+  if ((long long)blockIdx.x * kSortTile >= g.n) return;
+  unsigned digit[kSortTile / kBlock];
+  bool valid[kSortTile / kBlock];
+#pragma unroll
+  for (int j = 0; j < kSortTile / kBlock; ++j) {
+    const long long i = (long long)blockIdx.x * kSortTile + j * kBlock + threadIdx.x;
+    valid[j] = i < g.n;
+    digit[j] = 0;
+    if (!valid[j]) continue;
+    unsigned long long c = 0;
+    for (int a = 0; a < 3; ++a) {
+      double f = floor((double)g.xyz[(size_t)a * g.n + i] * g.inv_cell) + (double)kKeyLimit;
+      f = fmin(fmax(f, 0.0), (double)(2 * kKeyLimit - 1));  // NaN -> 0
+      const unsigned long long u = (unsigned long long)f;
+      const unsigned long long low = b >= 20 ? u : ((u & ((1ull << b) - 1ull)) | ((u >> 20) << b));
+      c |= spread3_21(low) << a;
+    }
+    code[g.off + i] = c;
+    idx[g.off + i] = (int)i;
+    digit[j] = (unsigned)c;
+  }
+  if (hist)
+    sort_tile_hist(digit, valid, hist + ((size_t)blockIdx.y * max_tiles + blockIdx.x) * 256);
+}
+
+// Positions [3][n] and interleaved covariances [n][6] in the sorted order, and the order itself.
+__global__ __launch_bounds__(kBlock) void gather_clouds_kernel(const SpatialSeg* __restrict__ segs,
+                                                               const int* __restrict__ order,
+                                                               int* __restrict__ internal) {
+  const SpatialSeg g = segs[blockIdx.y];
+  const size_t n = (size_t)g.n;
+  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < g.n;
+       i += (long long)gridDim.x * kBlock) {
+    const int j = order[g.off + i];
+    if (j < 0 || j >= g.n) {
+      *internal = 1;
       continue;
     }
-    for (int a = 0; a < 3; ++a) xyz_out[a * n + i] = xyz[a * n + j];
-    float2* o = reinterpret_cast<float2*>(cov6_out) + 3 * i;
-    o[0] = make_float2(cov[j], cov[n + j]);
-    o[1] = make_float2(cov[2 * n + j], cov[3 * n + j]);
-    o[2] = make_float2(cov[4 * n + j], cov[5 * n + j]);
+    for (int a = 0; a < 3; ++a) g.xyz_out[a * n + i] = g.xyz[a * n + j];
+    float2* o = reinterpret_cast<float2*>(g.cov6_out) + 3 * i;
+    o[0] = make_float2(g.cov[j], g.cov[n + j]);
+    o[1] = make_float2(g.cov[2 * n + j], g.cov[3 * n + j]);
+    o[2] = make_float2(g.cov[4 * n + j], g.cov[5 * n + j]);
+    g.perm[i] = j;
   }
 }
 
@@ -502,12 +718,8 @@ int bits_for(long long span) {  // bits to hold values 0..span
 
 }  // namespace
 
-hipError_t scan_exclusive(const int* in, int* out, long long n, hipStream_t s, Scratch& sc) {
-  return exclusive_scan(in, out, n, s, sc);
-}
-
 hipError_t radix_sort_pairs(unsigned long long** k, int** v, unsigned long long** kt, int** vt,
-                            long long n, int bits, unsigned* flags, hipStream_t s, Scratch& sc) {
+                            long long n, int bits, int* internal, hipStream_t s, Scratch& sc) {
   if (n <= 0) return hipSuccess;
   const long long ntiles = (n + kTile - 1) / kTile;
   int* hist = nullptr;
@@ -517,7 +729,7 @@ hipError_t radix_sort_pairs(unsigned long long** k, int** v, unsigned long long*
     radix_hist_kernel<<<(unsigned)ntiles, kBlock, 0, s>>>(*k, n, shift, hist, (int)ntiles);
     if ((e = exclusive_scan(hist, hist, 256 * ntiles, s, sc)) != hipSuccess) return e;
     radix_scatter_kernel<<<(unsigned)ntiles, kBlock, 0, s>>>(*k, *v, *kt, *vt, n, shift, hist,
-                                                             (int)ntiles, flags);
+                                                             (int)ntiles, internal);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     std::swap(*k, *kt);
     std::swap(*v, *vt);
@@ -525,65 +737,147 @@ hipError_t radix_sort_pairs(unsigned long long** k, int** v, unsigned long long*
   return hipSuccess;
 }
 
-vgicp_status spatial_copy(const float* xyz, const float* cov, int64_t n, double cell,
-                          float* xyz_out, float* cov6_out, float* box, int* perm_out,
-                          hipStream_t s) {
-  for (int a = 0; a < 3; ++a) {
-    box[a] = INFINITY;
-    box[3 + a] = -INFINITY;
+hipError_t sort_passes(SortBuffers& b, const SortSeg* segs, int nseg, long long max_n, int bits,
+                       int* internal, hipStream_t s) {
+  const int tiles = (int)sort_tiles(max_n), passes = (bits + 7) / 8;
+  const dim3 grid((unsigned)tiles, (unsigned)nseg);
+  for (int p = 0; p < passes; ++p) {
+    if (p > 0)
+      sort_hist_kernel<<<grid, kBlock, 0, s>>>(b.k, segs, (int)max_n, 8 * p, tiles, b.hist);
+    sort_pass_kernel<<<grid, kBlock, 0, s>>>(b.k, b.v, b.kt, b.vt, segs, (int)max_n, 8 * p, tiles,
+                                             b.hist, internal);
+    std::swap(b.k, b.kt);
+    std::swap(b.v, b.vt);
   }
-  if (n <= 0) return VGICP_OK;
-  Scratch sc;
-  unsigned long long *kA = nullptr, *kB = nullptr;
-  int *vA = nullptr, *vB = nullptr, *hist = nullptr;
-  unsigned* flags = nullptr;
-  const long long ntiles = (n + kTile - 1) / kTile;
+  return hipGetLastError();
+}
+
+hipError_t run_starts(const unsigned long long* key, long long n, int* start, int* tile_counts,
+                      int* count_out, hipStream_t s) {
+  return scan_with(RunHeads{key, start, n}, tile_counts, count_out, s);
+}
+
+hipError_t scan_values(const int* in, int* out, long long n, int* tile_counts, int* total,
+                       hipStream_t s) {
+  return scan_with(Ints{in, out, n}, tile_counts, total, s);
+}
+
+void launch_call_init(int* zero, long long words, int* bounds, BuildReport* report,
+                      hipStream_t s) {
+  const unsigned blocks = (unsigned)std::max<long long>(1, std::min<long long>((words + 1023) / 1024, 1024));
+  call_init_kernel<<<blocks, kBlock, 0, s>>>(zero, words, bounds, report);
+}
+
+vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipStream_t s) {
   hipError_t e;
-  if ((e = sc.alloc(&kA, (size_t)n)) || (e = sc.alloc(&kB, (size_t)n)) ||
-      (e = sc.alloc(&vA, (size_t)n)) || (e = sc.alloc(&vB, (size_t)n)) ||
-      (e = sc.alloc(&hist, (size_t)(256 * ntiles))) || (e = sc.alloc(&flags, 1)))
-    return hip_fail(e, "hipMalloc (cloud order)");
-  if ((e = hipMemsetAsync(flags, 0, sizeof(unsigned), s))) return hip_fail(e, "hipMemsetAsync");
-  morton_kernel<<<grid_for(n), kBlock, 0, s>>>(xyz, n, 1.0 / cell, kA, vA);
-  for (int shift = 0; shift < 63; shift += 8) {
-    radix_hist_kernel<<<(unsigned)ntiles, kBlock, 0, s>>>(kA, n, shift, hist, (int)ntiles);
-    if ((e = exclusive_scan(hist, hist, 256 * ntiles, s, sc)) != hipSuccess)
-      return hip_fail(e, "radix scan (cloud order)");
-    radix_scatter_kernel<<<(unsigned)ntiles, kBlock, 0, s>>>(kA, vA, kB, vB, n, shift, hist,
-                                                             (int)ntiles, flags);
-    std::swap(kA, kB);
-    std::swap(vA, vB);
+  const size_t C = jobs.size();
+  if (C == 0) return VGICP_OK;
+  // the clouds that factors read, those a pass can sort in one launch first
+  std::vector<SpatialSeg> segs;
+  for (size_t c = 0; c < C; ++c) {
+    const SpatialJob& j = jobs[c];
+    if (j.cell > 0.0)
+      segs.push_back({j.xyz, j.cov, j.xyz_out, j.cov6_out, j.perm, 0, 1.0 / j.cell, (int)j.n,
+                      (int)c});
   }
-  gather_cloud_kernel<<<grid_for(n), kBlock, 0, s>>>(xyz, cov, n, vA, xyz_out, cov6_out, flags);
-  if (perm_out &&
-      (e = hipMemcpyAsync(perm_out, vA, (size_t)n * sizeof(int), hipMemcpyDeviceToDevice, s)))
-    return hip_fail(e, "copy of the cloud order");
-  const int nb = std::min(grid_for(n), 64);
-  float* part = nullptr;
-  unsigned* bflags = nullptr;
-  if ((e = sc.alloc(&part, (size_t)nb * 6)) || (e = sc.alloc(&bflags, 1)) ||
-      (e = hipMemsetAsync(bflags, 0, sizeof(unsigned), s)))
-    return hip_fail(e, "cloud bounds scratch");
-  cloud_bounds_kernel<<<nb, kBlock, 0, s>>>(xyz, n, part, bflags);
-  std::vector<float> hp((size_t)nb * 6);
-  unsigned hf = 0, hb = 0;
-  if ((e = hipGetLastError()) ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(&hb, bflags, sizeof(hb), hipMemcpyDeviceToHost, s)) ||
-      (e = hipMemcpyAsync(hp.data(), part, hp.size() * sizeof(float), hipMemcpyDeviceToHost, s)) ||
-      (e = hipStreamSynchronize(s)))
-    return hip_fail(e, "cloud order");
-  if (hf) return fail(VGICP_E_HIP, "internal error in the cloud order");
-  for (int b = 0; b < nb; ++b)
-    for (int a = 0; a < 3; ++a) {
-      box[a] = std::min(box[a], hp[6 * b + a]);
-      box[3 + a] = std::max(box[3 + a], hp[6 * b + 3 + a]);
+  HostBlock hb;
+  if (!hb.p) return fail(VGICP_E_OOM, "pinned host block");
+  BuildReport* rep = static_cast<BuildReport*>(hb.p);
+  const int S = (int)segs.size();
+  std::vector<float> boxes(6 * C, 0.0f);
+  Arena a0;
+  a0.need<SpatialSeg>((size_t)S);
+  a0.need<float>((size_t)S * kBoxBlocks * 8);
+  a0.need<int>((size_t)S);
+  if ((e = a0.get(s))) return hip_fail(e, "pool allocation (cloud order)");
+  SpatialSeg* d_segs = a0.take<SpatialSeg>((size_t)S);
+  float* part = a0.take<float>((size_t)S * kBoxBlocks * 8);
+  int* tickets = a0.take<int>((size_t)S);
+  launch_call_init(reinterpret_cast<int*>(d_boxes), 6 * (long long)C, nullptr, rep, s);
+  if (S > 0) {
+    if ((e = hipMemcpyAsync(d_segs, segs.data(), (size_t)S * sizeof(SpatialSeg),
+                            hipMemcpyHostToDevice, s)))
+      return hip_fail(e, "cloud order");
+    launch_call_init(tickets, S, nullptr, nullptr, s);
+    for (int first = 0; first < S; first += 32768) {
+      const int m = std::min(S - first, 32768);
+      cloud_boxes_kernel<<<dim3(kBoxBlocks, (unsigned)m), kBlock, 0, s>>>(
+          d_segs + first, part + (size_t)first * kBoxBlocks * 8, tickets + first, d_boxes);
     }
-  if (hb)  // a non-finite coordinate: never skipped, so the kernels report it
+    if ((e = hipGetLastError()) ||
+        (e = hipMemcpyAsync(boxes.data(), d_boxes, boxes.size() * sizeof(float),
+                            hipMemcpyDeviceToHost, s)) ||
+        (e = hipStreamSynchronize(s)))
+      return hip_fail(e, "cloud boxes");
+  }
+  // bits of a cloud's cell coordinates: all in [-2^b, 2^b)
+  auto bits_of = [&](const SpatialSeg& g) {
+    int b = 0;
     for (int a = 0; a < 3; ++a) {
-      box[a] = -INFINITY;
-      box[3 + a] = INFINITY;
+      const double lo = std::floor((double)boxes[6 * (size_t)g.box + a] * g.inv_cell);
+      const double hi = std::floor((double)boxes[6 * (size_t)g.box + 3 + a] * g.inv_cell);
+      while (b < 20 && !(lo >= -std::ldexp(1.0, b) && hi < std::ldexp(1.0, b))) ++b;
     }
+    return b;
+  };
+  for (int first = 0; first < S;) {
+    // as many clouds together as fit 4 M points (their pairs and digit counts: about 150 MB)
+    long long pts = 0, max_n = 1;
+    int m = 0, b = 0;
+    bool big = false;
+    while (first + m < S && m < 32768) {
+      SpatialSeg& g = segs[first + m];
+      if (m > 0 && (big || g.n > kSortMax || pts + g.n > (4LL << 20))) break;
+      big = g.n > kSortMax;
+      g.off = pts;
+      pts += g.n;
+      if (g.n > 0) b = std::max(b, bits_of(g));
+      max_n = std::max<long long>(max_n, g.n);
+      ++m;
+    }
+    const int bits = b >= 20 ? 63 : 3 * (b + 1);
+    const long long tiles = sort_tiles(max_n);
+    const size_t words = big ? 0 : sort_hist_ints(m, max_n);
+    Arena ar;
+    Scratch sc;
+    ar.need<unsigned long long>((size_t)pts);
+    ar.need<unsigned long long>((size_t)pts);
+    ar.need<int>((size_t)pts);
+    ar.need<int>((size_t)pts);
+    ar.need<int>(words);
+    ar.need<SortSeg>((size_t)m);
+    if ((e = ar.get(s))) return hip_fail(e, "pool allocation (cloud order)");
+    SortBuffers sb;
+    sb.k = ar.take<unsigned long long>((size_t)pts);
+    sb.kt = ar.take<unsigned long long>((size_t)pts);
+    sb.v = ar.take<int>((size_t)pts);
+    sb.vt = ar.take<int>((size_t)pts);
+    sb.hist = ar.take<int>(words);
+    SortSeg* d_ss = ar.take<SortSeg>((size_t)m);
+    std::vector<SortSeg> ss;
+    for (int i = 0; i < m; ++i) ss.push_back({segs[first + i].off, segs[first + i].n, 0});
+    if ((e = hipMemcpyAsync(d_segs + first, segs.data() + first, (size_t)m * sizeof(SpatialSeg),
+                            hipMemcpyHostToDevice, s)) ||
+        (e = hipMemcpyAsync(d_ss, ss.data(), ss.size() * sizeof(SortSeg), hipMemcpyHostToDevice,
+                            s)))
+      return hip_fail(e, "cloud order");
+    morton_kernel<<<dim3((unsigned)tiles, (unsigned)m), kBlock, 0, s>>>(
+        d_segs + first, b, sb.k, sb.v, (int)tiles, big ? nullptr : sb.hist);
+    if (big)
+      e = radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, pts, bits, &rep->internal, s, sc);
+    else
+      e = sort_passes(sb, d_ss, m, max_n, bits, &rep->internal, s);
+    if (e) return hip_fail(e, "radix sort (cloud order)");
+    gather_clouds_kernel<<<dim3((unsigned)std::min<long long>((max_n + 255) / 256, 4096),
+                                (unsigned)m),
+                           kBlock, 0, s>>>(d_segs + first, sb.v, &rep->internal);
+    // the host vectors above are read by the copies until here
+    if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
+      return hip_fail(e, "cloud order");
+    first += m;
+  }
+  if ((e = hipStreamSynchronize(s))) return hip_fail(e, "cloud order");
+  if (rep->internal) return fail(VGICP_E_HIP, "internal error in the cloud order");
   return VGICP_OK;
 }
 
@@ -598,114 +892,80 @@ vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, doubl
   m->inv_res = 1.0 / res;
   int ex = 0;
   m->pow2 = (std::frexp(res, &ex) == 0.5) ? 1 : 0;
-  Scratch sc;
   auto cleanup = [&](vgicp_status st) {
     destroy_voxelmap(m);
     return st;
   };
-  int* kc = nullptr;
-  int* bounds = nullptr;
-  unsigned* flags = nullptr;  // the map build's own error word (the sticky one is not touched)
-  if ((e = sc.alloc(&kc, 3 * (size_t)n)) != hipSuccess ||
-      (e = sc.alloc(&bounds, 6)) != hipSuccess || (e = sc.alloc(&flags, 1)) != hipSuccess)
-    return cleanup(hip_fail(e, "hipMalloc (voxel map scratch)"));
-  bounds_init_kernel<<<1, 64, 0, s>>>(bounds, flags);
+  HostBlock hb;
+  if (!hb.p) return cleanup(fail(VGICP_E_OOM, "pinned host block"));
+  volatile BuildReport* rep = static_cast<BuildReport*>(hb.p);
+  BuildReport* report = static_cast<BuildReport*>(hb.p);
+  // the sort takes one launch per pass up to kSortMax points (63 key bits: 8 passes)
+  const bool small = n <= kSortMax;
+  const size_t n1 = (size_t)std::max<int64_t>(n, 1);
+  const size_t words = small && n > 0 ? sort_hist_ints(1, n) : 0;
+  Arena ar;
+  Scratch sc;
+  ar.need<int>(3 * n1);
+  ar.need<int>(8);
+  ar.need<int>(words);
+  ar.need<unsigned long long>(n1);
+  ar.need<unsigned long long>(n1);
+  ar.need<int>(n1);
+  ar.need<int>(n1);
+  ar.need<int>(n1 + 1);
+  ar.need<unsigned>(n1);
+  ar.need<int>(kRunTiles);
+  if ((e = ar.get(s)) != hipSuccess) return cleanup(hip_fail(e, "voxel map scratch"));
+  int* kc = ar.take<int>(3 * n1);
+  int* bounds = ar.take<int>(8);
+  SortBuffers sb;
+  sb.hist = ar.take<int>(words);
+  sb.k = ar.take<unsigned long long>(n1);
+  sb.kt = ar.take<unsigned long long>(n1);
+  sb.v = ar.take<int>(n1);
+  sb.vt = ar.take<int>(n1);
+  int* start = ar.take<int>(n1 + 1);
+  unsigned* rkey = ar.take<unsigned>(n1);
+  int* tile_counts = ar.take<int>(kRunTiles);
+  launch_call_init(nullptr, 0, bounds, report, s);
   if (n > 0)
-    coords_kernel<<<std::min(grid_for(n), 128), kBlock, 0, s>>>(xyz, cov, n, m->pow2, res, m->inv_res, kc,
-                                                 bounds, flags);
-  int hb[6];
-  unsigned hf = 0;
-  if ((e = hipGetLastError()) != hipSuccess ||
-      (e = hipMemcpyAsync(hb, bounds, sizeof(hb), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipStreamSynchronize(s)) != hipSuccess)
+    coords_kernel<<<std::min(grid_for(n), 128), kBlock, 0, s>>>(xyz, cov, n, m->pow2, res,
+                                                                m->inv_res, kc, bounds, report);
+  if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess)
     return cleanup(hip_fail(e, "voxel coordinates"));
-  if (hf) {
-    if (hf & kFlagNonFinite) return cleanup(fail(VGICP_E_NONFINITE, "non-finite map point"));
+  if (rep->nonfinite) return cleanup(fail(VGICP_E_NONFINITE, "non-finite map point"));
+  if (rep->keyrange)
     return cleanup(fail(VGICP_E_KEY_RANGE, "map point outside the voxel key range |k| < 2^20"));
-  }
 
   long long V = 0;
-  int* order = nullptr;  // point index in key order
-  unsigned long long* keyA = nullptr;
-  unsigned* rkey = nullptr;
   int bits = 0;
   if (n > 0) {
-    const int bx = bits_for((long long)hb[3] - hb[0]);
-    const int by = bits_for((long long)hb[4] - hb[1]);
-    const int bz = bits_for((long long)hb[5] - hb[2]);
-    bits = bx + by + bz;  // <= 63
+    const int b[3] = {bits_for((long long)rep->hi[0] - rep->lo[0]),
+                      bits_for((long long)rep->hi[1] - rep->lo[1]),
+                      bits_for((long long)rep->hi[2] - rep->lo[2])};
+    bits = b[0] + b[1] + b[2];  // <= 63
     for (int a = 0; a < 3; ++a) {
-      m->lo[a] = hb[a];
-      m->ext[a] = hb[3 + a] - hb[a] + 1;
+      m->lo[a] = rep->lo[a];
+      m->ext[a] = rep->hi[a] - rep->lo[a] + 1;
     }
-    m->by = by;
-    m->bz = bz;
+    m->by = b[1];
+    m->bz = b[2];
     m->key32 = bits <= 31;
-    unsigned long long* keyB = nullptr;
-    int *valA = nullptr, *valB = nullptr;
-    if ((e = sc.alloc(&keyA, (size_t)n)) != hipSuccess ||
-        (e = sc.alloc(&keyB, (size_t)n)) != hipSuccess ||
-        (e = sc.alloc(&valA, (size_t)n)) != hipSuccess ||
-        (e = sc.alloc(&valB, (size_t)n)) != hipSuccess)
-      return cleanup(hip_fail(e, "hipMalloc (sort buffers)"));
-    sortkey_kernel<<<grid_for(n), kBlock, 0, s>>>(kc, n, hb[0], hb[1], hb[2], by, bz, keyA,
-                                                  valA);
-    const long long ntiles = (n + kTile - 1) / kTile;
-    if (ntiles * 256 >= (1LL << 31))
+    if ((n + kTile - 1) / kTile * 256 >= (1LL << 31))
       return cleanup(fail(VGICP_E_CAPACITY, "map too large for the 32-bit sort offsets"));
-    int* hist = nullptr;
-    if ((e = sc.alloc(&hist, (size_t)(256 * ntiles))) != hipSuccess)
-      return cleanup(hip_fail(e, "hipMalloc (histograms)"));
-    for (int shift = 0; shift < bits; shift += 8) {
-      radix_hist_kernel<<<(unsigned)ntiles, kBlock, 0, s>>>(keyA, n, shift, hist, (int)ntiles);
-      if ((e = exclusive_scan(hist, hist, 256 * ntiles, s, sc)) != hipSuccess)
-        return cleanup(hip_fail(e, "radix scan"));
-      radix_scatter_kernel<<<(unsigned)ntiles, kBlock, 0, s>>>(keyA, valA, keyB, valB, n,
-                                                               shift, hist, (int)ntiles, flags);
-      std::swap(keyA, keyB);
-      std::swap(valA, valB);
-    }
-    order = valA;
-    int *head = nullptr, *vid = nullptr;
-    if ((e = sc.alloc(&head, (size_t)n)) != hipSuccess ||
-        (e = sc.alloc(&vid, (size_t)n)) != hipSuccess)
-      return cleanup(hip_fail(e, "hipMalloc (segments)"));
-    heads_kernel<<<grid_for(n), kBlock, 0, s>>>(keyA, n, head);
-    if ((e = exclusive_scan(head, vid, n, s, sc)) != hipSuccess)
-      return cleanup(hip_fail(e, "segment scan"));
-    int last[2] = {0, 0};
-    if ((e = hipGetLastError()) != hipSuccess ||
-        (e = hipMemcpyAsync(&last[0], vid + (n - 1), sizeof(int), hipMemcpyDeviceToHost, s)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(&last[1], head + (n - 1), sizeof(int), hipMemcpyDeviceToHost, s)) !=
-            hipSuccess ||
+    sortkey_kernel<<<(unsigned)sort_tiles(n), kBlock, 0, s>>>(
+        kc, n, m->lo[0], m->lo[1], m->lo[2], b[1], b[2], sb.k, sb.v, small ? sb.hist : nullptr);
+    e = small ? sort_passes(sb, nullptr, 1, n, bits, &report->internal, s)
+              : radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, bits, &report->internal, s, sc);
+    if (e != hipSuccess) return cleanup(hip_fail(e, "radix sort"));
+    if ((e = run_starts(sb.k, n, start, tile_counts, &report->count, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
       return cleanup(hip_fail(e, "voxel count"));
-    V = (long long)last[0] + last[1];
-    if (V <= 0 || V > n) return cleanup(fail(VGICP_E_HIP, "internal error: voxel count"));
-    int* start = nullptr;
-    if ((e = sc.alloc(&start, (size_t)V + 1)) != hipSuccess ||
-        (e = sc.alloc(&rkey, (size_t)V)) != hipSuccess)
-      return cleanup(hip_fail(e, "hipMalloc (segment starts)"));
-    seg_start_kernel<<<grid_for(n), kBlock, 0, s>>>(head, vid, n, start, (int)V, flags);
+    V = rep->count;
+    if (V <= 0 || V > n || rep->internal)
+      return cleanup(fail(VGICP_E_HIP, "internal error: voxel count"));
     m->V = V;
-    if ((e = hipMalloc(&m->keys, std::max<size_t>(V, 1) * sizeof(int64_t))) != hipSuccess ||
-        (e = hipMalloc(&m->mean, std::max<size_t>(3 * V, 1) * sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&m->cov, std::max<size_t>(6 * V, 1) * sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&m->count, std::max<size_t>(V, 1) * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc(&m->vox, std::max<size_t>(V, 1) * sizeof(VoxelData))) != hipSuccess)
-      return cleanup(fail(VGICP_E_OOM, "hipMalloc (voxel arrays)"));
-    stats_kernel<<<(unsigned)((V + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-        xyz, cov, n, kc, order, keyA, start, (int)V, reinterpret_cast<long long*>(m->keys), rkey,
-        m->mean, m->cov, m->count, m->vox, flags);
-  } else {
-    if ((e = hipMalloc(&m->keys, sizeof(int64_t))) != hipSuccess ||
-        (e = hipMalloc(&m->mean, sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&m->cov, sizeof(double))) != hipSuccess ||
-        (e = hipMalloc(&m->count, sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc(&m->vox, sizeof(VoxelData))) != hipSuccess)
-      return cleanup(fail(VGICP_E_OOM, "hipMalloc (voxel arrays)"));
   }
   // Grid layout: occupancy bricks of 4 x 4 x 2 voxels over the bounding box. The automatic
   // choice takes it while it needs at most kGridAutoBricks bricks or 32 per voxel; else the
@@ -721,61 +981,75 @@ vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, doubl
   } else if (layout == VGICP_LAYOUT_AUTO) {
     use_grid = nb <= kGridMaxBricks && (nb <= kGridAutoBricks || nb <= 32 * V);
   }
-  if (use_grid) {
-    m->layout = kLayoutGrid;
-    m->gby = (int)gby;
-    m->gbz = (int)gbz;
-    m->nbricks = std::max<long long>(nb, 1);
-    int* cnt = nullptr;
-    if ((e = hipMalloc(&m->bricks, (size_t)m->nbricks * sizeof(Brick))) != hipSuccess ||
-        (e = hipMalloc(&m->voxb, std::max<size_t>(V, 1) * sizeof(VoxelData))) != hipSuccess ||
-        (e = hipMalloc(&m->rec_id, std::max<size_t>(V, 1) * sizeof(int))) != hipSuccess)
-      return cleanup(fail(VGICP_E_OOM, "hipMalloc (voxel grid)"));
-    if ((e = sc.alloc(&cnt, (size_t)m->nbricks)) != hipSuccess ||
-        (e = hipMemsetAsync(m->bricks, 0, (size_t)m->nbricks * sizeof(Brick), s)) != hipSuccess)
-      return cleanup(hip_fail(e, "voxel grid scratch"));
-    if (V > 0) {
-      const unsigned vb = (unsigned)((V + kBlock - 1) / kBlock);
-      const long long* keys = reinterpret_cast<const long long*>(m->keys);
-      brick_mark_kernel<<<vb, kBlock, 0, s>>>(keys, (int)V, m->lo[0], m->lo[1], m->lo[2],
-                                               (int)gby, (int)gbz, m->bricks);
-      brick_count_kernel<<<grid_for(nb), kBlock, 0, s>>>(m->bricks, nb, cnt);
-      if ((e = exclusive_scan(cnt, cnt, nb, s, sc)) != hipSuccess)
-        return cleanup(hip_fail(e, "brick scan"));
-      brick_base_kernel<<<grid_for(nb), kBlock, 0, s>>>(m->bricks, nb, cnt);
-      brick_place_kernel<<<vb, kBlock, 0, s>>>(keys, (int)V, m->lo[0], m->lo[1], m->lo[2],
-                                                (int)gby, (int)gbz, m->bricks, m->vox, m->voxb,
-                                                m->rec_id);
-    }
-  } else {
-    m->layout = m->key32 ? kLayoutHash32 : kLayoutHash64;
-  }
   long long cap = 16;
   while (cap < 4 * V) cap <<= 1;
   if (cap > (1LL << 31)) return cleanup(fail(VGICP_E_CAPACITY, "voxel table above 2^31 slots"));
+  m->layout = use_grid ? kLayoutGrid : (m->key32 ? kLayoutHash32 : kLayoutHash64);
   m->cap = use_grid ? 0 : cap;
   if (use_grid) {
-    // no table: the grid resolves every key
-  } else if (m->key32) {
-    if ((e = hipMalloc(&m->slots32, (size_t)cap * sizeof(uint2))) != hipSuccess)
-      return cleanup(fail(VGICP_E_OOM, "hipMalloc (voxel table)"));
-    slots32_init_kernel<<<grid_for(cap), kBlock, 0, s>>>(m->slots32, cap);
-    if (V > 0)
-      insert32_kernel<<<(unsigned)((V + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-          rkey, (int)V, m->slots32, (unsigned)(cap - 1));
-  } else {
-    if ((e = hipMalloc(&m->slots64, (size_t)cap * sizeof(longlong2))) != hipSuccess)
-      return cleanup(fail(VGICP_E_OOM, "hipMalloc (voxel table)"));
-    slots64_init_kernel<<<grid_for(cap), kBlock, 0, s>>>(m->slots64, cap);
-    if (V > 0)
-      insert64_kernel<<<(unsigned)((V + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-          reinterpret_cast<const long long*>(m->keys), (int)V, m->slots64, (unsigned)(cap - 1));
+    m->gby = (int)gby;
+    m->gbz = (int)gbz;
+    m->nbricks = std::max<long long>(nb, 1);
   }
-  if ((e = hipGetLastError()) != hipSuccess ||
-      (e = hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipStreamSynchronize(s)) != hipSuccess)
+  // the map's arrays, one block
+  const size_t V1 = (size_t)std::max<long long>(V, 1);
+  const size_t slot_bytes = use_grid ? 0 : (size_t)cap * (m->key32 ? sizeof(uint2) : sizeof(longlong2));
+  Arena own;
+  own.need<int64_t>(V1);
+  own.need<double>(3 * V1);
+  own.need<double>(6 * V1);
+  own.need<int32_t>(V1);
+  own.need<VoxelData>(V1);
+  own.need<Brick>(use_grid ? (size_t)m->nbricks : 0);
+  own.need<VoxelData>(use_grid ? V1 : 0);
+  own.need<int>(use_grid ? V1 : 0);
+  own.need<char>(slot_bytes);
+  if ((e = own.get(s, true)) != hipSuccess) return cleanup(fail(VGICP_E_OOM, "voxel map arrays"));
+  m->keys = own.take<int64_t>(V1);
+  m->mean = own.take<double>(3 * V1);
+  m->cov = own.take<double>(6 * V1);
+  m->count = own.take<int32_t>(V1);
+  m->vox = own.take<VoxelData>(V1);
+  Brick* bricks = own.take<Brick>(use_grid ? (size_t)m->nbricks : 0);
+  VoxelData* voxb = own.take<VoxelData>(use_grid ? V1 : 0);
+  int* rec_id = own.take<int>(use_grid ? V1 : 0);
+  char* slots = own.take<char>(slot_bytes);
+  m->arena = own.base;
+  own.base = nullptr;  // the map's now
+  const long long* keys = reinterpret_cast<const long long*>(m->keys);
+  const unsigned vb = (unsigned)((V1 + kBlock - 1) / kBlock);
+  if (use_grid) {
+    m->bricks = bricks;
+    m->voxb = voxb;
+    m->rec_id = rec_id;
+    launch_call_init(reinterpret_cast<int*>(bricks), 2 * m->nbricks, nullptr, nullptr, s);
+  } else if (m->key32) {
+    m->slots32 = reinterpret_cast<uint2*>(slots);
+    slots32_init_kernel<<<grid_for(cap), kBlock, 0, s>>>(m->slots32, cap);
+  } else {
+    m->slots64 = reinterpret_cast<longlong2*>(slots);
+    slots64_init_kernel<<<grid_for(cap), kBlock, 0, s>>>(m->slots64, cap);
+  }
+  if (V > 0) {
+    stats_kernel<<<(unsigned)((V + 15) / 16), kBlock, 0, s>>>(
+        xyz, cov, n, kc, sb.v, sb.k, start, (int)V, reinterpret_cast<long long*>(m->keys), rkey,
+        m->mean, m->cov, m->count, m->vox, m->bricks, m->lo[0], m->lo[1], m->lo[2], (int)gby,
+        (int)gbz, &report->internal);
+    if (use_grid) {
+      if ((e = scan_with(BrickVoxels{m->bricks, nb}, tile_counts, nullptr, s)) != hipSuccess)
+        return cleanup(hip_fail(e, "brick scan"));
+      brick_place_kernel<<<vb, kBlock, 0, s>>>(keys, (int)V, m->lo[0], m->lo[1], m->lo[2],
+                                               (int)gby, (int)gbz, m->bricks, m->vox, m->voxb,
+                                               m->rec_id);
+    } else if (m->key32) {
+      insert32_kernel<<<vb, kBlock, 0, s>>>(rkey, (int)V, m->slots32, (unsigned)(cap - 1));
+    } else {
+      insert64_kernel<<<vb, kBlock, 0, s>>>(keys, (int)V, m->slots64, (unsigned)(cap - 1));
+    }
+  }
+  if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess)
     return cleanup(hip_fail(e, "voxel table"));
-  if (hf & kFlagInternal) return cleanup(fail(VGICP_E_HIP, "internal error in the voxel map build"));
+  if (rep->internal) return cleanup(fail(VGICP_E_HIP, "internal error in the voxel map build"));
   *out = m;
   return VGICP_OK;
 }
@@ -786,16 +1060,7 @@ void destroy_voxelmap(vgicp_voxelmap m) {
   (void)hipGetDevice(&cur);
   if (cur != m->device) (void)hipSetDevice(m->device);
   (void)hipDeviceSynchronize();
-  (void)hipFree(m->bricks);
-  (void)hipFree(m->voxb);
-  (void)hipFree(m->rec_id);
-  (void)hipFree(m->slots32);
-  (void)hipFree(m->slots64);
-  (void)hipFree(m->vox);
-  (void)hipFree(m->keys);
-  (void)hipFree(m->mean);
-  (void)hipFree(m->cov);
-  (void)hipFree(m->count);
+  if (m->arena) (void)hipFreeAsync(m->arena, nullptr);
   if (cur != m->device) (void)hipSetDevice(cur);
   delete m;
 }
