@@ -325,15 +325,19 @@ __global__ __launch_bounds__(kBlock) void knn_code_kernel(const float* __restric
   if (hist) sort_tile_hist(digit, valid, hist + (size_t)blockIdx.x * 256);
 }
 
-// Sorted copy of the positions.
+// Sorted copy of the positions, each with its point's index (one 16-byte load per candidate).
+struct alignas(16) SortedPoint {
+  float x, y, z;
+  int id;
+};
 __global__ __launch_bounds__(kBlock) void knn_gather_kernel(const float* __restrict__ xyz,
                                                             long long n,
                                                             const int* __restrict__ perm,
-                                                            float* __restrict__ xs) {
+                                                            SortedPoint* __restrict__ xs) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
-    const long long p = perm[i];
-    for (int a = 0; a < 3; ++a) xs[a * n + i] = xyz[a * n + p];
+    const int p = perm[i];
+    xs[i] = SortedPoint{xyz[p], xyz[n + p], xyz[2 * n + p], p};
   }
 }
 
@@ -398,8 +402,7 @@ __global__ __launch_bounds__(kBlock) void knn_level_tail_kernel(
 }
 
 struct KnnGrid {
-  const float* xs;         // [3][n] sorted positions
-  const int* perm;         // [n] original index of each sorted position
+  const SortedPoint* xs;   // [n] sorted positions and original indices
   const CellSlot* slots[kMaxLevels];
   unsigned mask[kMaxLevels];
   int levels;
@@ -452,14 +455,27 @@ constexpr int kMaxShell = 3;
 // Lanes that share one query.
 constexpr int kGroup = 16;
 
-__device__ inline double shfl_xor_d(double v, int m) {
-  const int lo = __shfl_xor(__double2loint(v), m, kGroup);
-  const int hi = __shfl_xor(__double2hiint(v), m, kGroup);
-  return __hiloint2double(hi, lo);
+// Rotation and upward shift (zeros enter) within the 16 lanes of a row: register moves, where a
+// shuffle goes through LDS.
+template <int N>
+__device__ inline int row_ror(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false);
+}
+template <int N>
+__device__ inline int row_shr0(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x110 + N, 0xf, 0xf, true);
+}
+template <int N>
+__device__ inline void row_least(double& d, int& id) {
+  const double od = __hiloint2double(row_ror<N>(__double2hiint(d)), row_ror<N>(__double2loint(d)));
+  const int oi = row_ror<N>(id);
+  const bool lt = od < d || (od == d && oi < id);
+  d = lt ? od : d;
+  id = lt ? oi : id;
 }
 
 // The group's `rounds` best pairs in order: every lane offers the head of its own sorted list,
-// a butterfly over the group's lanes picks the least (distance, index), its owner advances.
+// rotations over the group's lanes find the least (distance, index), its owner advances.
 // Returns the pair of the last round (the group's k-th); `out`, if given, receives round s at
 // out[s * n] from lane s mod kGroup.
 template <int K>
@@ -477,15 +493,10 @@ __device__ inline void group_select(const double (&bd)[K], const int (&bi)[K], i
       }
     double md = hd;
     int mi = hi;
-#pragma unroll
-    for (int m = 1; m < kGroup; m <<= 1) {
-      const double od = shfl_xor_d(md, m);
-      const int oi = __shfl_xor(mi, m, kGroup);
-      if (od < md || (od == md && oi < mi)) {
-        md = od;
-        mi = oi;
-      }
-    }
+    row_least<8>(md, mi);
+    row_least<4>(md, mi);
+    row_least<2>(md, mi);
+    row_least<1>(md, mi);
     if (mi != INT_MAX && mi == hi) ++head;  // indices are unique: exactly one owner
     if (out && (s % kGroup) == lane) out[(long long)s * n] = mi == INT_MAX ? -1 : mi;
     kd = md;
@@ -515,7 +526,8 @@ __global__ __launch_bounds__(kBlock) void knn_query_kernel(KnnGrid g, int k,
   const long long stride = (long long)gridDim.x * blockDim.x / kGroup;
   for (long long i = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / kGroup; i < n;
        i += stride) {
-    const double q0 = g.xs[i], q1 = g.xs[n + i], q2 = g.xs[2 * n + i];
+    const SortedPoint me = g.xs[i];
+    const double q0 = me.x, q1 = me.y, q2 = me.z;
     const int f0 = (int)floor(q0 * g.inv_h) - g.lo[0];
     const int f1 = (int)floor(q1 * g.inv_h) - g.lo[1];
     const int f2 = (int)floor(q2 * g.inv_h) - g.lo[2];
@@ -574,11 +586,32 @@ __global__ __launch_bounds__(kBlock) void knn_query_kernel(KnnGrid g, int k,
               }
             }
           }
-#pragma unroll 1
-          for (int src = 0; src < kGroup; ++src) {
-            const int st = __shfl(start, src, kGroup), ct = __shfl(count, src, kGroup);
-            for (int j = st + lane; j < st + ct; j += kGroup) {
-              const double x0 = g.xs[j], x1_ = g.xs[n + j], x2 = g.xs[2 * n + j];
+          // the cells' points as one list: lane l takes its entries l, l + 16, ... (two in flight)
+          int inc = count;
+          inc += row_shr0<1>(inc);
+          inc += row_shr0<2>(inc);
+          inc += row_shr0<4>(inc);
+          inc += row_shr0<8>(inc);
+          const int total = __shfl(inc, kGroup - 1, kGroup), excl = inc - count;
+          const int shift0 = start - excl;  // position of the list's entry c in this lane's cell: c + shift0
+          for (int c0 = 0; c0 < total; c0 += 2 * kGroup) {
+            SortedPoint p[2];
+            bool have[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const int c = c0 + h * kGroup + lane;
+              int cell = 0;  // the last cell whose entries begin at or before c
+#pragma unroll
+              for (int step = kGroup / 2; step > 0; step >>= 1)
+                if (__shfl(excl, cell + step, kGroup) <= c) cell += step;
+              const int j = c + __shfl(shift0, cell, kGroup);
+              have[h] = c < total;
+              p[h] = g.xs[have[h] ? j : i];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              if (!have[h]) continue;
+              const double x0 = p[h].x, x1_ = p[h].y, x2 = p[h].z;
               if (skip_seen) {
                 const int d0 = (((int)floor(x0 * g.inv_h) - g.lo[0]) >> psh) - p0;
                 const int d1 = (((int)floor(x1_ * g.inv_h) - g.lo[1]) >> psh) - p1;
@@ -588,7 +621,7 @@ __global__ __launch_bounds__(kBlock) void knn_query_kernel(KnnGrid g, int k,
               }
               const double dx_ = x0 - q0, dy_ = x1_ - q1, dz_ = x2 - q2;
               const double d = (dx_ * dx_ + dy_ * dy_) + dz_ * dz_;
-              const int id = g.perm[j];
+              const int id = p[h].id;
               if (d > gk || (d == gk && id > gki)) continue;  // cannot reach the group's k
               offer<K>(d, id, bd, bi, kth, kthi, k);
             }
@@ -610,7 +643,7 @@ __global__ __launch_bounds__(kBlock) void knn_query_kernel(KnnGrid g, int k,
         }
       }
     }
-    group_select<K>(bd, bi, k, lane, gk, gki, nbr + g.perm[i], n);
+    group_select<K>(bd, bi, k, lane, gk, gki, nbr + me.id, n);
   }
 }
 
@@ -852,7 +885,7 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   ar.need<unsigned long long>(N);
   ar.need<int>(N);
   ar.need<int>(N);
-  ar.need<float>(3 * N);
+  ar.need<SortedPoint>(N);
   if ((e = ar.get(s))) return hip_fail(e, "pool allocation (knn)");
   int* bounds = ar.take<int>(8);
   SortBuffers sb;
@@ -861,7 +894,7 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   sb.kt = ar.take<unsigned long long>(N);
   sb.v = ar.take<int>(N);
   sb.vt = ar.take<int>(N);
-  float* xs = ar.take<float>(3 * N);
+  SortedPoint* xs = ar.take<SortedPoint>(N);
   launch_call_init(nullptr, 0, bounds, report, s);
   knn_bounds_kernel<<<std::min(grid_for(n), 128), kBlock, 0, s>>>(xyz, n, bounds, report);
   // the cell estimate runs beside the bounds (a non-finite cloud is rejected after it)
@@ -944,13 +977,14 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   knn_level_tail_kernel<<<lgrid, kBlock, 0, s>>>(n, sb.k, tab, &report->internal);
   g.levels = levels;
   g.xs = xs;
-  g.perm = sb.v;
   g.h = h;
   g.inv_h = inv_h;
   g.n = n;
   const int qgrid = grid_for(n * kGroup);
-  if (k <= 8)
-    knn_query_kernel<8><<<qgrid, kBlock, 0, s>>>(g, k, nbr);
+  if (k <= 6)
+    knn_query_kernel<6><<<qgrid, kBlock, 0, s>>>(g, k, nbr);
+  else if (k <= 10)
+    knn_query_kernel<10><<<qgrid, kBlock, 0, s>>>(g, k, nbr);
   else if (k <= 16)
     knn_query_kernel<16><<<qgrid, kBlock, 0, s>>>(g, k, nbr);
   else
