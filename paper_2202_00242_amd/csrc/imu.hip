@@ -10,9 +10,9 @@
 //     the Cholesky factor of S: H = J^T S^-1 J, b = J^T S^-1 r, e = r^T S^-1 r.
 //   * with bias states: the preintegration's derivatives with respect to the biases, the
 //     first-order bias correction and the bias random walk (15 residuals, 30 unknowns).
-// A factor holds tens to hundreds of samples and a graph a few thousand factors: one thread per
-// factor, everything in registers, for the preintegration and the 18-unknown factor; one block
-// of 64 threads per factor for the 30-unknown one (its 900-entry Hessian is formed in parallel).
+// A factor holds tens to hundreds of samples and a graph a few thousand factors: 16 lanes per factor
+// for the preintegration, one thread, everything in registers, for the 18-unknown factor, eight
+// factors per block for the 30-unknown one (their 900-entry Hessians are formed in parallel).
 #include <cmath>
 
 #include "internal.h"
@@ -90,134 +90,147 @@ __device__ inline void so3_log_jrinv(const double R[3][3], double w[3], double J
     for (int cc = 0; cc < 3; ++cc) Ji[r][cc] = (r == cc ? 1.0 : 0.0) + 0.5 * K[r][cc] + g * K2[r][cc];
 }
 
-// COV: the mean and the noise covariance (pre, cov). JAC: the mean's derivatives with respect to
-// the biases instead (jac [F][9][6], rows (dphi, dv, dp), columns (b_a, b_w)): perturbing b_w by
-// d moves dR_{k+1} = dR_k E_k by dR_{k+1} Exp((E_k^T J_R + ... ) d), see the recursions below;
-// they use the values before the sample, as the covariance does.
-template <bool COV, bool JAC>
+// Broadcast of lane N of every row of 16 lanes (a register move).
+template <int N>
+__device__ inline double row_lane(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + N, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + N, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Preintegration, 16 lanes per factor: the mean and the sample's matrices are the same in all of
+// them; lane c < 9 carries column c of the noise covariance S, lanes 9 .. 14 the columns of the
+// mean's derivatives J with respect to the biases (b_a, b_w). With A the error propagation of a
+// sample (rows (E^T, 0, 0), (M1, I, 0), (M1 dt / 2, I dt, I), M1 = -dR [a]x dt) both go through the
+// same product, A S and A J; then S <- (A S) A^T + B Q B^T (columns 0 .. 2 of A S broadcast along
+// the row) and J gains -J_r dt (rotation, b_w), -dR dt and -dR dt^2 / 2 (velocity and position, b_a).
+// What depends on one sample only (its exponential, right Jacobian and noise) is computed for 16
+// samples at once, one per lane, and read back from LDS: done in turn by all lanes it was most of a
+// sample's 3.6 us. A thread per factor was 63 waves of 1,700 FP64 instructions a sample on a
+// quarter of the CUs and a second launch for the derivatives: 4,000 factors of 20 samples took 52 + 25 us.
+constexpr int kImuLanes = 16;
 __global__ __launch_bounds__(kImuBlock) void imu_preintegrate_kernel(
     const double* __restrict__ imu, long long m, const long long* __restrict__ seg, int F,
     const double* __restrict__ bias, double sg2, double sa2, double* __restrict__ pre,
     double* __restrict__ cov, double* __restrict__ jac, unsigned* __restrict__ flags) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= F) return;
+  __shared__ double sS[kImuBlock / kImuLanes][9][9];
+  __shared__ double sM[kImuBlock / kImuLanes][kImuLanes][24];  // E, J_r, a, dt, gyro and acc noise
+  const int f = (int)(((long long)blockIdx.x * kImuBlock + threadIdx.x) / kImuLanes);
+  const int c = threadIdx.x & (kImuLanes - 1), slot = threadIdx.x / kImuLanes;
+  if (f >= F) return;  // whole rows
   const long long k0 = seg[f], k1 = seg[f + 1];
   if (k0 < 0 || k1 < k0 || k1 > m) {
-    atomicOr(flags, kFlagBadIndex);
+    if (c == 0) atomicOr(flags, kFlagBadIndex);
     return;
   }
   const double ba[3] = {bias[6 * f], bias[6 * f + 1], bias[6 * f + 2]};
   const double bw[3] = {bias[6 * f + 3], bias[6 * f + 4], bias[6 * f + 5]};
   double dR[3][3] = {{1.0, 0.0, 0.0}, {0.0, 1.0, 0.0}, {0.0, 0.0, 1.0}};
   double dv[3] = {0.0, 0.0, 0.0}, dp[3] = {0.0, 0.0, 0.0}, T = 0.0;
-  double S[COV ? 9 : 1][COV ? 9 : 1];
-  if constexpr (COV) {
+  double x[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // this lane's column
+  // the column's place in its 3 x 3 block, and which block: S 0 .. 2, J 3 (b_a), 4 (b_w), 5 none
+  const int cc = c % 3, blk = c / 3;
+  bool bad = false;
+  for (long long k = k0; k < k1; ++k) {
+    const int at_lane = (int)((k - k0) & (kImuLanes - 1));
+    if (at_lane == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (k + c < k1) {
+        const double* row = imu + 7 * (k + c);
+        const double dt = row[6];
+        if (!(dt > 0.0) || !isfinite(dt)) bad = true;
+        const double wt[3] = {(row[0] - bw[0]) * dt, (row[1] - bw[1]) * dt, (row[2] - bw[2]) * dt};
+        double E[3][3], Jr[3][3];
+        so3_exp_jr(wt, E, Jr);
+        double* o = sM[slot][c];
 #pragma unroll
-    for (int r = 0; r < 9; ++r)
+        for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 9; ++c) S[r][c] = 0.0;
-  }
-  // bias derivatives: JR = d(dphi)/d(b_w), Jva / Jvw, Jpa / Jpw
-  double JR[JAC ? 3 : 1][3], Jva[JAC ? 3 : 1][3], Jvw[JAC ? 3 : 1][3], Jpa[JAC ? 3 : 1][3],
-      Jpw[JAC ? 3 : 1][3];
-  if constexpr (JAC) {
+          for (int q = 0; q < 3; ++q) {
+            o[3 * r + q] = E[r][q];
+            o[9 + 3 * r + q] = Jr[r][q];
+          }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) o[18 + r] = row[3 + r] - ba[r];
+        o[21] = dt;
+        o[22] = sg2 / dt * dt * dt;
+        o[23] = sa2 / dt * dt * dt;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    const double* o = sM[slot][at_lane];
+    double E[3][3], Jr[3][3];
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) JR[r][c] = Jva[r][c] = Jvw[r][c] = Jpa[r][c] = Jpw[r][c] = 0.0;
-  }
-  bool bad = false;
-  for (long long k = k0; k < k1; ++k) {
-    const double* row = imu + 7 * k;
-    const double dt = row[6];
-    if (!(dt > 0.0) || !isfinite(dt)) bad = true;
-    const double wt[3] = {(row[0] - bw[0]) * dt, (row[1] - bw[1]) * dt, (row[2] - bw[2]) * dt};
-    const double at[3] = {row[3] - ba[0], row[4] - ba[1], row[5] - ba[2]};
-    double E[3][3], Jr[3][3];
-    so3_exp_jr(wt, E, Jr);
-    // M1 = -dR [a]x dt; the position row of A is M1 dt / 2 and dt I
+      for (int q = 0; q < 3; ++q) {
+        E[r][q] = o[3 * r + q];
+        Jr[r][q] = o[9 + 3 * r + q];
+      }
+    const double at[3] = {o[18], o[19], o[20]};
+    const double dt = o[21], qg = o[22], qa = o[23];
+    // M1 = -dR [a]x dt
     double Ka[3][3], M1[3][3];
     hat3(at, Ka);
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        M1[r][c] = -(dR[r][0] * Ka[0][c] + dR[r][1] * Ka[1][c] + dR[r][2] * Ka[2][c]) * dt;
-    if constexpr (JAC) {
-      // with D = -dR [a]x JR (the rotation's bias derivative seen by the acceleration):
-      //   Jp += Jv dt + (-dR dt^2/2 | D dt^2/2), Jv += (-dR dt | D dt), JR <- E^T JR - J_r dt
-      double KJ[3][3], D[3][3];
+      for (int q = 0; q < 3; ++q)
+        M1[r][q] = -(dR[r][0] * Ka[0][q] + dR[r][1] * Ka[1][q] + dR[r][2] * Ka[2][q]) * dt;
+    // column of A S or A J
+    double y[9];
 #pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          KJ[r][c] = Ka[r][0] * JR[0][c] + Ka[r][1] * JR[1][c] + Ka[r][2] * JR[2][c];
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          D[r][c] = -(dR[r][0] * KJ[0][c] + dR[r][1] * KJ[1][c] + dR[r][2] * KJ[2][c]);
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          Jpa[r][c] += Jva[r][c] * dt - 0.5 * dR[r][c] * dt * dt;
-          Jpw[r][c] += Jvw[r][c] * dt + 0.5 * D[r][c] * dt * dt;
-          Jva[r][c] -= dR[r][c] * dt;
-          Jvw[r][c] += D[r][c] * dt;
-        }
-      double nJ[3][3];
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          nJ[r][c] = E[0][r] * JR[0][c] + E[1][r] * JR[1][c] + E[2][r] * JR[2][c] - Jr[r][c] * dt;
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) JR[r][c] = nJ[r][c];
+    for (int r = 0; r < 3; ++r) {
+      const double mm = M1[r][0] * x[0] + M1[r][1] * x[1] + M1[r][2] * x[2];
+      y[r] = E[0][r] * x[0] + E[1][r] * x[1] + E[2][r] * x[2];
+      y[3 + r] = mm + x[3 + r];
+      y[6 + r] = 0.5 * dt * mm + dt * x[3 + r] + x[6 + r];
     }
-    if constexpr (COV) {
-    // X = A S (row blocks: E^T S0, M1 S0 + S1, M1 dt/2 S0 + dt S1 + S2)
-    double X[9][9];
+    // this column's coefficients on columns 0 .. 2 of A S: row c of A's first block column, and its
+    // column of dR and J_r
+    double a0[3], dRc[3], Jrc[3];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) {
-        const double s0 = E[0][r] * S[0][c] + E[1][r] * S[1][c] + E[2][r] * S[2][c];
-        const double m = M1[r][0] * S[0][c] + M1[r][1] * S[1][c] + M1[r][2] * S[2][c];
-        X[r][c] = s0;
-        X[3 + r][c] = m + S[3 + r][c];
-        X[6 + r][c] = 0.5 * dt * m + dt * S[3 + r][c] + S[6 + r][c];
-      }
+    for (int q = 0; q < 3; ++q) {
+      const double e = cc == 0 ? E[q][0] : (cc == 1 ? E[q][1] : E[q][2]);
+      const double mq = cc == 0 ? M1[0][q] : (cc == 1 ? M1[1][q] : M1[2][q]);
+      a0[q] = blk == 0 ? e : (blk == 1 ? mq : 0.5 * dt * mq);
+      dRc[q] = cc == 0 ? dR[q][0] : (cc == 1 ? dR[q][1] : dR[q][2]);
+      Jrc[q] = cc == 0 ? Jr[q][0] : (cc == 1 ? Jr[q][1] : Jr[q][2]);
     }
-    // S = X A^T (column blocks: X0 E, X0 M1^T + X1, X0 M1^T dt/2 + dt X1 + X2)
 #pragma unroll
     for (int r = 0; r < 9; ++r) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const double e0 = X[r][0] * E[0][c] + X[r][1] * E[1][c] + X[r][2] * E[2][c];
-        const double m = X[r][0] * M1[c][0] + X[r][1] * M1[c][1] + X[r][2] * M1[c][2];
-        S[r][c] = e0;
-        S[r][3 + c] = m + X[r][3 + c];
-        S[r][6 + c] = 0.5 * dt * m + dt * X[r][3 + c] + X[r][6 + c];
-      }
+      // (A S) A^T: the position columns also take dt times the velocity column three lanes below
+      const double z = a0[0] * row_lane<0>(y[r]) + a0[1] * row_lane<1>(y[r]) + a0[2] * row_lane<2>(y[r]);
+      const double vel = __shfl_up(y[r], 3, kImuLanes);
+      x[r] = blk == 0 ? z : (blk == 1 ? z + y[r] : (blk == 2 ? z + dt * vel + y[r] : y[r]));
     }
-    // + B Q B^T: gyro noise through J_r dt into dphi; accelerometer noise through dR dt into dv
-    // and dR dt^2 / 2 into dp
-    const double qg = sg2 / dt * dt * dt, qa = sa2 / dt * dt * dt;
+    // + B Q B^T (gyro noise through J_r dt, accelerometer noise through dR dt and dR dt^2 / 2), or the
+    // derivatives' own terms
+    double jj[3], rr[3];
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+    for (int r = 0; r < 3; ++r) {
+      // column cc of J_r J_r^T and dR dR^T: row r times row cc
+      const double j0 = cc == 0 ? Jr[0][0] : (cc == 1 ? Jr[1][0] : Jr[2][0]);
+      const double j1 = cc == 0 ? Jr[0][1] : (cc == 1 ? Jr[1][1] : Jr[2][1]);
+      const double j2 = cc == 0 ? Jr[0][2] : (cc == 1 ? Jr[1][2] : Jr[2][2]);
+      const double r0 = cc == 0 ? dR[0][0] : (cc == 1 ? dR[1][0] : dR[2][0]);
+      const double r1 = cc == 0 ? dR[0][1] : (cc == 1 ? dR[1][1] : dR[2][1]);
+      const double r2 = cc == 0 ? dR[0][2] : (cc == 1 ? dR[1][2] : dR[2][2]);
+      jj[r] = Jr[r][0] * j0 + Jr[r][1] * j1 + Jr[r][2] * j2;
+      rr[r] = dR[r][0] * r0 + dR[r][1] * r1 + dR[r][2] * r2;
+    }
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const double jj = Jr[r][0] * Jr[c][0] + Jr[r][1] * Jr[c][1] + Jr[r][2] * Jr[c][2];
-        const double rr = dR[r][0] * dR[c][0] + dR[r][1] * dR[c][1] + dR[r][2] * dR[c][2];
-        S[r][c] += qg * jj;
-        S[3 + r][3 + c] += qa * rr;
-        S[3 + r][6 + c] += 0.5 * dt * qa * rr;
-        S[6 + r][3 + c] += 0.5 * dt * qa * rr;
-        S[6 + r][6 + c] += 0.25 * dt * dt * qa * rr;
-      }
+    for (int r = 0; r < 3; ++r) {
+      const double rot = blk == 0 ? qg * jj[r] : (blk == 4 ? -Jrc[r] * dt : 0.0);
+      const double vel = blk == 1 ? qa * rr[r]
+                                  : (blk == 2 ? 0.5 * dt * qa * rr[r] : (blk == 3 ? -dRc[r] * dt : 0.0));
+      const double pos = blk == 1 ? 0.5 * dt * qa * rr[r]
+                                  : (blk == 2 ? 0.25 * dt * dt * qa * rr[r]
+                                              : (blk == 3 ? -0.5 * dRc[r] * dt * dt : 0.0));
+      x[r] += rot;
+      x[3 + r] += vel;
+      x[6 + r] += pos;
     }
     // the mean
     double ra[3];
@@ -232,48 +245,42 @@ __global__ __launch_bounds__(kImuBlock) void imu_preintegrate_kernel(
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        nR[r][c] = dR[r][0] * E[0][c] + dR[r][1] * E[1][c] + dR[r][2] * E[2][c];
+      for (int q = 0; q < 3; ++q)
+        nR[r][q] = dR[r][0] * E[0][q] + dR[r][1] * E[1][q] + dR[r][2] * E[2][q];
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) dR[r][c] = nR[r][c];
+      for (int q = 0; q < 3; ++q) dR[r][q] = nR[r][q];
     T += dt;
   }
   if (bad) atomicOr(flags, kFlagNonFinite);
-  if constexpr (COV) {
+  if (c == 15) {
     double* o = pre + 16 * (long long)f;
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) o[3 * r + c] = dR[r][c];
-#pragma unroll
     for (int r = 0; r < 3; ++r) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) o[3 * r + q] = dR[r][q];
       o[9 + r] = dv[r];
       o[12 + r] = dp[r];
     }
     o[15] = T;
-    if (cov) {
-      double* oc = cov + 81 * (long long)f;
-#pragma unroll
-      for (int r = 0; r < 9; ++r)
-#pragma unroll
-        for (int c = 0; c < 9; ++c) oc[9 * r + c] = 0.5 * (S[r][c] + S[c][r]);
-    }
   }
-  if constexpr (JAC) {
-    double* o = jac + 54 * (long long)f;
+  if (jac && c >= 9 && c < 15) {
+    double* o = jac + 54 * (long long)f + (c - 9);
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+    for (int r = 0; r < 9; ++r) o[6 * r] = x[r];
+  }
+  // the symmetric part of S (the lanes' columns meet in LDS; a row's 16 lanes are in one wave)
+  if (c < 9) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        o[6 * r + c] = 0.0;
-        o[6 * r + 3 + c] = JR[r][c];
-        o[6 * (3 + r) + c] = Jva[r][c];
-        o[6 * (3 + r) + 3 + c] = Jvw[r][c];
-        o[6 * (6 + r) + c] = Jpa[r][c];
-        o[6 * (6 + r) + 3 + c] = Jpw[r][c];
-      }
+    for (int r = 0; r < 9; ++r) sS[slot][r][c] = x[r];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (c < 9) {
+    double* oc = cov + 81 * (long long)f + c;
+#pragma unroll
+    for (int r = 0; r < 9; ++r) oc[9 * r] = 0.5 * (x[r] + sS[slot][c][r]);
   }
 }
 
@@ -427,10 +434,12 @@ __global__ __launch_bounds__(kImuBlock) void imu_linearize_kernel(
 //   dR Exp(J_R,w db_w), dv + J_v db, dp + J_p db,
 // the residual above with them, and the bias random walk b_j - b_i (covariance
 // diag(sigma_ba^2, sigma_bw^2) dt): 15 residuals over 30 unknowns [xi_i, v_i, b_i, xi_j, v_j, b_j].
-// One block of 64 threads per factor: thread 0 forms the residual and the Jacobian's nonzero
-// blocks in LDS and the Cholesky factor of the preintegration covariance; the threads whiten the
-// 31 columns of [J | r] (one each) and form H = J~^T J~ (an entry each), b = J~^T r~, e = |r~|^2.
-constexpr int kImuBiasThreads = 64;
+// Eight factors per block of 256 threads: a lane per factor forms the residual and the Jacobian's
+// nonzero blocks in LDS while a lane per factor of another wave forms the Cholesky factor of the
+// preintegration covariance in registers (with a block per factor that serial part was issued for
+// one lane at a time, and 4,000 of them took 40 us); then a thread per column whitens [J | r], and a
+// thread per column of H = J~^T J~ keeps its own column of J~ in registers; b = J~^T r~, e = |r~|^2.
+constexpr int kImuBiasThreads = 256, kImuBiasFactors = 8;
 __global__ __launch_bounds__(kImuBiasThreads) void imu_linearize_bias_kernel(
     const double* __restrict__ pre, const double* __restrict__ cov,
     const double* __restrict__ jac, const double* __restrict__ bias0,
@@ -438,20 +447,55 @@ __global__ __launch_bounds__(kImuBiasThreads) void imu_linearize_bias_kernel(
     const double* __restrict__ vel, const double* __restrict__ biases, int P, double g0,
     double g1, double g2, double qa, double qw, double* __restrict__ H,
     double* __restrict__ bout, double* __restrict__ err, unsigned* __restrict__ flags) {
-  __shared__ double J[15][31];  // column 30: the residual
-  __shared__ double L[9][9];
-  __shared__ double wb[6];
-  __shared__ int ok;
-  const int f = blockIdx.x, t = threadIdx.x;
-  for (int e = t; e < 15 * 31; e += kImuBiasThreads) J[e / 31][e % 31] = 0.0;
+  __shared__ double sJ[kImuBiasFactors][15][31];  // column 30: the residual
+  __shared__ double sL[kImuBiasFactors][9][9];    // below the diagonal L, on it 1 / L[c][c]
+  __shared__ double sw[kImuBiasFactors][6];
+  __shared__ int ok_range[kImuBiasFactors], ok_val[kImuBiasFactors], ok_pd[kImuBiasFactors];
+  const int f0 = blockIdx.x * kImuBiasFactors, t = threadIdx.x;
+  for (int e = t; e < kImuBiasFactors * 15 * 31; e += kImuBiasThreads) (&sJ[0][0][0])[e] = 0.0;
   __syncthreads();
-  if (t == 0) {
-    ok = 1;
+  if (t >= 64 && t < 64 + kImuBiasFactors && f0 + t - 64 < F) {
+    const int u = t - 64;
+    const double* S = cov + 81 * (long long)(f0 + u);
+    double L[9][9];
+    bool pd = true;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+      double d = S[9 * c + c];
+#pragma unroll
+      for (int q = 0; q < c; ++q) d -= L[c][q] * L[c][q];
+      if (!(d > 1e-13 * S[9 * c + c])) {  // not positive definite to working precision
+        pd = false;
+        d = 1.0;
+      }
+      const double lc = sqrt(d), inv = 1.0 / lc;
+      L[c][c] = lc;
+#pragma unroll
+      for (int r = c + 1; r < 9; ++r) {
+        double v = S[9 * r + c];
+#pragma unroll
+        for (int q = 0; q < c; ++q) v -= L[r][q] * L[c][q];
+        L[r][c] = v * inv;
+      }
+      sL[u][c][c] = inv;
+    }
+#pragma unroll
+    for (int r = 0; r < 9; ++r)
+#pragma unroll
+      for (int c = 0; c < r; ++c) sL[u][r][c] = L[r][c];
+    ok_pd[u] = pd ? 1 : 0;
+  }
+  if (t < kImuBiasFactors && f0 + t < F) {
+    const int f = f0 + t;
+    double (*J)[31] = sJ[t];
+    double* wb = sw[t];
+    int ok = 1;
     const int i = idx[2 * f], j = idx[2 * f + 1];
     if (i < 0 || i >= P || j < 0 || j >= P) {
       atomicOr(flags, kFlagBadIndex);
-      ok = 0;
+      ok_range[t] = 0;
     } else {
+      ok_range[t] = 1;
       const double* p = pre + 16 * (long long)f;
       const double* Jb = jac + 54 * (long long)f;  // [9][6]
       const double* Ti = poses + 12 * (long long)i;
@@ -551,60 +595,53 @@ __global__ __launch_bounds__(kImuBiasThreads) void imu_linearize_bias_kernel(
         wb[k] = 1.0 / sqrt(q);
         if (!(q > 0.0) || !isfinite(q)) ok = 0;
       }
-      // Cholesky factor of the preintegration covariance
-      const double* S = cov + 81 * (long long)f;
-      bool pd = true;
-      for (int c = 0; c < 9; ++c) {
-        double d = S[9 * c + c];
-        for (int q = 0; q < c; ++q) d -= L[c][q] * L[c][q];
-        if (!(d > 1e-13 * S[9 * c + c])) {
-          pd = false;
-          d = 1.0;
-        }
-        const double lc = sqrt(d);
-        L[c][c] = lc;
-        const double inv = 1.0 / lc;
-        for (int r = c + 1; r < 9; ++r) {
-          double v = S[9 * r + c];
-          for (int q = 0; q < c; ++q) v -= L[r][q] * L[c][q];
-          L[r][c] = v * inv;
-        }
-        for (int r = 0; r < c; ++r) L[r][c] = 0.0;
-      }
-      if (!pd || !ok) {
-        atomicOr(flags, kFlagNonFinite);
-        ok = pd && ok;
-      }
     }
+    ok_val[t] = ok;
   }
   __syncthreads();
-  if (!ok) return;
+  if (t < kImuBiasFactors && f0 + t < F && ok_range[t] && !(ok_val[t] && ok_pd[t]))
+    atomicOr(flags, kFlagNonFinite);
   // whiten the columns of [J | r]: L^-1 for the preintegration rows, 1 / sqrt(q dt) for the walk
-  if (t < 31) {
-    for (int r = 0; r < 9; ++r) {
-      double v = J[r][t];
-      for (int q = 0; q < r; ++q) v -= L[r][q] * J[q][t];
-      J[r][t] = v / L[r][r];
+  if (t < kImuBiasFactors * 31) {
+    const int u = t / 31, c = t - 31 * u;
+    if (f0 + u < F && ok_range[u] && ok_val[u] && ok_pd[u]) {
+      double y[9];
+#pragma unroll
+      for (int r = 0; r < 9; ++r) {
+        double v = sJ[u][r][c];
+#pragma unroll
+        for (int q = 0; q < r; ++q) v -= sL[u][r][q] * y[q];
+        y[r] = v * sL[u][r][r];
+      }
+#pragma unroll
+      for (int r = 0; r < 9; ++r) sJ[u][r][c] = y[r];
+#pragma unroll
+      for (int r = 0; r < 6; ++r) sJ[u][9 + r][c] *= sw[u][r];
     }
-    for (int r = 9; r < 15; ++r) J[r][t] *= wb[r - 9];
   }
   __syncthreads();
-  double* Ho = H + 900 * (long long)f;
-  for (int e = t; e < 900; e += kImuBiasThreads) {
-    const int a = e / 30, c = e % 30;
-    double v = 0.0;
-    for (int r = 0; r < 15; ++r) v += J[r][a] * J[r][c];
-    Ho[e] = v;
-  }
-  if (t < 30) {
-    double v = 0.0;
-    for (int r = 0; r < 15; ++r) v += J[r][t] * J[r][30];
-    bout[30 * (long long)f + t] = v;
-  }
-  if (t == 0) {
-    double e = 0.0;
-    for (int r = 0; r < 15; ++r) e += J[r][30] * J[r][30];
-    err[f] = e;
+  if (t < kImuBiasFactors * 30) {
+    const int u = t / 30, c = t - 30 * u;
+    const int f = f0 + u;
+    if (f >= F || !(ok_range[u] && ok_val[u] && ok_pd[u])) return;
+    double col[15];
+#pragma unroll
+    for (int r = 0; r < 15; ++r) col[r] = sJ[u][r][c];
+    double* Ho = H + 900 * (long long)f + c;
+    for (int a = 0; a < 30; ++a) {  // column c of row a: a wave's lanes write whole rows
+      double v = 0.0;
+#pragma unroll
+      for (int r = 0; r < 15; ++r) v += sJ[u][r][a] * col[r];
+      Ho[30 * a] = v;
+    }
+    double v = 0.0, e = 0.0;
+#pragma unroll
+    for (int r = 0; r < 15; ++r) {
+      v += col[r] * sJ[u][r][30];
+      e += sJ[u][r][30] * sJ[u][r][30];
+    }
+    bout[30 * (long long)f + c] = v;
+    if (c == 0) err[f] = e;
   }
 }
 
@@ -615,14 +652,10 @@ void launch_imu_preintegrate(const double* imu, int64_t m, const int64_t* seg, i
                              double sigma_g, double sigma_a, double* pre, double* cov,
                              double* jac, unsigned* flags, hipStream_t s) {
   if (F <= 0) return;
-  const unsigned grid = (unsigned)((F + kImuBlock - 1) / kImuBlock);
-  imu_preintegrate_kernel<true, false><<<grid, kImuBlock, 0, s>>>(
+  const unsigned grid = (unsigned)(((long long)F * kImuLanes + kImuBlock - 1) / kImuBlock);
+  imu_preintegrate_kernel<<<grid, kImuBlock, 0, s>>>(
       imu, (long long)m, reinterpret_cast<const long long*>(seg), F, bias, sigma_g * sigma_g,
-      sigma_a * sigma_a, pre, cov, nullptr, flags);
-  if (jac)
-    imu_preintegrate_kernel<false, true><<<grid, kImuBlock, 0, s>>>(
-        imu, (long long)m, reinterpret_cast<const long long*>(seg), F, bias, 0.0, 0.0, nullptr,
-        nullptr, jac, flags);
+      sigma_a * sigma_a, pre, cov, jac, flags);
 }
 
 void launch_imu_linearize_bias(const double* pre, const double* cov, const double* jac,
@@ -632,7 +665,7 @@ void launch_imu_linearize_bias(const double* pre, const double* cov, const doubl
                                double* H, double* b, double* err, unsigned* flags,
                                hipStream_t s) {
   if (F <= 0) return;
-  imu_linearize_bias_kernel<<<F, kImuBiasThreads, 0, s>>>(
+  imu_linearize_bias_kernel<<<(F + kImuBiasFactors - 1) / kImuBiasFactors, kImuBiasThreads, 0, s>>>(
       pre, cov, jac, bias0, idx, F, poses, vel, biases, P, g[0], g[1], g[2],
       sigma_ba * sigma_ba, sigma_bw * sigma_bw, H, b, err, flags);
 }
