@@ -365,6 +365,31 @@ VGICP_API vgicp_status vgicp_backward_tangent(vgicp_voxelmap map, const float* x
                                               vgicp_precision precision, double* grad_xi,
                                               float* grad_xyz, vgicp_stream stream);
 
+/* The calls above with the caller's own device workspace for the per-tile partial sums, instead of a
+ * stream-ordered allocation per call (18 us of a small factor's 40): same arguments, kernels, results
+ * (bitwise) and errors, and E_INVALID_ARG for a NULL workspace, E_CAPACITY for one smaller than
+ * vgicp_workspace_size(n). The workspace (8-byte aligned) is written and read by the call's work on
+ * `stream` only: it may be used again by later work of the same stream at once, by others after an
+ * ordering of the caller's. */
+VGICP_API vgicp_status vgicp_workspace_size(int64_t n, int64_t* bytes);
+VGICP_API vgicp_status vgicp_linearize_workspace(
+    vgicp_voxelmap map, const float* xyz, const float* cov, int64_t n, const double* T_target,
+    const double* T_source, int32_t binary, vgicp_precision precision, double* H, double* b,
+    double* err, int64_t* inliers, int32_t* corr, void* workspace, int64_t workspace_bytes,
+    vgicp_stream stream);
+VGICP_API vgicp_status vgicp_evaluate_workspace(vgicp_voxelmap map, const float* xyz,
+                                                const float* cov, int64_t n,
+                                                const double* T_target, const double* T_source,
+                                                vgicp_precision precision, double* err,
+                                                int64_t* inliers, int32_t* corr,
+                                                void* workspace, int64_t workspace_bytes,
+                                                vgicp_stream stream);
+VGICP_API vgicp_status vgicp_backward_tangent_workspace(
+    vgicp_voxelmap map, const float* xyz, const float* cov, int64_t n, const double* T_target,
+    const double* T_source, const double* xi_target, const double* xi_source, int32_t binary,
+    const int32_t* corr, const double* grad_err, vgicp_precision precision, double* grad_xi,
+    float* grad_xyz, void* workspace, int64_t workspace_bytes, vgicp_stream stream);
+
 /* ---------------------------------------------------------------------------- batches */
 
 /* Prepares a batch of factors (Sec. III-F: one factor per submap pair, re-linearized in

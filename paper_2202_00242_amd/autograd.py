@@ -43,8 +43,9 @@ class VGICPCost(torch.autograd.Function):
         gxi, gp = V.vgicp_backward_tangent(ctx.vmap, xyz, cov, Tt, Ts, xt, xs, ctx.binary, corr,
                                            g, ctx.precision,
                                            want_points=ctx.needs_input_grad[2])
-        g_s = gxi[:6].to(ctx.xi_device)
-        g_t = gxi[6:].to(ctx.xi_device) if ctx.binary else None
+        gxi = gxi.to(ctx.xi_device)  # one copy for both halves
+        g_s = gxi[:6]
+        g_t = gxi[6:] if ctx.binary else None
         return g_s, g_t, gp, None, None, None, None, None, None
 
 

@@ -93,29 +93,73 @@ int device_cu_count(int device) {
   return d && d->cus > 0 ? d->cus : 256;
 }
 
-hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s) {
-  static std::mutex mu;
-  static std::map<int, hipMemPool_t> pools;  // one per device, for the life of the process
+namespace {
+struct Block {
+  void* p;
+  size_t bytes;
+  int device;
+};
+std::mutex g_block_mutex;
+std::vector<Block>& idle_blocks() {  // not destroyed: calls may run while the process ends
+  static auto* v = new std::vector<Block>;
+  return *v;
+}
+}  // namespace
+
+// Sizes are powers of two up to 16 MiB (at least 64 KiB) and multiples of an eighth of one above, so
+// that calls of other sizes find the blocks again.
+hipError_t block_take(void** p, size_t* bytes) {
+  size_t b = 1u << 16;
+  while (b < *bytes) b <<= 1;
+  if (b > (16u << 20)) b = (*bytes + b / 16 - 1) / (b / 16) * (b / 16);
+  *bytes = b;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  hipMemPool_t pool = nullptr;
   {
-    std::lock_guard<std::mutex> lk(mu);
-    auto it = pools.find(dev);
-    if (it == pools.end()) {
-      hipMemPoolProps props{};
-      props.allocType = hipMemAllocationTypePinned;
-      props.location.type = hipMemLocationTypeDevice;
-      props.location.id = dev;
-      if ((e = hipMemPoolCreate(&pool, &props)) != hipSuccess) return e;
-      uint64_t keep = kPoolKeep;
-      (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-      it = pools.emplace(dev, pool).first;
-    }
-    pool = it->second;
+    std::lock_guard<std::mutex> lk(g_block_mutex);
+    auto& v = idle_blocks();
+    for (size_t i = v.size(); i-- > 0;)
+      if (v[i].device == dev && v[i].bytes == b) {
+        *p = v[i].p;
+        v.erase(v.begin() + (long)i);
+        return hipSuccess;
+      }
   }
-  return hipMallocFromPoolAsync(p, bytes, pool, s);
+  e = hipMalloc(p, b);
+  if (e == hipSuccess) return e;
+  // out of memory: the idle blocks go first
+  std::vector<Block> idle;
+  {
+    std::lock_guard<std::mutex> lk(g_block_mutex);
+    idle.swap(idle_blocks());
+  }
+  for (const Block& k : idle) (void)hipFree(k.p);
+  if (idle.empty()) return e;
+  (void)hipGetLastError();
+  return hipMalloc(p, b);
+}
+
+void block_give(void* p, size_t bytes, int device) {
+  if (!p) return;
+  std::vector<Block> drop;
+  {
+    std::lock_guard<std::mutex> lk(g_block_mutex);
+    auto& v = idle_blocks();
+    v.push_back({p, bytes, device});
+    size_t kept = 0;
+    for (const Block& k : v) kept += k.device == device ? k.bytes : 0;
+    for (size_t i = 0; i < v.size() && kept > kBlocksKeep;) {  // the oldest first
+      if (v[i].device != device) {
+        ++i;
+        continue;
+      }
+      kept -= v[i].bytes;
+      drop.push_back(v[i]);
+      v.erase(v.begin() + (long)i);
+    }
+  }
+  for (const Block& k : drop) (void)hipFree(k.p);
 }
 
 namespace {
@@ -506,7 +550,8 @@ static vgicp_status single_factor(vgicp_voxelmap map, const float* xyz, const fl
                                   int64_t n, const double* T_target, const double* T_source,
                                   int32_t binary, int precision, bool linearize, double* H,
                                   double* b, double* err, int64_t* inliers, int32_t* corr,
-                                  vgicp_stream stream, bool noalloc = false) {
+                                  vgicp_stream stream, bool noalloc = false,
+                                  void* workspace = nullptr, size_t workspace_bytes = 0) {
   vgicp_status st = check_map(map);
   if (st != VGICP_OK) return st;
   if ((st = check_cloud(xyz, cov, n)) != VGICP_OK) return st;
@@ -532,6 +577,10 @@ static vgicp_status single_factor(vgicp_voxelmap map, const float* xyz, const fl
                                         std::to_string(kNoAllocMaxTiles));
     if (!(partials = device_scratch(map->device)))
       return fail(VGICP_E_HIP, "static scratch address");
+  } else if (workspace) {
+    if (workspace_bytes < (size_t)std::max(ntiles, 1) * kPartialStride * sizeof(double))
+      return fail(VGICP_E_CAPACITY, "workspace smaller than vgicp_workspace_size");
+    partials = static_cast<double*>(workspace);
   } else if ((e = hipMallocAsync(reinterpret_cast<void**>(&partials),
                                  (size_t)std::max(ntiles, 1) * kPartialStride * sizeof(double),
                                  s)) != hipSuccess) {
@@ -540,7 +589,7 @@ static vgicp_status single_factor(vgicp_voxelmap map, const float* xyz, const fl
   launch_plain(map->view(), T, xyz, cov, n, binary, precision, linearize, partials, ntiles, tile,
                corr, flags, H, b, err, inliers, s);
   e = hipGetLastError();
-  if (!noalloc) (void)hipFreeAsync(partials, s);
+  if (!noalloc && !workspace) (void)hipFreeAsync(partials, s);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return VGICP_OK;
 }
@@ -580,7 +629,8 @@ static vgicp_status backward_impl(vgicp_voxelmap map, const float* xyz, const fl
                                   const double* xi_target, const double* xi_source,
                                   int32_t binary, const int32_t* corr, const double* grad_err,
                                   int precision, double* grad_xi, float* grad_xyz,
-                                  vgicp_stream stream) {
+                                  vgicp_stream stream, void* workspace = nullptr,
+                                  size_t workspace_bytes = 0) {
   vgicp_status st = check_map(map);
   if (st != VGICP_OK) return st;
   if ((st = check_cloud(xyz, cov, n)) != VGICP_OK) return st;
@@ -613,16 +663,66 @@ static vgicp_status backward_impl(vgicp_voxelmap map, const float* xyz, const fl
   const RelPose T = make_rel_pose(Tt, Ts, map->inv_res);
   const int tile = plain_tile_for(n, device_cu_count(map->device));
   const int ntiles = (int)((n + tile - 1) / tile);
-  double* partials = nullptr;
-  hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&partials),
-                                (size_t)std::max(ntiles, 1) * 6 * sizeof(double), s);
+  double* partials = static_cast<double*>(workspace);
+  const size_t want = (size_t)std::max(ntiles, 1) * 6 * sizeof(double);
+  if (workspace && workspace_bytes < want)
+    return fail(VGICP_E_CAPACITY, "workspace smaller than vgicp_workspace_size");
+  hipError_t e = workspace ? hipSuccess
+                           : hipMallocAsync(reinterpret_cast<void**>(&partials), want, s);
   if (e != hipSuccess) return hip_fail(e, "hipMallocAsync (partials)");
   launch_backward(map->view(), T, J, xyz, cov, n, binary, precision, corr, grad_err, partials,
                   ntiles, tile, grad_xi, grad_xyz, s);
   e = hipGetLastError();
-  (void)hipFreeAsync(partials, s);
+  if (!workspace) (void)hipFreeAsync(partials, s);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return VGICP_OK;
+}
+
+VGICP_API vgicp_status vgicp_workspace_size(int64_t n, int64_t* bytes) {
+  if (!bytes) return fail(VGICP_E_INVALID_ARG, "bytes is NULL");
+  *bytes = 0;
+  if (n < 0) return fail(VGICP_E_INVALID_ARG, "negative point count");
+  if (n >= kMaxCloudPoints) return fail(VGICP_E_CAPACITY, "cloud of 2^30 points or more");
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  const int tile = plain_tile_for(n, device_cu_count(dev));
+  *bytes = std::max<int64_t>((n + tile - 1) / tile, 1) * kPartialStride * (int64_t)sizeof(double);
+  return VGICP_OK;
+}
+
+VGICP_API vgicp_status vgicp_linearize_workspace(
+    vgicp_voxelmap map, const float* xyz, const float* cov, int64_t n, const double* T_target,
+    const double* T_source, int32_t binary, vgicp_precision precision, double* H, double* b,
+    double* err, int64_t* inliers, int32_t* corr, void* workspace, int64_t workspace_bytes,
+    vgicp_stream stream) {
+  if (!workspace || workspace_bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  return single_factor(map, xyz, cov, n, T_target, T_source, binary, (int)precision, true, H, b,
+                       err, inliers, corr, stream, false, workspace, (size_t)workspace_bytes);
+}
+
+VGICP_API vgicp_status vgicp_evaluate_workspace(vgicp_voxelmap map, const float* xyz,
+                                                const float* cov, int64_t n,
+                                                const double* T_target, const double* T_source,
+                                                vgicp_precision precision, double* err,
+                                                int64_t* inliers, int32_t* corr,
+                                                void* workspace, int64_t workspace_bytes,
+                                                vgicp_stream stream) {
+  if (!workspace || workspace_bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  return single_factor(map, xyz, cov, n, T_target, T_source, 0, (int)precision, false, nullptr,
+                       nullptr, err, inliers, corr, stream, false, workspace,
+                       (size_t)workspace_bytes);
+}
+
+VGICP_API vgicp_status vgicp_backward_tangent_workspace(
+    vgicp_voxelmap map, const float* xyz, const float* cov, int64_t n, const double* T_target,
+    const double* T_source, const double* xi_target, const double* xi_source, int32_t binary,
+    const int32_t* corr, const double* grad_err, vgicp_precision precision, double* grad_xi,
+    float* grad_xyz, void* workspace, int64_t workspace_bytes, vgicp_stream stream) {
+  if (!workspace || workspace_bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  return backward_impl(map, xyz, cov, n, T_target, T_source, xi_target, xi_source, binary, corr,
+                       grad_err, (int)precision, grad_xi, grad_xyz, stream, workspace,
+                       (size_t)workspace_bytes);
 }
 
 VGICP_API vgicp_status vgicp_backward(vgicp_voxelmap map, const float* xyz, const float* cov,
@@ -685,7 +785,8 @@ struct vgicp_batch_s {
   double *d_lm_Hc = nullptr, *d_lm_bc = nullptr, *d_lm_cand = nullptr, *d_lm_lambda = nullptr;
   int *d_lm_pos = nullptr, *d_lm_accept = nullptr;
   vgicp_schedule sched{256, 8192, 4, 4};  // 4 blocks of 4 waves: the batch kernel's 16 waves per CU
-  void* arena = nullptr;            // the pool block of the copies, boxes, relative poses, counters
+  void* arena = nullptr;            // the device block of the copies, boxes, relative poses, counters
+  size_t arena_bytes = 0;
   RelPose* d_rel = nullptr;
   unsigned long long* d_heads = nullptr;
   char* d_sched = nullptr;          // one upload: the factors, the queue segments, the work items
@@ -816,25 +917,19 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
   const size_t o_items = o_seg + Arena::up(seg.size() * sizeof(int));
   const size_t bytes = o_items + items.size() * sizeof(WorkItem);
   const size_t np = (size_t)std::max<int64_t>(total, 1) * (size_t)(sc.block / 64) * kPartialStride;
-  // another schedule may need more: the old blocks' readers are done (set_schedule synchronises)
+  // another schedule may need more: the old blocks' readers are done (the callers synchronise)
   auto grow = [&](void** p, size_t* cap, size_t want) {
     if (want <= *cap) return hipSuccess;
-    if (*p) (void)hipFreeAsync(*p, nullptr);
+    block_give(*p, *cap, b->device);
     *p = nullptr;
     *cap = 0;
-    Arena a;
-    a.need<char>(want);
-    const hipError_t ge = a.get(nullptr, true);
-    if (ge == hipSuccess) {
-      *p = a.base;
-      *cap = want;
-      a.base = nullptr;
-    }
+    const hipError_t ge = block_take(p, &want);
+    if (ge == hipSuccess) *cap = want;
     return ge;
   };
   if ((e = grow(reinterpret_cast<void**>(&b->d_sched), &b->sched_cap, bytes)) ||
       (e = grow(reinterpret_cast<void**>(&b->d_partials), &b->partials_cap, np * sizeof(double))))
-    return hip_fail(e, "pool allocation (schedule)");
+    return hip_fail(e, "device block (schedule)");
   b->d_factors = reinterpret_cast<FactorView*>(b->d_sched);
   b->d_seg = reinterpret_cast<int*>(b->d_sched + o_seg);
   b->d_items = reinterpret_cast<WorkItem*>(b->d_sched + o_items);
@@ -1040,9 +1135,9 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
   own.need<float>(6 * (size_t)std::max(n_clouds, 1));
   own.need<RelPose>(F1);
   own.need<unsigned long long>(kNumXcd * kHeadStride);
-  if ((e = own.get(nullptr, true))) {
+  if ((e = own.get(nullptr))) {
     delete b;
-    return hip_fail(e, "pool allocation (batch)");
+    return hip_fail(e, "device block (batch)");
   }
   b->d_cov6 = own.take<float>(6 * pts1);
   b->d_xyz = own.take<float>(3 * pts1);
@@ -1050,8 +1145,7 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
   b->d_boxes = own.take<float>(6 * (size_t)std::max(n_clouds, 1));
   b->d_rel = own.take<RelPose>(F1);
   b->d_heads = own.take<unsigned long long>(kNumXcd * kHeadStride);
-  b->arena = own.base;
-  own.base = nullptr;  // the batch's now
+  b->arena = own.keep(&b->arena_bytes);
   for (int f = 0; f < n_factors; ++f) {
     const vgicp_factor& fc = factors[f];
     if (fc.target_map < 0 || fc.target_map >= n_maps || fc.source_cloud < 0 ||
@@ -1662,8 +1756,9 @@ VGICP_API vgicp_status vgicp_batch_destroy(vgicp_batch batch) {
   batch->drop_graphs();
   if (batch->capture_stream) (void)hipStreamDestroy(batch->capture_stream);
   if (batch->done) (void)hipEventDestroy(batch->done);
-  for (void* p : {batch->arena, (void*)batch->d_sched, (void*)batch->d_partials})
-    if (p) (void)hipFreeAsync(p, nullptr);
+  block_give(batch->arena, batch->arena_bytes, batch->device);
+  block_give(batch->d_sched, batch->sched_cap, batch->device);
+  block_give(batch->d_partials, batch->partials_cap, batch->device);
   for (void* p : {(void*)batch->d_gpts, (void*)batch->d_gf, (void*)batch->d_gbptr,
                   (void*)batch->d_gbcontrib, (void*)batch->d_cptr, (void*)batch->d_cfac,
                   (void*)batch->d_cloud_n, (void*)batch->d_cloud_off, (void*)batch->d_gout})

@@ -28,7 +28,8 @@ struct vgicp_voxelmap_s {
   int64_t nbricks = 0;
   int gby = 0, gbz = 0;
   vgicp::VoxelData* voxb = nullptr;  // [V] records in brick order (grid layout)
-  void* arena = nullptr;             // the device memory of all the arrays here
+  void* arena = nullptr;             // the device block of all the arrays here
+  size_t arena_bytes = 0;
   int* rec_id = nullptr;             // [V] voxel id of each brick-ordered record
   uint2* slots32 = nullptr;          // [cap] {relative key, id}, when key32
   longlong2* slots64 = nullptr;      // [cap] {packed key, id}, otherwise
@@ -85,34 +86,31 @@ double* device_scratch(int device);
 void relative_pose(const double* Tt, const double* Ts, double* Tts);
 RelPose make_rel_pose(const double* Tt, const double* Ts, double inv_res);
 
-// Device memory of one host call: one block of the library's stream-ordered pool, cut up by take().
-// (hipMalloc per buffer and hipFree, which waits for the device, were half of a sweep's 920 us.) The
-// pool keeps at most kPoolKeep bytes between calls; the block goes back to it on the call's stream,
-// so calls on other streams and threads never see it before this call's work is done.
-constexpr size_t kPoolKeep = 256u << 20;
-hipError_t pool_alloc(void** p, size_t bytes, hipStream_t s);
+// Device blocks that outlive a call. A block is handed out to one owner at a time and comes back only
+// when nothing on the device uses it any more (the owners below wait first), so it is safe across
+// streams and threads; idle blocks of a device are kept up to kBlocksKeep bytes, the rest is freed.
+// (hipMalloc and hipFree per buffer were half of a sweep's 920 us; a stream-ordered pool still took
+// 18 us per allocation and release.) bytes: asked for, then the block's size.
+constexpr size_t kBlocksKeep = 256u << 20;
+hipError_t block_take(void** p, size_t* bytes);
+void block_give(void* p, size_t bytes, int device);
+
+// Device memory of one host call that synchronises its stream: one block, cut up by take(). Sizes
+// are added up with need() first; get() takes the block. On every way out the stream is waited for
+// before the block goes back. A map or batch keeps its block with keep() and gives it back after a
+// device synchronisation.
 struct Arena {
   hipStream_t s = nullptr;
   char* base = nullptr;
   size_t used = 0, size = 0;
-  // Sizes are added up with need() first; get() allocates; take() hands out in any order.
   static size_t up(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
   template <typename T>
   void need(size_t count) {
     size += up(std::max<size_t>(count, 1) * sizeof(T));
   }
-  // Scratch blocks are powers of two of at least 1 MiB, lasting ones powers of two up to 16 MiB and
-  // multiples of an eighth of one above: calls of other sizes then find the pool's blocks again (a
-  // block that the pool has to map anew costs some 300 us).
-  hipError_t get(hipStream_t stream, bool lasting = false) {
+  hipError_t get(hipStream_t stream) {
     s = stream;
-    size_t bytes = 1u << 16;
-    while (bytes < size) bytes <<= 1;
-    if (!lasting)
-      bytes = std::max<size_t>(bytes, 1u << 20);
-    else if (bytes > (16u << 20))
-      bytes = (size + bytes / 16 - 1) / (bytes / 16) * (bytes / 16);
-    return pool_alloc(reinterpret_cast<void**>(&base), bytes, s);
+    return block_take(reinterpret_cast<void**>(&base), &size);
   }
   template <typename T>
   T* take(size_t count) {
@@ -120,8 +118,18 @@ struct Arena {
     used += up(std::max<size_t>(count, 1) * sizeof(T));
     return p;
   }
+  void* keep(size_t* bytes) {
+    void* p = base;
+    *bytes = size;
+    base = nullptr;
+    return p;
+  }
   ~Arena() {
-    if (base) (void)hipFreeAsync(base, s);
+    if (!base) return;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipStreamSynchronize(s);
+    block_give(base, size, dev);
   }
 };
 

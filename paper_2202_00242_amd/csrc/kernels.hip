@@ -775,41 +775,48 @@ __global__ void backward_finalize_kernel(const double* __restrict__ partials, in
                                          RelPose T, int binary, TangentMap J,
                                          const double* __restrict__ grad_err,
                                          double* __restrict__ grad_xi) {
-  __shared__ double s[6];
+  __shared__ double s[12];  // source gradient, then the target's
   const int i = threadIdx.x;
   if (i < 6) {
     double a = 0.0;
-    for (int t = 0; t < ntiles; ++t) a += partials[(long long)t * 6 + i];
+    int t = 0;
+    for (; t + 16 <= ntiles; t += 16) {  // sixteen loads in flight, added in order
+      double v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[q] = partials[(long long)(t + q) * 6 + i];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) a += v[q];
+    }
+    for (; t < ntiles; ++t) a += partials[(long long)t * 6 + i];
     s[i] = a * (*grad_err);
   }
   __syncthreads();
-  if (i == 0) {
-    double g[12];
-    for (int k = 0; k < 6; ++k) g[k] = s[k];
-    if (binary) {
-      double Rt[9], st[3], A[36];
-      for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) Rt[3 * r + c] = T.R[3 * c + r];
-      for (int r = 0; r < 3; ++r)
-        st[r] = -(Rt[3 * r] * T.t[0] + Rt[3 * r + 1] * T.t[1] + Rt[3 * r + 2] * T.t[2]);
-      adjoint(Rt, st, A);
-      for (int c = 0; c < 6; ++c) {
-        double x = 0.0;
-        for (int r = 0; r < 6; ++r) x += A[6 * r + c] * s[r];
-        g[6 + c] = -x;
-      }
+  if (binary && i < 6) {
+    // column i of A = Ad(T_st), T_st = [R^T | -R^T t]: [[R^T, 0], [[st]x R^T, R^T]]
+    double st[3];
+    for (int r = 0; r < 3; ++r)
+      st[r] = -(T.R[r] * T.t[0] + T.R[3 + r] * T.t[1] + T.R[6 + r] * T.t[2]);
+    const int c = i < 3 ? i : i - 3;
+    // column c of R^T is row c of R
+    const double c0 = c == 0 ? T.R[0] : (c == 1 ? T.R[3] : T.R[6]);
+    const double c1 = c == 0 ? T.R[1] : (c == 1 ? T.R[4] : T.R[7]);
+    const double c2 = c == 0 ? T.R[2] : (c == 1 ? T.R[5] : T.R[8]);
+    const double x0 = st[1] * c2 - st[2] * c1, x1 = st[2] * c0 - st[0] * c2,
+                 x2 = st[0] * c1 - st[1] * c0;
+    const double g = i < 3 ? (c0 * s[0] + c1 * s[1] + c2 * s[2]) + (x0 * s[3] + x1 * s[4] + x2 * s[5])
+                           : c0 * s[3] + c1 * s[4] + c2 * s[5];
+    s[6 + i] = -g;
+  }
+  __syncthreads();
+  if (i < (binary ? 12 : 6)) {
+    const int h = i < 6 ? 0 : 6, c = i - h;
+    const double* Jh = h == 0 ? J.Js : J.Jt;
+    double x = s[i];
+    if (J.use) {
+      x = 0.0;
+      for (int r = 0; r < 6; ++r) x += Jh[6 * r + c] * s[h + r];
     }
-    for (int h = 0; h < (binary ? 2 : 1); ++h) {
-      const double* Jh = h == 0 ? J.Js : J.Jt;
-      for (int c = 0; c < 6; ++c) {
-        double x = g[6 * h + c];
-        if (J.use) {
-          x = 0.0;
-          for (int r = 0; r < 6; ++r) x += Jh[6 * r + c] * g[6 * h + r];
-        }
-        grad_xi[6 * h + c] = x;
-      }
-    }
+    grad_xi[i] = x;
   }
 }
 

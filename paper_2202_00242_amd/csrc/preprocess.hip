@@ -785,7 +785,7 @@ vgicp_status downsample(const float* xyz, const float* t, int64_t n, double res,
   ar.need<int>(kRunTiles);
   ar.need<int>(2);
   hipError_t e;
-  if ((e = ar.get(s))) return hip_fail(e, "pool allocation (downsample)");
+  if ((e = ar.get(s))) return hip_fail(e, "device block (downsample)");
   int* kc = ar.take<int>(3 * N);
   int* bounds = ar.take<int>(8);
   SortBuffers sb;
@@ -886,7 +886,7 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   ar.need<int>(N);
   ar.need<int>(N);
   ar.need<SortedPoint>(N);
-  if ((e = ar.get(s))) return hip_fail(e, "pool allocation (knn)");
+  if ((e = ar.get(s))) return hip_fail(e, "device block (knn)");
   int* bounds = ar.take<int>(8);
   SortBuffers sb;
   sb.hist = ar.take<int>(words);
@@ -956,7 +956,7 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   Arena at_ar;
   Scratch sc;
   at_ar.need<CellSlot>(slots_total);
-  if ((e = at_ar.get(s))) return hip_fail(e, "pool allocation (knn)");
+  if ((e = at_ar.get(s))) return hip_fail(e, "device block (knn)");
   CellSlot* slots = at_ar.take<CellSlot>(slots_total);
   for (int L = 0; L < levels; ++L) {
     tab.slots[L] = slots + at[L];

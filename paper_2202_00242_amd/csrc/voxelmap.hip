@@ -789,7 +789,7 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
   a0.need<SpatialSeg>((size_t)S);
   a0.need<float>((size_t)S * kBoxBlocks * 8);
   a0.need<int>((size_t)S);
-  if ((e = a0.get(s))) return hip_fail(e, "pool allocation (cloud order)");
+  if ((e = a0.get(s))) return hip_fail(e, "device block (cloud order)");
   SpatialSeg* d_segs = a0.take<SpatialSeg>((size_t)S);
   float* part = a0.take<float>((size_t)S * kBoxBlocks * 8);
   int* tickets = a0.take<int>((size_t)S);
@@ -846,7 +846,7 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
     ar.need<int>((size_t)pts);
     ar.need<int>(words);
     ar.need<SortSeg>((size_t)m);
-    if ((e = ar.get(s))) return hip_fail(e, "pool allocation (cloud order)");
+    if ((e = ar.get(s))) return hip_fail(e, "device block (cloud order)");
     SortBuffers sb;
     sb.k = ar.take<unsigned long long>((size_t)pts);
     sb.kt = ar.take<unsigned long long>((size_t)pts);
@@ -1004,7 +1004,7 @@ vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, doubl
   own.need<VoxelData>(use_grid ? V1 : 0);
   own.need<int>(use_grid ? V1 : 0);
   own.need<char>(slot_bytes);
-  if ((e = own.get(s, true)) != hipSuccess) return cleanup(fail(VGICP_E_OOM, "voxel map arrays"));
+  if ((e = own.get(s)) != hipSuccess) return cleanup(fail(VGICP_E_OOM, "voxel map arrays"));
   m->keys = own.take<int64_t>(V1);
   m->mean = own.take<double>(3 * V1);
   m->cov = own.take<double>(6 * V1);
@@ -1014,8 +1014,7 @@ vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, doubl
   VoxelData* voxb = own.take<VoxelData>(use_grid ? V1 : 0);
   int* rec_id = own.take<int>(use_grid ? V1 : 0);
   char* slots = own.take<char>(slot_bytes);
-  m->arena = own.base;
-  own.base = nullptr;  // the map's now
+  m->arena = own.keep(&m->arena_bytes);
   const long long* keys = reinterpret_cast<const long long*>(m->keys);
   const unsigned vb = (unsigned)((V1 + kBlock - 1) / kBlock);
   if (use_grid) {
@@ -1060,7 +1059,7 @@ void destroy_voxelmap(vgicp_voxelmap m) {
   (void)hipGetDevice(&cur);
   if (cur != m->device) (void)hipSetDevice(m->device);
   (void)hipDeviceSynchronize();
-  if (m->arena) (void)hipFreeAsync(m->arena, nullptr);
+  if (m->arena) block_give(m->arena, m->arena_bytes, m->device);
   if (cur != m->device) (void)hipSetDevice(cur);
   delete m;
 }

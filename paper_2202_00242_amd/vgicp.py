@@ -68,6 +68,11 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "vgicp_linearize": [P, P, P, I64, P, P, I32, S, P, P, P, P, P, P],
         "vgicp_linearize_noalloc": [P, P, P, I64, P, P, I32, S, P, P, P, P, P, P],
         "vgicp_evaluate": [P, P, P, I64, P, P, S, P, P, P, P],
+        "vgicp_workspace_size": [I64, P],
+        "vgicp_linearize_workspace": [P, P, P, I64, P, P, I32, S, P, P, P, P, P, P, I64, P],
+        "vgicp_evaluate_workspace": [P, P, P, I64, P, P, S, P, P, P, P, I64, P],
+        "vgicp_backward_tangent_workspace": [P, P, P, I64, P, P, P, P, I32, P, P, S, P, P, P, I64,
+                                             P],
         "vgicp_backward": [P, P, P, I64, P, P, I32, P, P, S, P, P, P],
         "vgicp_backward_tangent": [P, P, P, I64, P, P, P, P, I32, P, P, S, P, P, P],
         "vgicp_batch_create": [P, I32, P, I32, P, I32, I32, P],
@@ -118,19 +123,19 @@ def _check(st: int, what: str):
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the raw handle, without building a Stream object per call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if isinstance(stream, torch.cuda.Stream) else int(stream)
 
 
 def _dev(t: torch.Tensor, dtype, shape=None, name="tensor"):
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     return t
 
@@ -145,6 +150,9 @@ def _cloud(xyz: torch.Tensor, cov: torch.Tensor):
 
 
 def _pose(T) -> np.ndarray:
+    if (type(T) is np.ndarray and T.shape == (12,) and T.dtype == np.float64
+            and T.flags.c_contiguous):
+        return T
     a = T.detach().cpu().numpy() if isinstance(T, torch.Tensor) else np.asarray(T)
     a = np.asarray(a, dtype=np.float64)
     if a.shape == (4, 4):
@@ -153,12 +161,21 @@ def _pose(T) -> np.ndarray:
     return a
 
 
-def _np_ptr(a: np.ndarray):
-    return a.ctypes.data_as(ctypes.c_void_p)
+def _np_ptr(a: np.ndarray) -> int:
+    """Address of an array that the caller keeps alive across the call."""
+    return a.__array_interface__["data"][0]
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
+
+
+def _workspace(n: int, device) -> torch.Tensor:
+    """Partial sums of one single-factor call on the current stream, from torch's allocator: it hands
+    the memory out again to later work of the same stream only."""
+    size = ctypes.c_int64()
+    _check(_lib.vgicp_workspace_size(n, ctypes.byref(size)), "vgicp_workspace_size")
+    return torch.empty(size.value, dtype=torch.uint8, device=device)
 
 
 def version() -> str:
@@ -413,9 +430,14 @@ def _linearize(fn, name, m, xyz, cov, T_target, T_source, binary, precision, wan
                "inliers": torch.empty(1, dtype=torch.int64, device=dev),
                "corr": torch.empty(n, dtype=torch.int32, device=dev) if want_corr else None}
     Tt, Ts = _pose(T_target), _pose(T_source)
-    _check(fn(m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), int(bool(binary)),
-              int(precision), _ptr(out["H"]), _ptr(out["b"]), _ptr(out["err"]),
-              _ptr(out["inliers"]), _ptr(out.get("corr")), _stream(stream)), name)
+    args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), int(bool(binary)),
+            int(precision), _ptr(out["H"]), _ptr(out["b"]), _ptr(out["err"]),
+            _ptr(out["inliers"]), _ptr(out.get("corr"))]
+    if stream is None and fn is _lib.vgicp_linearize:
+        ws = _workspace(n, dev)
+        fn = _lib.vgicp_linearize_workspace
+        args += [_ptr(ws), ws.numel()]
+    _check(fn(*args, _stream(stream)), name)
     return out
 
 
@@ -427,9 +449,14 @@ def vgicp_evaluate(m: VoxelMap, xyz, cov, T_target, T_source, precision: int = V
            "inliers": torch.empty(1, dtype=torch.int64, device=dev),
            "corr": torch.empty(n, dtype=torch.int32, device=dev) if want_corr else None}
     Tt, Ts = _pose(T_target), _pose(T_source)
-    _check(_lib.vgicp_evaluate(m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts),
-                               int(precision), _ptr(out["err"]), _ptr(out["inliers"]),
-                               _ptr(out["corr"]), _stream(stream)), "vgicp_evaluate")
+    fn = _lib.vgicp_evaluate
+    args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), int(precision),
+            _ptr(out["err"]), _ptr(out["inliers"]), _ptr(out["corr"])]
+    if stream is None:
+        ws = _workspace(n, dev)
+        fn = _lib.vgicp_evaluate_workspace
+        args += [_ptr(ws), ws.numel()]
+    _check(fn(*args, _stream(stream)), "vgicp_evaluate")
     return out
 
 
@@ -444,6 +471,13 @@ def vgicp_backward(m: VoxelMap, xyz, cov, T_target, T_source, binary: bool, corr
     gxi = torch.empty(12 if binary else 6, dtype=torch.float64, device=dev)
     gp = torch.empty((3, n), dtype=torch.float32, device=dev) if want_points else None
     Tt, Ts = _pose(T_target), _pose(T_source)
+    if stream is None:  # at xi = 0, with torch's workspace
+        ws = _workspace(n, dev)
+        _check(_lib.vgicp_backward_tangent_workspace(
+            m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), None, None,
+            int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision), _ptr(gxi), _ptr(gp),
+            _ptr(ws), ws.numel(), _stream(None)), "vgicp_backward")
+        return gxi, gp
     _check(_lib.vgicp_backward(m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts),
                                int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision),
                                _ptr(gxi), _ptr(gp), _stream(stream)), "vgicp_backward")
@@ -466,11 +500,15 @@ def vgicp_backward_tangent(m: VoxelMap, xyz, cov, T_target, T_source, xi_target,
     Tt, Ts = _pose(T_target), _pose(T_source)
     xt = None if xi_target is None else np.ascontiguousarray(xi_target, np.float64).reshape(6)
     xs = None if xi_source is None else np.ascontiguousarray(xi_source, np.float64).reshape(6)
-    _check(_lib.vgicp_backward_tangent(m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt),
-                                       _np_ptr(Ts), None if xt is None else _np_ptr(xt),
-                                       None if xs is None else _np_ptr(xs), int(bool(binary)),
-                                       _ptr(corr), _ptr(grad_err), int(precision), _ptr(gxi),
-                                       _ptr(gp), _stream(stream)), "vgicp_backward_tangent")
+    fn = _lib.vgicp_backward_tangent
+    args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts),
+            None if xt is None else _np_ptr(xt), None if xs is None else _np_ptr(xs),
+            int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision), _ptr(gxi), _ptr(gp)]
+    if stream is None:
+        ws = _workspace(n, dev)
+        fn = _lib.vgicp_backward_tangent_workspace
+        args += [_ptr(ws), ws.numel()]
+    _check(fn(*args, _stream(stream)), "vgicp_backward_tangent")
     return gxi, gp
 
 
