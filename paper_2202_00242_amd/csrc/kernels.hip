@@ -341,37 +341,59 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
 template <int PREC>
 using RealOf = typename std::conditional<PREC == kMathFp64, double, float>::type;
 
-// Full per-point work of one inlier (its voxel is known): fused covariance, inverse,
-// residual and target-frame Gauss-Newton terms.
-template <int PREC, bool LIN, bool AOS, class Acc>
-__device__ inline void inlier_terms(const MapView& m, const RelPose& T,
-                                    const float* __restrict__ cov, int n, QueueEntry e,
-                                    int point, Acc& acc, int& nin, unsigned& fl) {
-  using Real = RealOf<PREC>;
+// One inlier with what its terms read: position, covariance, voxel record. Loaded a row of lookups
+// ahead of its use (wave_body), so that the lookups cover the loads' latency.
+struct Inlier {
+  float x, y, z;
+  int point;
   float c[6];
+  double mean[3], cov[6];
+};
+
+template <bool AOS>
+__device__ inline void load_inlier(const MapView& m, const float* __restrict__ cov, int n,
+                                   const Queue& qe, int i, Inlier& e) {
+  const QueueEntry q = qe.e[i];
+  e.x = q.x;
+  e.y = q.y;
+  e.z = q.z;
+  e.point = qe.point[i];
   if constexpr (AOS) {  // interleaved [n][6] (24 bytes): three 8-byte loads
-    const float2* c2 = gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)point;
+    const gptr<const float2> c2 =
+        gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)e.point;
     const float2 c01 = c2[0], c23 = c2[1], c45 = c2[2];
-    c[0] = c01.x, c[1] = c01.y, c[2] = c23.x, c[3] = c23.y, c[4] = c45.x, c[5] = c45.y;
+    e.c[0] = c01.x, e.c[1] = c01.y, e.c[2] = c23.x, e.c[3] = c23.y, e.c[4] = c45.x, e.c[5] = c45.y;
   } else {  // the caller's planes [6][n]
 #pragma unroll
-    for (int a = 0; a < 6; ++a) c[a] = gbl(cov + (size_t)a * n)[(unsigned)point];
+    for (int a = 0; a < 6; ++a) e.c[a] = gbl(cov + (size_t)a * n)[(unsigned)e.point];
   }
-  const VoxelData vd = gbl(m.rec)[(unsigned)e.rec];
+  const gptr<const VoxelData> v = gbl(m.rec) + (unsigned)q.rec;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) e.mean[a] = v->mean[a];
+#pragma unroll
+  for (int a = 0; a < 6; ++a) e.cov[a] = v->cov[a];
+}
+
+// Full per-point work of one inlier (its voxel is known): fused covariance, inverse,
+// residual and target-frame Gauss-Newton terms.
+template <int PREC, bool LIN, class Acc>
+__device__ inline void inlier_terms(const RelPose& T, const Inlier& e, Acc& acc, int& nin,
+                                    unsigned& fl) {
+  using Real = RealOf<PREC>;
   Real qq[3], d[3];
   if constexpr (PREC == kNaiveWorld) {
     naive_point(T, e.x, e.y, e.z, qq);
-    for (int a = 0; a < 3; ++a) d[a] = (float)vd.mean[a] - qq[a];
+    for (int a = 0; a < 3; ++a) d[a] = (float)e.mean[a] - qq[a];
   } else {
     double q[3];
     transform_exact(T.R, T.t, e.x, e.y, e.z, q);
     for (int a = 0; a < 3; ++a) {
       qq[a] = (Real)q[a];
-      d[a] = (Real)(vd.mean[a] - q[a]);
+      d[a] = (Real)(e.mean[a] - q[a]);
     }
   }
   Real o[6];
-  const bool ok = fused_inverse<Real>(T.R, vd.cov, c, o);
+  const bool ok = fused_inverse<Real>(T.R, e.cov, e.c, o);
   fl |= ok ? 0u : (unsigned)kFlagNonFinite;
   add_point_terms<LIN>(qq, d, o, acc);
   nin += ok ? 1 : 0;
@@ -390,23 +412,17 @@ struct GradAcc {
 };
 
 template <int PREC>
-__device__ inline void inlier_grad(const MapView& m, const RelPose& T,
-                                   const float* __restrict__ cov, QueueEntry e, int point,
-                                   GradAcc& acc, int& nin, unsigned& fl,
-                                   float* __restrict__ gz) {
+__device__ inline void inlier_grad(const RelPose& T, const Inlier& e, GradAcc& acc, int& nin,
+                                   unsigned& fl, float* __restrict__ gz) {
   using Real = RealOf<PREC>;
-  float c[6];
-  const float2* c2 = gbl(reinterpret_cast<const float2*>(cov)) + 3 * (size_t)(unsigned)point;
-  const float2 c01 = c2[0], c23 = c2[1], c45 = c2[2];
-  c[0] = c01.x, c[1] = c01.y, c[2] = c23.x, c[3] = c23.y, c[4] = c45.x, c[5] = c45.y;
-  const VoxelData vd = gbl(m.rec)[(unsigned)e.rec];
+  const float* c = e.c;
   double q[3];
   transform_exact(T.R, T.t, e.x, e.y, e.z, q);
   Real d[3];
-  for (int a = 0; a < 3; ++a) d[a] = (Real)(vd.mean[a] - q[a]);
-  const gptr<float> g = gblw(gz) + 3 * (size_t)(unsigned)point;
+  for (int a = 0; a < 3; ++a) d[a] = (Real)(e.mean[a] - q[a]);
+  const gptr<float> g = gblw(gz) + 3 * (size_t)(unsigned)e.point;
   Real o[6];
-  if (!fused_inverse<Real>(T.R, vd.cov, c, o)) {
+  if (!fused_inverse<Real>(T.R, e.cov, c, o)) {
     fl |= kFlagNonFinite;
     g[0] = 0.0f;
     g[1] = 0.0f;
@@ -437,15 +453,14 @@ __device__ inline void inlier_grad(const MapView& m, const RelPose& T,
   ++nin;
 }
 
-// Phase B of one queued inlier: linearization / evaluation terms, or gradient terms.
-template <int PREC, bool LIN, bool AOS, bool GRAD, class Acc>
-__device__ inline void phase_b(const MapView& m, const RelPose& T, const float* __restrict__ cov,
-                               int n, const Queue& qe, int i, Acc& acc, int& nin, unsigned& fl,
-                               float* __restrict__ gz) {
+// Phase B of one inlier: linearization / evaluation terms, or gradient terms.
+template <int PREC, bool LIN, bool GRAD, class Acc>
+__device__ inline void phase_b(const RelPose& T, const Inlier& e, Acc& acc, int& nin,
+                               unsigned& fl, float* __restrict__ gz) {
   if constexpr (GRAD)
-    inlier_grad<PREC>(m, T, cov, qe.e[i], qe.point[i], acc, nin, fl, gz);
+    inlier_grad<PREC>(T, e, acc, nin, fl, gz);
   else
-    inlier_terms<PREC, LIN, AOS>(m, T, cov, n, qe.e[i], qe.point[i], acc, nin, fl);
+    inlier_terms<PREC, LIN>(T, e, acc, nin, fl);
 }
 
 // ------------------------------------------------------------------ one tile
@@ -478,6 +493,8 @@ __device__ inline void wave_body(const MapView& m, const RelPose& T,
   const int lane = threadIdx.x & 63;
   const Planes P = make_planes(xyz, n);
   int cnt = 0, h = 0;
+  Inlier held;  // the last 64 inliers taken from the queue: their terms are formed when the next are
+  bool pending = false;
   // positions double-buffered: the next row is loaded while this one is resolved
   Chunk<U> cur;
   cur.load(P, base, lane);
@@ -496,8 +513,13 @@ __device__ inline void wave_body(const MapView& m, const RelPose& T,
     if (cnt >= 64) {
       wave_sync();
       int head = 0;
-      for (; cnt - head >= 64; head += 64)
-        phase_b<PREC, LIN, AOS, GRAD>(m, T, cov, n, qe, head + lane, acc, nin, fl, gz);
+      for (; cnt - head >= 64; head += 64) {
+        Inlier now;
+        load_inlier<AOS>(m, cov, n, qe, head + lane, now);
+        if (pending) phase_b<PREC, LIN, GRAD>(T, held, acc, nin, fl, gz);
+        held = now;
+        pending = true;
+      }
       const int rem = cnt - head;
       // move the tail to the front (through registers: every lane reads before any writes)
       const int src = min(head + lane, cnt - 1);
@@ -516,7 +538,10 @@ __device__ inline void wave_body(const MapView& m, const RelPose& T,
     }
   }
   wave_sync();
-  if (lane < cnt) phase_b<PREC, LIN, AOS, GRAD>(m, T, cov, n, qe, lane, acc, nin, fl, gz);
+  Inlier last;
+  if (lane < cnt) load_inlier<AOS>(m, cov, n, qe, lane, last);
+  if (pending) phase_b<PREC, LIN, GRAD>(T, held, acc, nin, fl, gz);
+  if (lane < cnt) phase_b<PREC, LIN, GRAD>(T, last, acc, nin, fl, gz);
   wave_sync();
 }
 
