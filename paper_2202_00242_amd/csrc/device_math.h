@@ -32,6 +32,15 @@ __device__ __forceinline__ gptr<const T> gbl(const T* p) {
   return (gptr<const T>)p;
 }
 
+// A wave-uniform structure that the kernel only reads, for scalar loads at this very place: the
+// compiler cannot move them ahead of the branch or loop they are in.
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* here(const T* p) {
+  auto q = (const __attribute__((address_space(4))) T*)p;
+  asm("" : "+s"(q));
+  return q;
+}
+
 template <class T>
 __device__ __forceinline__ gptr<T> gblw(T* p) {
   return (gptr<T>)p;

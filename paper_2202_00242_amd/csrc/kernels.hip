@@ -192,18 +192,39 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
     unsigned dx, dy, dz;  // voxel relative to the map's box
     bool inbox;
     auto exact = [&]() {
-      int k[3];
+      int k[3], lo[3];
       bool finite;
-      if constexpr (FAST) {  // rare: no code of its own per key arithmetic
-        finite = m.pow2 ? point_key<PREC, false>(m, T, x[u], y[u], z[u], k)
-                        : point_key<PREC, true>(m, T, x[u], y[u], z[u], k);
+      if constexpr (FAST) {
+        // rare: no code of its own per key arithmetic, and no scalar registers outside this branch
+        // (read ahead of the loop, its 48 words of pose and map made the loop keep its own scalars
+        // in vector lanes: 22 of the 70 VALU instructions of a row; overlap rates of 160 submaps 1,481 us
+        // with that, 875 without)
+        const auto Tg = here(&T);
+        const auto mg = here(&m);
+        const bool pow2 = mg->pow2 != 0;  // point_key's two key arithmetics
+        double R[9], t[3], q[3];
+#pragma unroll
+        for (int a = 0; a < 9; ++a) R[a] = pow2 ? Tg->Rk[a] : Tg->R[a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) t[a] = pow2 ? Tg->tk[a] : Tg->t[a];
+        transform_exact(R, t, x[u], y[u], z[u], q);
+        finite = isfinite(q[0] + q[1] + q[2]);
+        if (!pow2) {
+          const double res = mg->res;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) q[a] /= res;
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) k[a] = floor_sat_i32(q[a]);
+        lo[0] = mg->lo[0], lo[1] = mg->lo[1], lo[2] = mg->lo[2];
       } else {
         finite = point_key<PREC, DIV>(m, T, x[u], y[u], z[u], k);
+        lo[0] = m.lo[0], lo[1] = m.lo[1], lo[2] = m.lo[2];
       }
       if (valid && !finite) fl |= kFlagNonFinite;
-      dx = finite ? (unsigned)k[0] - (unsigned)m.lo[0] : ~0u;
-      dy = (unsigned)k[1] - (unsigned)m.lo[1];
-      dz = (unsigned)k[2] - (unsigned)m.lo[2];
+      dx = finite ? (unsigned)k[0] - (unsigned)lo[0] : ~0u;
+      dy = (unsigned)k[1] - (unsigned)lo[1];
+      dz = (unsigned)k[2] - (unsigned)lo[2];
     };
     if constexpr (FAST) {
       float s[3], f[3];
@@ -1046,6 +1067,24 @@ batch_kernel(const FactorView* __restrict__ F, const RelPose* __restrict__ rel,
   if (fl) atomicOr(flags, fl);
 }
 
+// Points [lo, end) of a source that have a voxel in the map (a loop per lookup structure: one loop
+// around all three holds the scalars of each).
+template <int LAYOUT>
+__device__ inline int count_points(const MapView& m, const RelPose& T, const Planes& P, int lo,
+                                   int end, int lane, unsigned& fl) {
+  constexpr int U = 2;
+  const Queue none{nullptr, nullptr};
+  int cnt = 0;
+  Chunk<U> cur, nxt;
+  cur.load(P, lo, lane);
+  for (int base = lo; base < end; base += 64 * U) {
+    resolve<kCountOnly, false, LAYOUT, U, true>(m, T, cur, nxt, P, base + 64 * U, base, end, lane,
+                                                none, cnt, nullptr, fl);
+    cur = nxt;
+  }
+  return cnt;
+}
+
 // Overlap counts: every point's voxel, nothing else. The counts are whole numbers, so the cut is
 // free: a wave takes a tile's share of 1 / waves in one piece, the items are dealt to the waves in
 // turn (their cost is even: no counter is shared), 64 items' skip flags are read at once, and the
@@ -1054,7 +1093,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void b
     const FactorView* __restrict__ F, const RelPose* __restrict__ rel,
     const WorkItem* __restrict__ items, const int* __restrict__ seg, BatchCut cut,
     int* __restrict__ counts, unsigned* flags) {
-  constexpr int U = 2;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int xcd = blockIdx.x & (kNumXcd - 1);
@@ -1078,24 +1116,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void b
       const Planes P = make_planes(f.xyz, (int)f.n);
       const int lo = wt * cut.tile + w * share;
       const int end = (int)min((long long)lo + share, f.n);
-      int cnt = 0;
-      Chunk<U> cur;
-      cur.load(P, lo, lane);
-      for (int base = lo; base < end; base += 64 * U) {
-        Chunk<U> nxt;
-        const Queue none{nullptr, nullptr};
-#define VGICP_COUNT(LAYOUT)                                                                     \
-  resolve<kCountOnly, false, LAYOUT, U, true>(m, T, cur, nxt, P, base + 64 * U, base, end, lane, \
-                                              none, cnt, nullptr, fl)
-        if (m.bricks)
-          VGICP_COUNT(kLayoutGrid);
-        else if (m.slots32)
-          VGICP_COUNT(kLayoutHash32);
-        else
-          VGICP_COUNT(kLayoutHash64);
-#undef VGICP_COUNT
-        cur = nxt;
-      }
+      const int cnt = m.bricks    ? count_points<kLayoutGrid>(m, T, P, lo, end, lane, fl)
+                      : m.slots32 ? count_points<kLayoutHash32>(m, T, P, lo, end, lane, fl)
+                                  : count_points<kLayoutHash64>(m, T, P, lo, end, lane, fl);
       if (lane == 0) counts[(size_t)(f.tile_base + wt) * cut.waves + w] = cnt;
     }
   }
