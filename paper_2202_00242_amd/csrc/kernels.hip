@@ -237,7 +237,7 @@ __device__ inline void resolve(const MapView& m, const RelPose& T, const Chunk<U
       dx = (unsigned)floor_i32_f32(s[0]);
       dy = (unsigned)floor_i32_f32(s[1]);
       dz = (unsigned)floor_i32_f32(s[2]);
-      // a NaN coordinate fails the comparison (the box of such a cloud is infinite: thr < 0)
+      // (a cloud with a coordinate that is not finite has an infinite box: thr < 0, never sure)
       const bool sure = fmaxf(fmaxf(f[0], f[1]), f[2]) <= T.thr;
       if (__ballot(!sure) != 0ull) {
         if (!sure) exact();
