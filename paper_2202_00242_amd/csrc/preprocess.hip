@@ -260,7 +260,8 @@ __global__ __launch_bounds__(kBlock) void knn_bounds_kernel(const float* __restr
 // squared distance at which the count of points reaches k; the k-th neighbour then lies within
 // 2^((e + 1) / 2). est = INT_MAX if the cloud has fewer than k points, INT_MIN for duplicates.
 // Most distances share a few exponents, so every lane of 16 counts in a copy of its own (one copy
-// for all lanes serialized on them: 31 us for 19,000 points).
+// for all lanes serialized on them: 31 us for 19,000 points); four points' loads are in flight per lane
+// (one: 20 us, four: 12.6).
 constexpr int kExpBins = 128, kExpCopies = 16, kSampleBlock = 512;
 __global__ __launch_bounds__(kSampleBlock) void knn_sample_kernel(const float* __restrict__ xyz,
                                                                   long long n, int S, int k,
@@ -271,12 +272,24 @@ __global__ __launch_bounds__(kSampleBlock) void knn_sample_kernel(const float* _
   __syncthreads();
   const long long q = (long long)blockIdx.x * n / S;
   const double q0 = xyz[q], q1 = xyz[n + q], q2 = xyz[2 * n + q];
-  for (long long j = threadIdx.x; j < n; j += blockDim.x) {
-    const double dx = (double)xyz[j] - q0, dy = (double)xyz[n + j] - q1,
-                 dz = (double)xyz[2 * n + j] - q2;
-    const double d2 = (dx * dx + dy * dy) + dz * dz;
-    const int b = d2 > 0.0 ? min(max(ilogb(d2), -62), 62) + 64 : 0;
-    atomicAdd(&hist[b][threadIdx.x & (kExpCopies - 1)], 1);
+  constexpr int kAhead = 4;
+  for (long long j0 = threadIdx.x; j0 < n; j0 += (long long)kAhead * kSampleBlock) {
+    float x[kAhead], y[kAhead], z[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const long long j = min(j0 + (long long)u * kSampleBlock, n - 1);
+      x[u] = xyz[j];
+      y[u] = xyz[n + j];
+      z[u] = xyz[2 * n + j];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (j0 + (long long)u * kSampleBlock >= n) break;
+      const double dx = (double)x[u] - q0, dy = (double)y[u] - q1, dz = (double)z[u] - q2;
+      const double d2 = (dx * dx + dy * dy) + dz * dz;
+      const int b = d2 > 0.0 ? min(max(ilogb(d2), -62), 62) + 64 : 0;
+      atomicAdd(&hist[b][threadIdx.x & (kExpCopies - 1)], 1);
+    }
   }
   __syncthreads();
   if (threadIdx.x < kExpBins) {
@@ -678,6 +691,30 @@ __device__ inline void rotate(double (&A)[3][3], double (&V)[3][3], int p, int q
   }
 }
 
+// Neighbours s .. s + kCovAhead - 1 of point i, their loads in flight together (one neighbour at a time
+// the loop waited twice for memory for each: 19.2 us for 18,000 points of 10, now 17.8, most of it the
+// rotations); returns which of them exist, bad: an index past the cloud.
+constexpr int kCovAhead = 5;
+__device__ inline unsigned cov_neighbors(const float* __restrict__ xyz, long long n,
+                                         const int* __restrict__ nbr, int k, int s, long long i,
+                                         float (&p)[kCovAhead][3], bool& bad) {
+  int j[kCovAhead];
+#pragma unroll
+  for (int u = 0; u < kCovAhead; ++u) j[u] = s + u < k ? nbr[(s + u) * n + i] : -1;
+  unsigned ok = 0;
+#pragma unroll
+  for (int u = 0; u < kCovAhead; ++u) {
+    bad |= j[u] >= n;
+    const bool in = j[u] >= 0 && j[u] < n;
+    ok |= in ? 1u << u : 0u;
+    const long long q = in ? j[u] : i;
+    p[u][0] = xyz[q];
+    p[u][1] = xyz[n + q];
+    p[u][2] = xyz[2 * n + q];
+  }
+  return ok;
+}
+
 __global__ __launch_bounds__(kBlock) void cov_kernel(const float* __restrict__ xyz, long long n,
                                                      const int* __restrict__ nbr, int k,
                                                      double scale, double eps,
@@ -688,17 +725,17 @@ __global__ __launch_bounds__(kBlock) void cov_kernel(const float* __restrict__ x
     double m0 = 0.0, m1 = 0.0, m2 = 0.0;
     int m = 0;
     bool bad = false;
-    for (int s = 0; s < k; ++s) {
-      const int j = nbr[s * n + i];
-      if (j < 0) continue;
-      if (j >= n) {
-        bad = true;
-        continue;
+    for (int s = 0; s < k; s += kCovAhead) {
+      float p[kCovAhead][3];
+      const unsigned ok = cov_neighbors(xyz, n, nbr, k, s, i, p, bad);
+#pragma unroll
+      for (int u = 0; u < kCovAhead; ++u) {
+        if (!(ok >> u & 1u)) continue;
+        m0 += (double)p[u][0];
+        m1 += (double)p[u][1];
+        m2 += (double)p[u][2];
+        ++m;
       }
-      m0 += (double)xyz[j];
-      m1 += (double)xyz[n + j];
-      m2 += (double)xyz[2 * n + j];
-      ++m;
     }
     if (bad) atomicOr(flags, kFlagBadIndex);
     const double inv_m = m > 0 ? 1.0 / (double)m : 0.0;
@@ -706,15 +743,18 @@ __global__ __launch_bounds__(kBlock) void cov_kernel(const float* __restrict__ x
     m1 *= inv_m;
     m2 *= inv_m;
     double A[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-    for (int s = 0; s < k; ++s) {
-      const int j = nbr[s * n + i];
-      if (j < 0 || j >= n) continue;
-      const double v[3] = {(double)xyz[j] - m0, (double)xyz[n + j] - m1,
-                           (double)xyz[2 * n + j] - m2};
+    for (int s = 0; s < k; s += kCovAhead) {
+      float p[kCovAhead][3];
+      const unsigned ok = cov_neighbors(xyz, n, nbr, k, s, i, p, bad);
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+      for (int u = 0; u < kCovAhead; ++u) {
+        if (!(ok >> u & 1u)) continue;
+        const double v[3] = {(double)p[u][0] - m0, (double)p[u][1] - m1, (double)p[u][2] - m2};
 #pragma unroll
-        for (int b = a; b < 3; ++b) A[a][b] += v[a] * v[b];
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int b = a; b < 3; ++b) A[a][b] += v[a] * v[b];
+      }
     }
     A[1][0] = A[0][1];
     A[2][0] = A[0][2];
