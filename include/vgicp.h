@@ -121,9 +121,10 @@ typedef struct {
 
 /* Launch schedule of the batched kernel (chosen by vgicp_batch_autotune or set by hand).
  * block: threads per block (256 or 512); tile: source points per work item (a multiple of
- * block, at most 32 * block); blocks_per_cu: blocks per compute unit in the persistent grid;
- * lookahead: source points each lane resolves together in the lookup phase (2, 4 or 8: more
- * memory requests in flight per wave, more registers per wave). */
+ * block, at most 32 * block), shared by block / 64 waves; lookahead (2, 4 or 8): a wave takes its
+ * share of a tile in chunks of 64 * lookahead points. These three fix the order of a factor's sums.
+ * blocks_per_cu: blocks of `block` threads per compute unit, an upper bound of the persistent grid
+ * (never more than stay resident). */
 typedef struct {
   int32_t block;
   int32_t tile;
@@ -146,7 +147,7 @@ typedef struct {
  *   Output order: ascending cell in (x, y, z) lexicographic order, then creation order within
  *   the cell. xyz_out is written as [3][m] in its first 3 m floats (capacity >= m points);
  *   t_out (may be NULL) receives the m voxel timestamps when t is given. *n_out = m.
- * Synchronises the stream (twice: after the range checks and to learn m). Errors:
+ * Synchronises the stream (after the range checks and to learn m). Errors:
  * E_INVALID_ARG, E_NONFINITE (NaN/Inf position or timestamp), E_KEY_RANGE (|cell| >= 2^20),
  * E_CAPACITY (m > capacity: *n_out holds m, nothing is written; or n >= 2^30). */
 VGICP_API vgicp_status vgicp_downsample(const float* xyz, const float* t, int64_t n,
@@ -255,8 +256,8 @@ VGICP_API vgicp_status vgicp_imu_linearize_bias(
 /* Builds the voxel map of one target cloud (Sec. III-A: per voxel, the arithmetic mean of
  * the member points' means and of their covariances, summed in FP64 in increasing point
  * index; no minimum count). xyz/cov: device, [3][n] / [6][n], read during the call only;
- * n >= 0; resolution > 0 and finite. Runs on `stream` and synchronises it once (the voxel
- * count sizes the table). On success *out owns the map: release it with
+ * n >= 0; resolution > 0 and finite. Runs on `stream` and synchronises it (the
+ * box, then the voxel count size the table; the map is ready on return). On success *out owns the map: release it with
  * vgicp_destroy_voxelmap. Errors: E_INVALID_ARG, E_NONFINITE (NaN/Inf point),
  * E_KEY_RANGE, E_OOM, E_HIP; *out is then NULL. */
 VGICP_API vgicp_status vgicp_build_voxelmap(const float* xyz, const float* cov, int64_t n,
@@ -397,7 +398,7 @@ VGICP_API vgicp_status vgicp_backward_tangent_workspace(
  * copied during the call; the maps and the cloud memory they name must outlive the batch.
  * n_poses is the length of the pose array later passed to vgicp_batch_linearize. The batch
  * splits every factor's source into tiles and orders the work so that factors sharing a
- * target run together on one XCD (its L2 keeps the target's voxel table). At creation the
+ * source cloud run together on one XCD (its L2 keeps the cloud's points). At creation the
  * batch copies every source cloud (36 bytes per point) in a spatial order - the Morton order of
  * its cells at the finest resolution of the maps it is matched against - with interleaved
  * covariances: neighbouring points then read neighbouring bricks and voxel records, and an

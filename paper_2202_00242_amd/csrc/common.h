@@ -54,7 +54,7 @@ static_assert(sizeof(VoxelData) == 80, "VoxelData is five 16-byte words");
 // What a kernel needs to know about a voxel map. Voxel coordinates k are first tested
 // against the map's bounding box [lo, lo + ext). Inside it, one of three structures gives the
 // voxel id:
-//  * grid: occupancy bricks over the box (one 16-byte load per point); the lookup gives a
+//  * grid: occupancy bricks over the box (one 8-byte load per point); the lookup gives a
 //      position in the brick-ordered records, rec_id maps it back to the voxel id;
 //  * hash32: an open-addressing table of {rk, id} pairs (8 bytes) keyed by the relative key
 //      rk = ((kx - lo0) << (by + bz)) | ((ky - lo1) << bz) | (kz - lo2)  (rk fits in 31 bits);
