@@ -173,9 +173,7 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 def _workspace(n: int, device) -> torch.Tensor:
     """Partial sums of one single-factor call on the current stream, from torch's allocator: it hands
     the memory out again to later work of the same stream only."""
-    size = ctypes.c_int64()
-    _check(_lib.vgicp_workspace_size(n, ctypes.byref(size)), "vgicp_workspace_size")
-    return torch.empty(size.value, dtype=torch.uint8, device=device)
+    return torch.empty(vgicp_workspace_size(n), dtype=torch.uint8, device=device)
 
 
 def version() -> str:
@@ -400,6 +398,13 @@ def vgicp_voxelmap_export(m: VoxelMap, stream=None):
     return {"keys": keys, "mean": mean, "cov": cov, "count": count}
 
 
+def vgicp_workspace_size(n: int) -> int:
+    """Bytes of the workspace that a *_workspace call on a cloud of n points needs."""
+    size = ctypes.c_int64()
+    _check(_lib.vgicp_workspace_size(int(n), ctypes.byref(size)), "vgicp_workspace_size")
+    return size.value
+
+
 def vgicp_linearize(m: VoxelMap, xyz, cov, T_target, T_source, binary: bool,
                     precision: int = VGICP_ACC_FP64, want_corr: bool = False, stream=None,
                     out=None):
@@ -418,8 +423,16 @@ def vgicp_linearize_noalloc(m: VoxelMap, xyz, cov, T_target, T_source, binary: b
                       T_target, T_source, binary, precision, want_corr, stream, out)
 
 
+def vgicp_linearize_workspace(m: VoxelMap, xyz, cov, T_target, T_source, binary: bool, workspace,
+                              precision: int = VGICP_ACC_FP64, want_corr: bool = False,
+                              stream=None, out=None):
+    """vgicp_linearize with the caller's device workspace (a uint8 tensor)."""
+    return _linearize(_lib.vgicp_linearize, "vgicp_linearize_workspace", m, xyz, cov, T_target,
+                      T_source, binary, precision, want_corr, stream, out, workspace)
+
+
 def _linearize(fn, name, m, xyz, cov, T_target, T_source, binary, precision, want_corr, stream,
-               out):
+               out, workspace=None):
     n = _cloud(xyz, cov)
     d = 12 if binary else 6
     dev = xyz.device
@@ -433,8 +446,9 @@ def _linearize(fn, name, m, xyz, cov, T_target, T_source, binary, precision, wan
     args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), int(bool(binary)),
             int(precision), _ptr(out["H"]), _ptr(out["b"]), _ptr(out["err"]),
             _ptr(out["inliers"]), _ptr(out.get("corr"))]
-    if stream is None and fn is _lib.vgicp_linearize:
-        ws = _workspace(n, dev)
+    if workspace is not None or (stream is None and fn is _lib.vgicp_linearize):
+        ws = _workspace(n, dev) if workspace is None else _dev(
+            workspace, torch.uint8, (workspace.numel(),), "workspace")
         fn = _lib.vgicp_linearize_workspace
         args += [_ptr(ws), ws.numel()]
     _check(fn(*args, _stream(stream)), name)
@@ -443,6 +457,17 @@ def _linearize(fn, name, m, xyz, cov, T_target, T_source, binary, precision, wan
 
 def vgicp_evaluate(m: VoxelMap, xyz, cov, T_target, T_source, precision: int = VGICP_ACC_FP64,
                    want_corr: bool = False, stream=None):
+    return _evaluate(m, xyz, cov, T_target, T_source, precision, want_corr, stream)
+
+
+def vgicp_evaluate_workspace(m: VoxelMap, xyz, cov, T_target, T_source, workspace,
+                             precision: int = VGICP_ACC_FP64, want_corr: bool = False,
+                             stream=None):
+    """vgicp_evaluate with the caller's device workspace (a uint8 tensor)."""
+    return _evaluate(m, xyz, cov, T_target, T_source, precision, want_corr, stream, workspace)
+
+
+def _evaluate(m, xyz, cov, T_target, T_source, precision, want_corr, stream, workspace=None):
     n = _cloud(xyz, cov)
     dev = xyz.device
     out = {"err": torch.empty(1, dtype=torch.float64, device=dev),
@@ -452,8 +477,9 @@ def vgicp_evaluate(m: VoxelMap, xyz, cov, T_target, T_source, precision: int = V
     fn = _lib.vgicp_evaluate
     args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), int(precision),
             _ptr(out["err"]), _ptr(out["inliers"]), _ptr(out["corr"])]
-    if stream is None:
-        ws = _workspace(n, dev)
+    if workspace is not None or stream is None:
+        ws = _workspace(n, dev) if workspace is None else _dev(
+            workspace, torch.uint8, (workspace.numel(),), "workspace")
         fn = _lib.vgicp_evaluate_workspace
         args += [_ptr(ws), ws.numel()]
     _check(fn(*args, _stream(stream)), "vgicp_evaluate")
@@ -464,6 +490,9 @@ def vgicp_backward(m: VoxelMap, xyz, cov, T_target, T_source, binary: bool, corr
                    grad_err: torch.Tensor, precision: int = VGICP_ACC_FP64,
                    want_points: bool = True, stream=None):
     """Returns (grad_xi (6|12,) f64, grad_xyz (3, n) f32 or None) as device tensors."""
+    if stream is None:  # xi = 0, with torch's workspace
+        return _backward_tangent(m, xyz, cov, T_target, T_source, None, None, binary, corr,
+                                 grad_err, precision, want_points, None)
     n = _cloud(xyz, cov)
     _dev(corr, torch.int32, (n,), "corr")
     _dev(grad_err, torch.float64, (1,), "grad_err")
@@ -471,13 +500,6 @@ def vgicp_backward(m: VoxelMap, xyz, cov, T_target, T_source, binary: bool, corr
     gxi = torch.empty(12 if binary else 6, dtype=torch.float64, device=dev)
     gp = torch.empty((3, n), dtype=torch.float32, device=dev) if want_points else None
     Tt, Ts = _pose(T_target), _pose(T_source)
-    if stream is None:  # at xi = 0, with torch's workspace
-        ws = _workspace(n, dev)
-        _check(_lib.vgicp_backward_tangent_workspace(
-            m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), None, None,
-            int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision), _ptr(gxi), _ptr(gp),
-            _ptr(ws), ws.numel(), _stream(None)), "vgicp_backward")
-        return gxi, gp
     _check(_lib.vgicp_backward(m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts),
                                int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision),
                                _ptr(gxi), _ptr(gp), _stream(stream)), "vgicp_backward")
@@ -491,6 +513,21 @@ def vgicp_backward_tangent(m: VoxelMap, xyz, cov, T_target, T_source, xi_target,
     """vgicp_backward at T Exp(xi), the pose gradient in the tangent coordinates xi.
     xi_target / xi_source: 6 values or None. Returns (grad_xi (6|12,) f64, grad_xyz (3, n) f32
     or None) as device tensors."""
+    return _backward_tangent(m, xyz, cov, T_target, T_source, xi_target, xi_source, binary, corr,
+                             grad_err, precision, want_points, stream)
+
+
+def vgicp_backward_tangent_workspace(m: VoxelMap, xyz, cov, T_target, T_source, xi_target,
+                                     xi_source, binary: bool, corr, grad_err: torch.Tensor,
+                                     workspace, precision: int = VGICP_ACC_FP64,
+                                     want_points: bool = True, stream=None):
+    """vgicp_backward_tangent with the caller's device workspace (a uint8 tensor)."""
+    return _backward_tangent(m, xyz, cov, T_target, T_source, xi_target, xi_source, binary, corr,
+                             grad_err, precision, want_points, stream, workspace)
+
+
+def _backward_tangent(m, xyz, cov, T_target, T_source, xi_target, xi_source, binary, corr,
+                      grad_err, precision, want_points, stream, workspace=None):
     n = _cloud(xyz, cov)
     _dev(corr, torch.int32, (n,), "corr")
     _dev(grad_err, torch.float64, (1,), "grad_err")
@@ -504,8 +541,9 @@ def vgicp_backward_tangent(m: VoxelMap, xyz, cov, T_target, T_source, xi_target,
     args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts),
             None if xt is None else _np_ptr(xt), None if xs is None else _np_ptr(xs),
             int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision), _ptr(gxi), _ptr(gp)]
-    if stream is None:
-        ws = _workspace(n, dev)
+    if workspace is not None or stream is None:
+        ws = _workspace(n, dev) if workspace is None else _dev(
+            workspace, torch.uint8, (workspace.numel(),), "workspace")
         fn = _lib.vgicp_backward_tangent_workspace
         args += [_ptr(ws), ws.numel()]
     _check(fn(*args, _stream(stream)), "vgicp_backward_tangent")

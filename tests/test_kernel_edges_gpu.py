@@ -6,8 +6,6 @@ around a block of 8, caller workspaces.
 Bars: counts, keys, neighbours, filtered points and correspondences are bitwise equal; H, b, e and
 gradients within the parity tests' bounds (tests/gpu_util.py); the same sums from another launch
 shape are bitwise equal."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
@@ -333,9 +331,7 @@ def test_caller_workspaces(V, n):
         sx = x.cpu().numpy()
         ref = oracle.gradient(om, sx, covs(n), Tt, Ts, True, e["corr"].cpu().numpy())["g_xi"]
         assert np.max(np.abs(gxi.cpu().numpy() - ref)) <= 1e-9 * np.linalg.norm(ref)
-    need = ctypes.c_int64()
-    assert V._lib.vgicp_workspace_size(n, ctypes.byref(need)) == 0
-    need = need.value
+    need = V.vgicp_workspace_size(n)
     ws = torch.empty(max(need, 8), dtype=torch.uint8, device="cuda")
     err = torch.full((1,), -7.0, dtype=torch.float64, device="cuda")
     nin = torch.full((1,), -7, dtype=torch.int64, device="cuda")
@@ -354,3 +350,16 @@ def test_caller_workspaces(V, n):
     torch.cuda.synchronize()
     if n:
         assert nin.item() == int(e["inliers"].item())
+    # the binding's forms
+    same(V.vgicp_linearize_workspace(m, x, c, Tt, Ts, True, ws, 3, want_corr=True), a,
+         ("H", "b", "err", "inliers", "corr"))
+    same(V.vgicp_evaluate_workspace(m, x, c, Tt, Ts, ws, 3, want_corr=True), e,
+         ("err", "inliers", "corr"))
+    xi = np.full(6, 0.01)
+    for u, w in zip(V.vgicp_backward_tangent_workspace(m, x, c, Tt, Ts, xi, xi, True, e["corr"], g,
+                                                       ws, 3),
+                    V.vgicp_backward_tangent(m, x, c, Tt, Ts, xi, xi, True, e["corr"], g, 3,
+                                             stream=cs)):
+        assert torch.equal(u, w)
+    with pytest.raises(V.VGICPError):
+        V.vgicp_evaluate_workspace(m, x, c, Tt, Ts, ws[:8], 3)
