@@ -70,7 +70,10 @@ vgicp_status fail(vgicp_status st, const std::string& msg) {
   return st;
 }
 
+// The caller gets the error: the runtime's own note of it is taken away, or the next call's launch check
+// would find it again (one refused allocation failed the call after it too).
 vgicp_status hip_fail(hipError_t e, const char* what) {
+  (void)hipGetLastError();
   std::string m = std::string(what) + ": " + hipGetErrorString(e);
   if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) return fail(VGICP_E_OOM, m);
   return fail(VGICP_E_HIP, m);
@@ -128,6 +131,7 @@ hipError_t block_take(void** p, size_t* bytes) {
   }
   e = hipMalloc(p, b);
   if (e == hipSuccess) return e;
+  (void)hipGetLastError();  // noted for the caller only, see hip_fail
   // out of memory: the idle blocks go first
   std::vector<Block> idle;
   {
@@ -136,8 +140,8 @@ hipError_t block_take(void** p, size_t* bytes) {
   }
   for (const Block& k : idle) (void)hipFree(k.p);
   if (idle.empty()) return e;
-  (void)hipGetLastError();
-  return hipMalloc(p, b);
+  if ((e = hipMalloc(p, b)) != hipSuccess) (void)hipGetLastError();
+  return e;
 }
 
 void block_give(void* p, size_t bytes, int device) {
@@ -179,7 +183,10 @@ HostBlock::HostBlock() {
       return;
     }
   }
-  if (hipHostMalloc(&p, kHostBlockBytes, hipHostMallocPortable) != hipSuccess) p = nullptr;
+  if (hipHostMalloc(&p, kHostBlockBytes, hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    p = nullptr;
+  }
 }
 
 HostBlock::~HostBlock() {

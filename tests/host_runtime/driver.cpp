@@ -1,0 +1,306 @@
+// Host-side tests of libvgicp.so without a GPU: this program defines the HIP runtime functions that the
+// library calls (they take the place of the runtime's, since a program's own symbols come first), with
+// device memory in host memory, kernels that do nothing and refusals on demand. What it checks is the
+// library's host code: who owns which block of memory, on which device, and what is left after a
+// refused allocation. Usage: driver <test>; prints "<test> ok".
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <string>
+#include <vector>
+
+#include "../../include/vgicp.h"
+
+#define CHECK(c)                                                         \
+  do {                                                                   \
+    if (!(c)) {                                                          \
+      std::printf("%s:%d: %s (%s)\n", __FILE__, __LINE__, #c, vgicp_last_error()); \
+      std::exit(1);                                                      \
+    }                                                                    \
+  } while (0)
+
+// ------------------------------------------------------------------ the runtime
+
+namespace {
+
+struct Alloc {
+  size_t bytes;
+  int device;
+};
+struct Launch {  // a launch of batch_kernel
+  char *items, *partials;
+};
+struct Dim3 {
+  uint32_t x, y, z;
+};
+struct Config {
+  Dim3 grid, block;
+  size_t shared;
+  void* stream;
+};
+struct Graph {
+  std::vector<Launch> launches;
+};
+
+constexpr int kOk = 0, kInvalid = 1, kOutOfMemory = 2;
+std::mutex g_mu;
+std::map<char*, Alloc> g_live;                 // device memory
+std::map<char*, size_t> g_pinned;
+std::map<const void*, char*> g_symbols;
+size_t g_refuse_above = ~(size_t)0;            // device allocations of more bytes are refused
+size_t g_largest = 0;                          // largest device allocation so far
+Graph* g_capture = nullptr;
+std::vector<Launch> g_ran;                     // executed launches of batch_kernel
+thread_local int t_device = 0, t_error = kOk;
+thread_local std::vector<Config> t_config;
+
+// Host stub -> device name. The library registers its kernels before this program's globals exist.
+std::map<const void*, std::string>& kernels() {
+  static auto* m = new std::map<const void*, std::string>;
+  return *m;
+}
+
+int error(int e) {
+  t_error = e;
+  return e;
+}
+
+// The allocation that holds p, nullptr when it is not live.
+const Alloc* owner(const void* p) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  auto it = g_live.upper_bound((char*)p);
+  if (it == g_live.begin()) return nullptr;
+  --it;
+  return (char*)p < it->first + it->second.bytes ? &it->second : nullptr;
+}
+
+size_t live_count() {
+  std::lock_guard<std::mutex> lk(g_mu);
+  return g_live.size();
+}
+
+}  // namespace
+
+extern "C" {
+
+void** __hipRegisterFatBinary(const void*) {
+  static void* binary = nullptr;
+  return &binary;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*,
+                           void*, void*, int*) {
+  kernels()[host] = name;
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t shared, void* s) {
+  t_config.push_back({g, b, shared, s});
+  return kOk;
+}
+int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* shared, void** s) {
+  const Config c = t_config.back();
+  t_config.pop_back();
+  *g = c.grid;
+  *b = c.block;
+  *shared = c.shared;
+  *s = c.stream;
+  return kOk;
+}
+int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
+  if (kernels()[f].find("12batch_kernel") != std::string::npos) {
+    const Launch l = {*(char**)args[2], *(char**)args[6]};
+    std::lock_guard<std::mutex> lk(g_mu);
+    (g_capture ? g_capture->launches : g_ran).push_back(l);
+  }
+  return kOk;
+}
+
+int hipGetDevice(int* d) {
+  *d = t_device;
+  return kOk;
+}
+int hipSetDevice(int d) {
+  t_device = d;
+  return kOk;
+}
+int hipDeviceSynchronize() { return kOk; }
+int hipGetDevicePropertiesR0600(void*, int) { return kInvalid; }  // the library assumes 256 CUs
+const char* hipGetErrorString(int) { return "refused"; }
+int hipGetLastError() {
+  const int e = t_error;
+  t_error = kOk;
+  return e;
+}
+int hipGetSymbolAddress(void** p, const void* s) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  char*& m = g_symbols[s];
+  if (!m) m = (char*)std::calloc(1, 1 << 20);
+  *p = m;
+  return kOk;
+}
+
+int hipMalloc(void** p, size_t n) {
+  if (n > g_refuse_above) return error(kOutOfMemory);
+  char* q = (char*)std::calloc(1, n ? n : 1);
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_live[q] = {n, t_device};
+  if (n > g_largest) g_largest = n;
+  *p = q;
+  return kOk;
+}
+int hipFree(void* p) {
+  if (!p) return kOk;
+  {
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (g_live.erase((char*)p) == 0) {
+      std::printf("hipFree of memory that is not live\n");
+      std::exit(1);
+    }
+  }
+  std::free(p);
+  return kOk;
+}
+int hipMallocAsync(void** p, size_t n, void*) { return hipMalloc(p, n); }
+int hipFreeAsync(void* p, void*) { return hipFree(p); }
+int hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::calloc(1, n);
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_pinned[(char*)*p] = n;
+  return kOk;
+}
+int hipHostFree(void* p) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_pinned.erase((char*)p);
+  std::free(p);
+  return kOk;
+}
+int hipMemcpy(void* d, const void* s, size_t n, int) {
+  std::memcpy(d, s, n);
+  return kOk;
+}
+int hipMemcpyAsync(void* d, const void* s, size_t n, int k, void*) { return hipMemcpy(d, s, n, k); }
+int hipMemset(void* d, int v, size_t n) {
+  std::memset(d, v, n);
+  return kOk;
+}
+int hipMemsetAsync(void* d, int v, size_t n, void*) { return hipMemset(d, v, n); }
+
+int hipEventCreateWithFlags(void** e, unsigned) {
+  *e = std::malloc(1);
+  return kOk;
+}
+int hipEventCreate(void** e) { return hipEventCreateWithFlags(e, 0); }
+int hipEventDestroy(void* e) {
+  std::free(e);
+  return kOk;
+}
+int hipEventRecord(void*, void*) { return kOk; }
+int hipEventSynchronize(void*) { return kOk; }
+int hipEventElapsedTime(float* ms, void*, void*) {
+  static int n = 0;
+  *ms = 1.0f + 0.001f * (float)(n++ % 97);
+  return kOk;
+}
+int hipStreamCreateWithFlags(void** s, unsigned) {
+  *s = std::malloc(1);
+  return kOk;
+}
+int hipStreamDestroy(void* s) {
+  std::free(s);
+  return kOk;
+}
+int hipStreamSynchronize(void*) { return kOk; }
+int hipStreamWaitEvent(void*, void*, unsigned) { return kOk; }
+int hipStreamBeginCapture(void*, int) {
+  g_capture = new Graph;
+  return kOk;
+}
+int hipStreamEndCapture(void*, void** g) {
+  *g = g_capture;
+  g_capture = nullptr;
+  return kOk;
+}
+int hipGraphInstantiate(void** x, void* g, void*, char*, size_t) {
+  *x = new Graph(*(Graph*)g);
+  return kOk;
+}
+int hipGraphDestroy(void* g) {
+  delete (Graph*)g;
+  return kOk;
+}
+int hipGraphExecDestroy(void* x) {
+  delete (Graph*)x;
+  return kOk;
+}
+int hipGraphLaunch(void* x, void*) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  for (const Launch& l : ((Graph*)x)->launches) g_ran.push_back(l);
+  return kOk;
+}
+
+}  // extern "C"
+
+// ------------------------------------------------------------------ the tests
+
+namespace {
+
+// A device pointer of the caller's that nothing on the host reads.
+template <typename T>
+T* some(size_t i = 1) {
+  return reinterpret_cast<T*>(4096 * i);
+}
+
+vgicp_voxelmap empty_map() {
+  vgicp_voxelmap m = nullptr;
+  CHECK(vgicp_build_voxelmap(nullptr, nullptr, 0, 0.5, nullptr, &m) == VGICP_OK);
+  return m;
+}
+
+vgicp_batch make_batch(vgicp_voxelmap m, const std::vector<int64_t>& sizes) {
+  std::vector<vgicp_cloud> clouds;
+  std::vector<vgicp_factor> factors;
+  for (size_t c = 0; c < sizes.size(); ++c) {
+    clouds.push_back({some<float>(), some<float>(), sizes[c]});
+    factors.push_back({0, (int32_t)c, 0, 1, 1});
+  }
+  vgicp_batch b = nullptr;
+  CHECK(vgicp_batch_create(&m, 1, clouds.data(), (int32_t)clouds.size(), factors.data(),
+                           (int32_t)factors.size(), 2, &b) == VGICP_OK);
+  return b;
+}
+
+// A refused allocation fails its own call and nothing after it.
+void refusal_is_forgotten() {
+  const vgicp_voxelmap m = empty_map();
+  const vgicp_batch a = make_batch(m, std::vector<int64_t>(8, 100000));
+  const vgicp_schedule small{256, 2048, 4, 4};
+  g_refuse_above = 0;
+  CHECK(vgicp_batch_set_schedule(a, &small) == VGICP_E_OOM);
+  g_refuse_above = ~(size_t)0;
+  vgicp_batch_destroy(make_batch(m, {100}));
+  // memory that does not come from the kept blocks
+  const double* grad = some<double>();
+  g_refuse_above = 0;
+  CHECK(vgicp_batch_backward(a, grad, VGICP_ACC_FP64, grad, some<double>(2), nullptr, nullptr, nullptr) ==
+        VGICP_E_OOM);
+  g_refuse_above = ~(size_t)0;
+  vgicp_batch_destroy(make_batch(m, {100}));
+  vgicp_batch_destroy(a);
+  vgicp_destroy_voxelmap(m);
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> tests = {
+      {"refusal_is_forgotten", refusal_is_forgotten},
+  };
+  const auto it = tests.find(argc > 1 ? argv[1] : "");
+  if (it == tests.end()) return 2;
+  it->second();
+  std::printf("%s ok\n", argv[1]);
+  return 0;
+}

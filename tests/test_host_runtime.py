@@ -1,0 +1,34 @@
+"""Host code of libvgicp.so on a HIP runtime of host memory (tests/host_runtime/driver.cpp): ownership
+of the device blocks that outlive a call, refused allocations, devices, threads. CPU only."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2202_00242_amd")
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not os.path.exists(os.path.join(PKG, "libvgicp.so")):
+        from paper_2202_00242_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("host_runtime") / "driver")
+    src = os.path.join(ROOT, "tests", "host_runtime", "driver.cpp")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-rdynamic", "-pthread", "-o", exe, src,
+                        f"-L{PKG}", "-l:libvgicp.so", f"-Wl,-rpath,{PKG}",
+                        "-Wl,--allow-shlib-undefined"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return exe
+
+
+def run(driver, name):
+    r = subprocess.run([driver, name], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and f"{name} ok" in r.stdout, (r.returncode, r.stdout + r.stderr)
+
+
+def test_refused_allocation_fails_its_own_call_only(driver):
+    run(driver, "refusal_is_forgotten")
