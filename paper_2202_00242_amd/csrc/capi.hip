@@ -914,45 +914,56 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
         for (int t = 0; t < ntiles[f]; ++t) items.push_back({f, t});
   }
   seg[kNumXcd] = (int)items.size();
+  std::vector<FactorView> hf = b->hf;
   for (int f = 0; f < b->F; ++f) {
-    b->hf[f].tile_base = base[f];
-    b->hf[f].ntiles = ntiles[f];
+    hf[f].tile_base = base[f];
+    hf[f].ntiles = ntiles[f];
   }
   hipError_t e;
   // [factors | segments | items] in one block and one copy
-  const size_t o_seg = Arena::up(b->hf.size() * sizeof(FactorView));
+  const size_t o_seg = Arena::up(hf.size() * sizeof(FactorView));
   const size_t o_items = o_seg + Arena::up(seg.size() * sizeof(int));
   const size_t bytes = o_items + items.size() * sizeof(WorkItem);
   const size_t np = (size_t)std::max<int64_t>(total, 1) * (size_t)(sc.block / 64) * kPartialStride;
-  // another schedule may need more: the old blocks' readers are done (the callers synchronise)
-  auto grow = [&](void** p, size_t* cap, size_t want) {
-    if (want <= *cap) return hipSuccess;
-    block_give(*p, *cap, b->device);
-    *p = nullptr;
-    *cap = 0;
-    const hipError_t ge = block_take(p, &want);
-    if (ge == hipSuccess) *cap = want;
-    return ge;
-  };
-  if ((e = grow(reinterpret_cast<void**>(&b->d_sched), &b->sched_cap, bytes)) ||
-      (e = grow(reinterpret_cast<void**>(&b->d_partials), &b->partials_cap, np * sizeof(double))))
-    return hip_fail(e, "device block (schedule)");
-  b->d_factors = reinterpret_cast<FactorView*>(b->d_sched);
-  b->d_seg = reinterpret_cast<int*>(b->d_sched + o_seg);
-  b->d_items = reinterpret_cast<WorkItem*>(b->d_sched + o_items);
   std::vector<char> image(bytes);
-  if (b->F > 0) std::memcpy(image.data(), b->hf.data(), b->hf.size() * sizeof(FactorView));
+  if (b->F > 0) std::memcpy(image.data(), hf.data(), hf.size() * sizeof(FactorView));
   std::memcpy(image.data() + o_seg, seg.data(), seg.size() * sizeof(int));
   if (!items.empty())
     std::memcpy(image.data() + o_items, items.data(), items.size() * sizeof(WorkItem));
-  if ((e = hipMemcpy(b->d_sched, image.data(), bytes, hipMemcpyHostToDevice)))
+  // The batch keeps its schedule, graphs and blocks until the new ones are all there: a block given
+  // back before that would be in two hands after a refused allocation.
+  void *sched = nullptr, *partials = nullptr;
+  size_t sched_cap = bytes, partials_cap = np * sizeof(double);
+  const bool more = partials_cap > b->partials_cap;
+  if ((e = block_take(&sched, &sched_cap))) return hip_fail(e, "device block (schedule)");
+  if (more && (e = block_take(&partials, &partials_cap))) {
+    block_give(sched, sched_cap, b->device);
+    return hip_fail(e, "device block (partial sums)");
+  }
+  if ((e = hipMemcpy(sched, image.data(), bytes, hipMemcpyHostToDevice))) {
+    block_give(sched, sched_cap, b->device);
+    if (more) block_give(partials, partials_cap, b->device);
     return hip_fail(e, "upload schedule");
+  }
+  // the old blocks' readers are done (the callers synchronise)
+  b->drop_graphs();
+  block_give(b->d_sched, b->sched_cap, b->device);
+  b->d_sched = static_cast<char*>(sched);
+  b->sched_cap = sched_cap;
+  if (more) {
+    block_give(b->d_partials, b->partials_cap, b->device);
+    b->d_partials = static_cast<double*>(partials);
+    b->partials_cap = partials_cap;
+  }
+  b->hf.swap(hf);
+  b->d_factors = reinterpret_cast<FactorView*>(b->d_sched);
+  b->d_seg = reinterpret_cast<int*>(b->d_sched + o_seg);
+  b->d_items = reinterpret_cast<WorkItem*>(b->d_sched + o_items);
   b->total_tiles = (int)total;
   const int cus = device_cu_count(b->device);
   const int blocks = cus * sc.blocks_per_cu * (sc.block / 256);
   b->grid = ((blocks + kNumXcd - 1) / kNumXcd) * kNumXcd;
   b->sched = sc;
-  b->drop_graphs();
   return VGICP_OK;
 }
 

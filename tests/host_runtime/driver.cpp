@@ -272,6 +272,21 @@ vgicp_batch make_batch(vgicp_voxelmap m, const std::vector<int64_t>& sizes) {
   return b;
 }
 
+// The memory that a linearization of the batch runs on.
+Launch linearize(vgicp_batch b) {
+  g_ran.clear();
+  CHECK(vgicp_batch_linearize(b, some<double>(), VGICP_ACC_FP64, some<double>(2), some<double>(3),
+                              some<double>(4), some<int64_t>(5), nullptr) == VGICP_OK);
+  CHECK(g_ran.size() == 1);
+  CHECK(owner(g_ran[0].items) && owner(g_ran[0].partials));
+  return g_ran[0];
+}
+
+bool same(const vgicp_schedule& a, const vgicp_schedule& b) {
+  return a.block == b.block && a.tile == b.tile && a.blocks_per_cu == b.blocks_per_cu &&
+         a.lookahead == b.lookahead;
+}
+
 // A refused allocation fails its own call and nothing after it.
 void refusal_is_forgotten() {
   const vgicp_voxelmap m = empty_map();
@@ -292,11 +307,47 @@ void refusal_is_forgotten() {
   vgicp_destroy_voxelmap(m);
 }
 
+// A schedule whose memory is refused leaves the batch as it was: on its old schedule, with memory that
+// nobody else is given.
+void schedule_refused() {
+  const vgicp_voxelmap m = empty_map();
+  const std::vector<int64_t> sizes(8, 100000);
+  const vgicp_batch a = make_batch(m, sizes);
+  const Launch before = linearize(a);
+  vgicp_schedule old, now, small{256, 2048, 4, 4};
+  CHECK(vgicp_batch_get_schedule(a, &old) == VGICP_OK);
+  g_refuse_above = 0;
+  CHECK(vgicp_batch_set_schedule(a, &small) == VGICP_E_OOM);
+  g_refuse_above = ~(size_t)0;
+  CHECK(vgicp_batch_get_schedule(a, &now) == VGICP_OK && same(old, now));
+  const vgicp_batch b = make_batch(m, sizes);
+  const Launch mine = linearize(a), other = linearize(b);
+  CHECK(mine.partials != other.partials && mine.items != other.items);
+  CHECK(mine.partials == before.partials && mine.items == before.items);
+  // the candidates that fit are timed, the others are skipped, and the batch runs on the choice
+  g_refuse_above = 300 << 10;
+  vgicp_schedule chosen;
+  CHECK(vgicp_batch_autotune(a, some<double>(), VGICP_ACC_FP64, nullptr, &chosen, nullptr) == VGICP_OK);
+  CHECK(vgicp_batch_get_schedule(a, &now) == VGICP_OK && same(chosen, now));
+  g_refuse_above = ~(size_t)0;
+  const Launch tuned = linearize(a);
+  CHECK(tuned.partials != other.partials && tuned.items != other.items);
+  // and without refusals it changes
+  CHECK(vgicp_batch_set_schedule(a, &small) == VGICP_OK);
+  CHECK(vgicp_batch_get_schedule(a, &now) == VGICP_OK && same(small, now));
+  const Launch changed = linearize(a);
+  CHECK(changed.partials != other.partials && changed.items != other.items);
+  vgicp_batch_destroy(a);
+  vgicp_batch_destroy(b);
+  vgicp_destroy_voxelmap(m);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"refusal_is_forgotten", refusal_is_forgotten},
+      {"schedule_refused", schedule_refused},
   };
   const auto it = tests.find(argc > 1 ? argv[1] : "");
   if (it == tests.end()) return 2;

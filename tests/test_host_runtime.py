@@ -32,3 +32,7 @@ def run(driver, name):
 
 def test_refused_allocation_fails_its_own_call_only(driver):
     run(driver, "refusal_is_forgotten")
+
+
+def test_refused_schedule_leaves_the_batch_as_it_was(driver):
+    run(driver, "schedule_refused")
