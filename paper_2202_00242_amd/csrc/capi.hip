@@ -831,6 +831,20 @@ struct vgicp_batch_s {
 
 namespace {
 
+// Makes a batch's device current for a call that takes memory or waits on it.
+struct OnDevice {
+  int cur = 0;
+  bool moved = false;
+  explicit OnDevice(int device) {
+    moved = hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess;
+  }
+  ~OnDevice() {
+    if (moved) (void)hipSetDevice(cur);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+};
+
 // Orders a call on the batch after the previous one (see vgicp_batch_s::done).
 vgicp_status batch_begin(vgicp_batch b, hipStream_t s) {
   hipError_t e;
@@ -1203,6 +1217,7 @@ VGICP_API vgicp_status vgicp_batch_create(const vgicp_voxelmap* maps, int32_t n_
 
 VGICP_API vgicp_status vgicp_batch_refresh(vgicp_batch batch, vgicp_stream stream) {
   if (!batch) return fail(VGICP_E_INVALID_ARG, "batch is NULL");
+  const OnDevice on(batch->device);
   hipStream_t s = stream_of(stream);
   vgicp_status st0 = batch_begin(batch, s);
   if (st0 != VGICP_OK) return st0;
@@ -1220,6 +1235,8 @@ VGICP_API vgicp_status vgicp_batch_set_schedule(vgicp_batch batch,
                                                 const vgicp_schedule* schedule) {
   if (!batch || !schedule) return fail(VGICP_E_INVALID_ARG, "NULL argument");
   if (!valid_schedule(*schedule)) return fail(VGICP_E_INVALID_ARG, "unsupported schedule");
+  // its blocks are taken from and, once their readers are done, given back to the batch's device
+  const OnDevice on(batch->device);
   hipError_t e = hipDeviceSynchronize();
   if (e) return hip_fail(e, "hipDeviceSynchronize");
   return apply_schedule(batch, *schedule);

@@ -52,6 +52,7 @@ std::map<char*, size_t> g_pinned;
 std::map<const void*, char*> g_symbols;
 size_t g_refuse_above = ~(size_t)0;            // device allocations of more bytes are refused
 size_t g_largest = 0;                          // largest device allocation so far
+int g_synchronised = -1;                       // device of the last device synchronisation
 Graph* g_capture = nullptr;
 std::vector<Launch> g_ran;                     // executed launches of batch_kernel
 thread_local int t_device = 0, t_error = kOk;
@@ -126,7 +127,10 @@ int hipSetDevice(int d) {
   t_device = d;
   return kOk;
 }
-int hipDeviceSynchronize() { return kOk; }
+int hipDeviceSynchronize() {
+  g_synchronised = t_device;
+  return kOk;
+}
 int hipGetDevicePropertiesR0600(void*, int) { return kInvalid; }  // the library assumes 256 CUs
 const char* hipGetErrorString(int) { return "refused"; }
 int hipGetLastError() {
@@ -342,12 +346,38 @@ void schedule_refused() {
   vgicp_destroy_voxelmap(m);
 }
 
+// A batch's calls without a device argument of their own work on the batch's device, whichever is
+// current, and leave that one current.
+void other_device_current() {
+  const vgicp_voxelmap m = empty_map();
+  const vgicp_batch a = make_batch(m, std::vector<int64_t>(8, 100000));
+  const vgicp_schedule small{256, 2048, 4, 4};
+  CHECK(hipSetDevice(1) == kOk);
+  CHECK(vgicp_batch_set_schedule(a, &small) == VGICP_OK);
+  CHECK(t_device == 1 && g_synchronised == 0);
+  // what was given back is the other device's memory, and no other's is taken from it
+  const vgicp_voxelmap m1 = empty_map();
+  const vgicp_batch b = make_batch(m1, std::vector<int64_t>(8, 100000));
+  const Launch other = linearize(b);
+  CHECK(owner(other.items)->device == 1 && owner(other.partials)->device == 1);
+  CHECK(vgicp_batch_refresh(a, nullptr) == VGICP_OK);
+  CHECK(t_device == 1);
+  CHECK(hipSetDevice(0) == kOk);
+  const Launch mine = linearize(a);
+  CHECK(owner(mine.items)->device == 0 && owner(mine.partials)->device == 0);
+  vgicp_batch_destroy(a);
+  vgicp_batch_destroy(b);
+  vgicp_destroy_voxelmap(m);
+  vgicp_destroy_voxelmap(m1);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"refusal_is_forgotten", refusal_is_forgotten},
       {"schedule_refused", schedule_refused},
+      {"other_device_current", other_device_current},
   };
   const auto it = tests.find(argc > 1 ? argv[1] : "");
   if (it == tests.end()) return 2;

@@ -36,3 +36,7 @@ def test_refused_allocation_fails_its_own_call_only(driver):
 
 def test_refused_schedule_leaves_the_batch_as_it_was(driver):
     run(driver, "schedule_refused")
+
+
+def test_batch_calls_with_another_device_current(driver):
+    run(driver, "other_device_current")
