@@ -772,7 +772,8 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
   hipError_t e;
   const size_t C = jobs.size();
   if (C == 0) return VGICP_OK;
-  // the clouds that factors read, those a pass can sort in one launch first
+  // the clouds that factors read, the largest first: a group's digit counts and grid are those of its
+  // largest cloud for every cloud in it
   std::vector<SpatialSeg> segs;
   for (size_t c = 0; c < C; ++c) {
     const SpatialJob& j = jobs[c];
@@ -780,6 +781,8 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
       segs.push_back({j.xyz, j.cov, j.xyz_out, j.cov6_out, j.perm, 0, 1.0 / j.cell, (int)j.n,
                       (int)c});
   }
+  std::stable_sort(segs.begin(), segs.end(),
+                   [](const SpatialSeg& a, const SpatialSeg& b) { return a.n > b.n; });
   HostBlock hb;
   if (!hb.p) return fail(VGICP_E_OOM, "pinned host block");
   BuildReport* rep = static_cast<BuildReport*>(hb.p);
@@ -821,13 +824,19 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
     return b;
   };
   for (int first = 0; first < S;) {
-    // as many clouds together as fit 4 M points (their pairs and digit counts: about 150 MB)
+    // as many clouds together as fit 4 M points (24 bytes each for their pairs: 96 MiB) and 2^16 tiles
+    // of the largest (1 KB of digit counts each: 64 MiB). Clouds of one size reach the second bound
+    // only where a cloud is far smaller than a tile (32,768 single points: 32 MiB); without it a cloud of
+    // 2^18 points among 4,000 of 900 made 1 GB of counts.
+    constexpr long long kGroupPoints = 4LL << 20, kGroupTiles = 1LL << 16;
     long long pts = 0, max_n = 1;
     int m = 0, b = 0;
     bool big = false;
     while (first + m < S && m < 32768) {
       SpatialSeg& g = segs[first + m];
-      if (m > 0 && (big || g.n > kSortMax || pts + g.n > (4LL << 20))) break;
+      if (m > 0 && (big || g.n > kSortMax || pts + g.n > kGroupPoints ||
+                    (m + 1) * sort_tiles(std::max<long long>(max_n, g.n)) > kGroupTiles))
+        break;
       big = g.n > kSortMax;
       g.off = pts;
       pts += g.n;

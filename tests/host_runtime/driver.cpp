@@ -371,6 +371,20 @@ void other_device_current() {
   vgicp_destroy_voxelmap(m1);
 }
 
+// The clouds of a batch are put in order together; one large cloud among many small ones does not
+// make each of those pay for it. 3.9 M points: 154 MB of copies, at most 160 MB to order them.
+void order_memory() {
+  const vgicp_voxelmap m = empty_map();
+  std::vector<int64_t> sizes(4000, 900);
+  sizes[700] = 260000;
+  sizes[2900] = 262144;
+  g_largest = 0;
+  const vgicp_batch b = make_batch(m, sizes);
+  CHECK(g_largest <= 200u << 20);
+  vgicp_batch_destroy(b);
+  vgicp_destroy_voxelmap(m);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -378,6 +392,7 @@ int main(int argc, char** argv) {
       {"refusal_is_forgotten", refusal_is_forgotten},
       {"schedule_refused", schedule_refused},
       {"other_device_current", other_device_current},
+      {"order_memory", order_memory},
   };
   const auto it = tests.find(argc > 1 ? argv[1] : "");
   if (it == tests.end()) return 2;

@@ -40,3 +40,7 @@ def test_refused_schedule_leaves_the_batch_as_it_was(driver):
 
 def test_batch_calls_with_another_device_current(driver):
     run(driver, "other_device_current")
+
+
+def test_memory_of_ordering_small_clouds_beside_large_ones(driver):
+    run(driver, "order_memory")
