@@ -368,9 +368,10 @@ VGICP_API vgicp_status vgicp_backward_tangent(vgicp_voxelmap map, const float* x
 
 /* The calls above with the caller's own device workspace for the per-tile partial sums, instead of a
  * stream-ordered allocation per call (18 us of a small factor's 40): same arguments, kernels, results
- * (bitwise) and errors, and E_INVALID_ARG for a NULL workspace, E_CAPACITY for one smaller than
- * vgicp_workspace_size(n). The workspace (8-byte aligned) is written and read by the call's work on
- * `stream` only: it may be used again by later work of the same stream at once, by others after an
+ * (bitwise) and errors, and E_INVALID_ARG for a workspace that is NULL or not 8-byte aligned, E_CAPACITY
+ * for one smaller than the call needs (never more than vgicp_workspace_size(n); that size does not grow
+ * steadily with n, so it is to be asked for each n). The workspace is written and read by the call's work
+ * on `stream` only: it may be used again by later work of the same stream at once, by others after an
  * ordering of the caller's. */
 VGICP_API vgicp_status vgicp_workspace_size(int64_t n, int64_t* bytes);
 VGICP_API vgicp_status vgicp_linearize_workspace(

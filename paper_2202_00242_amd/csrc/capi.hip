@@ -698,12 +698,20 @@ VGICP_API vgicp_status vgicp_workspace_size(int64_t n, int64_t* bytes) {
   return VGICP_OK;
 }
 
+static vgicp_status check_workspace(const void* workspace, int64_t bytes) {
+  if (!workspace || bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  if (reinterpret_cast<uintptr_t>(workspace) % sizeof(double) != 0)
+    return fail(VGICP_E_INVALID_ARG, "workspace is not 8-byte aligned");
+  return VGICP_OK;
+}
+
 VGICP_API vgicp_status vgicp_linearize_workspace(
     vgicp_voxelmap map, const float* xyz, const float* cov, int64_t n, const double* T_target,
     const double* T_source, int32_t binary, vgicp_precision precision, double* H, double* b,
     double* err, int64_t* inliers, int32_t* corr, void* workspace, int64_t workspace_bytes,
     vgicp_stream stream) {
-  if (!workspace || workspace_bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  const vgicp_status ws = check_workspace(workspace, workspace_bytes);
+  if (ws != VGICP_OK) return ws;
   return single_factor(map, xyz, cov, n, T_target, T_source, binary, (int)precision, true, H, b,
                        err, inliers, corr, stream, false, workspace, (size_t)workspace_bytes);
 }
@@ -715,7 +723,8 @@ VGICP_API vgicp_status vgicp_evaluate_workspace(vgicp_voxelmap map, const float*
                                                 int64_t* inliers, int32_t* corr,
                                                 void* workspace, int64_t workspace_bytes,
                                                 vgicp_stream stream) {
-  if (!workspace || workspace_bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  const vgicp_status ws = check_workspace(workspace, workspace_bytes);
+  if (ws != VGICP_OK) return ws;
   return single_factor(map, xyz, cov, n, T_target, T_source, 0, (int)precision, false, nullptr,
                        nullptr, err, inliers, corr, stream, false, workspace,
                        (size_t)workspace_bytes);
@@ -726,7 +735,8 @@ VGICP_API vgicp_status vgicp_backward_tangent_workspace(
     const double* T_source, const double* xi_target, const double* xi_source, int32_t binary,
     const int32_t* corr, const double* grad_err, vgicp_precision precision, double* grad_xi,
     float* grad_xyz, void* workspace, int64_t workspace_bytes, vgicp_stream stream) {
-  if (!workspace || workspace_bytes < 0) return fail(VGICP_E_INVALID_ARG, "NULL workspace");
+  const vgicp_status ws = check_workspace(workspace, workspace_bytes);
+  if (ws != VGICP_OK) return ws;
   return backward_impl(map, xyz, cov, n, T_target, T_source, xi_target, xi_source, binary, corr,
                        grad_err, (int)precision, grad_xi, grad_xyz, stream, workspace,
                        (size_t)workspace_bytes);

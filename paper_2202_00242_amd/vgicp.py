@@ -170,6 +170,13 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+def _flat(t, name: str) -> torch.Tensor:
+    """A caller's block of device bytes."""
+    if _dev(t, torch.uint8, name=name).dim() != 1:
+        raise ValueError(f"{name} must have one dimension")
+    return t
+
+
 def _workspace(n: int, device) -> torch.Tensor:
     """Partial sums of one single-factor call on the current stream, from torch's allocator: it hands
     the memory out again to later work of the same stream only."""
@@ -447,8 +454,7 @@ def _linearize(fn, name, m, xyz, cov, T_target, T_source, binary, precision, wan
             int(precision), _ptr(out["H"]), _ptr(out["b"]), _ptr(out["err"]),
             _ptr(out["inliers"]), _ptr(out.get("corr"))]
     if workspace is not None or (stream is None and fn is _lib.vgicp_linearize):
-        ws = _workspace(n, dev) if workspace is None else _dev(
-            workspace, torch.uint8, (workspace.numel(),), "workspace")
+        ws = _workspace(n, dev) if workspace is None else _flat(workspace, "workspace")
         fn = _lib.vgicp_linearize_workspace
         args += [_ptr(ws), ws.numel()]
     _check(fn(*args, _stream(stream)), name)
@@ -478,8 +484,7 @@ def _evaluate(m, xyz, cov, T_target, T_source, precision, want_corr, stream, wor
     args = [m.handle, _ptr(xyz), _ptr(cov), n, _np_ptr(Tt), _np_ptr(Ts), int(precision),
             _ptr(out["err"]), _ptr(out["inliers"]), _ptr(out["corr"])]
     if workspace is not None or stream is None:
-        ws = _workspace(n, dev) if workspace is None else _dev(
-            workspace, torch.uint8, (workspace.numel(),), "workspace")
+        ws = _workspace(n, dev) if workspace is None else _flat(workspace, "workspace")
         fn = _lib.vgicp_evaluate_workspace
         args += [_ptr(ws), ws.numel()]
     _check(fn(*args, _stream(stream)), "vgicp_evaluate")
@@ -542,8 +547,7 @@ def _backward_tangent(m, xyz, cov, T_target, T_source, xi_target, xi_source, bin
             None if xt is None else _np_ptr(xt), None if xs is None else _np_ptr(xs),
             int(bool(binary)), _ptr(corr), _ptr(grad_err), int(precision), _ptr(gxi), _ptr(gp)]
     if workspace is not None or stream is None:
-        ws = _workspace(n, dev) if workspace is None else _dev(
-            workspace, torch.uint8, (workspace.numel(),), "workspace")
+        ws = _workspace(n, dev) if workspace is None else _flat(workspace, "workspace")
         fn = _lib.vgicp_backward_tangent_workspace
         args += [_ptr(ws), ws.numel()]
     _check(fn(*args, _stream(stream)), "vgicp_backward_tangent")

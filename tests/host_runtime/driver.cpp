@@ -3,6 +3,7 @@
 // device memory in host memory, kernels that do nothing and refusals on demand. What it checks is the
 // library's host code: who owns which block of memory, on which device, and what is left after a
 // refused allocation. Usage: driver <test>; prints "<test> ok".
+#include <atomic>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -52,6 +53,7 @@ std::map<char*, size_t> g_pinned;
 std::map<const void*, char*> g_symbols;
 size_t g_refuse_above = ~(size_t)0;            // device allocations of more bytes are refused
 size_t g_largest = 0;                          // largest device allocation so far
+std::atomic<int> g_launched{0};                // kernels launched
 int g_synchronised = -1;                       // device of the last device synchronisation
 Graph* g_capture = nullptr;
 std::vector<Launch> g_ran;                     // executed launches of batch_kernel
@@ -111,6 +113,7 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* shared, void** s) {
   return kOk;
 }
 int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
+  ++g_launched;
   if (kernels()[f].find("12batch_kernel") != std::string::npos) {
     const Launch l = {*(char**)args[2], *(char**)args[6]};
     std::lock_guard<std::mutex> lk(g_mu);
@@ -385,6 +388,34 @@ void order_memory() {
   vgicp_destroy_voxelmap(m);
 }
 
+// The caller's workspace: absent, misaligned and short ones are refused before anything is launched.
+void workspace_checks() {
+  const vgicp_voxelmap m = empty_map();
+  const double T[12] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0};
+  double* out = some<double>(2);
+  int64_t need = 0;
+  CHECK(vgicp_workspace_size(1000, &need) == VGICP_OK && need > 0);
+  auto all = [&](void* ws, int64_t bytes, vgicp_status want) {
+    g_launched = 0;
+    CHECK(vgicp_linearize_workspace(m, some<float>(), some<float>(), 1000, T, T, 1, VGICP_ACC_FP64, out,
+                                    out, out, some<int64_t>(3), nullptr, ws, bytes, nullptr) == want);
+    CHECK(vgicp_evaluate_workspace(m, some<float>(), some<float>(), 1000, T, T, VGICP_ACC_FP64, out,
+                                   some<int64_t>(3), nullptr, ws, bytes, nullptr) == want);
+    CHECK(vgicp_backward_tangent_workspace(m, some<float>(), some<float>(), 1000, T, T, nullptr, nullptr,
+                                           1, some<int32_t>(4), out, VGICP_ACC_FP64, out, nullptr, ws,
+                                           bytes, nullptr) == want);
+    CHECK((g_launched > 0) == (want == VGICP_OK));
+  };
+  char* ws = some<char>(5);
+  all(ws, need, VGICP_OK);
+  all(ws + 8, need, VGICP_OK);
+  all(nullptr, need, VGICP_E_INVALID_ARG);
+  all(ws, -1, VGICP_E_INVALID_ARG);
+  for (int off = 1; off < 8; ++off) all(ws + off, need, VGICP_E_INVALID_ARG);
+  all(ws, 8, VGICP_E_CAPACITY);
+  vgicp_destroy_voxelmap(m);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -393,6 +424,7 @@ int main(int argc, char** argv) {
       {"schedule_refused", schedule_refused},
       {"other_device_current", other_device_current},
       {"order_memory", order_memory},
+      {"workspace_checks", workspace_checks},
   };
   const auto it = tests.find(argc > 1 ? argv[1] : "");
   if (it == tests.end()) return 2;

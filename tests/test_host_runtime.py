@@ -44,3 +44,7 @@ def test_batch_calls_with_another_device_current(driver):
 
 def test_memory_of_ordering_small_clouds_beside_large_ones(driver):
     run(driver, "order_memory")
+
+
+def test_workspace_checks(driver):
+    run(driver, "workspace_checks")

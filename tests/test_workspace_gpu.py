@@ -1,0 +1,37 @@
+"""What the binding refuses as a caller's workspace: every form with ValueError where it is no flat block
+of device bytes, and with the library's E_INVALID_ARG where it is not 8-byte aligned."""
+import numpy as np
+import pytest
+import torch
+
+from tests import tiny
+from tests.gpu_util import cloud_dev, dev
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def test_refused_workspaces():
+    import paper_2202_00242_amd.vgicp as V
+    rng = np.random.default_rng(3)
+    x, c = cloud_dev(*tiny.cloud(rng, 500))
+    m = V.vgicp_build_voxelmap(x, c, 0.5)
+    T = np.eye(4)
+    corr = V.vgicp_evaluate(m, x, c, T, T, want_corr=True)["corr"]
+    g = dev(np.ones(1))
+    size = V.vgicp_workspace_size(500)
+    block = torch.zeros(size + 16, dtype=torch.uint8, device="cuda")
+    forms = [lambda ws: V.vgicp_linearize_workspace(m, x, c, T, T, True, ws),
+             lambda ws: V.vgicp_evaluate_workspace(m, x, c, T, T, ws),
+             lambda ws: V.vgicp_backward_tangent_workspace(m, x, c, T, T, None, None, True, corr, g, ws)]
+    for form in forms:
+        for ws in (bytearray(size), np.zeros(size, np.uint8), 1234, block.cpu(), block[::2],
+                   block.view(2, -1), block[:size // 8 * 8].view(torch.float64)):
+            with pytest.raises(ValueError):
+                form(ws)
+        for off in (1, 4, 7):
+            with pytest.raises(V.VGICPError) as ei:
+                form(block[off:off + size])
+            assert ei.value.status == V.VGICP_E_INVALID_ARG
+        form(block[8:8 + size])
+    torch.cuda.synchronize()
