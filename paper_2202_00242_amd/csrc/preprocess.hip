@@ -67,18 +67,28 @@ __global__ __launch_bounds__(kBlock) void ds_cells_kernel(const float* __restric
   if (fl & kFlagKeyRange) report->keyrange = 1;
 }
 
-// Sort key of a timestamp: its FP32 bits made monotone as unsigned (-0 counted as +0).
+// Sort key of a timestamp: its FP32 bits made monotone as unsigned (-0 counted as +0). One block per
+// sort tile; hist (may be null): the first pass's digit counts.
 __global__ __launch_bounds__(kBlock) void ds_time_key_kernel(const float* __restrict__ t,
                                                              long long n,
                                                              unsigned long long* __restrict__ key,
-                                                             int* __restrict__ idx) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
+                                                             int* __restrict__ idx,
+                                                             int* __restrict__ hist) {
+  unsigned digit[kSortTile / kBlock];
+  bool valid[kSortTile / kBlock];
+#pragma unroll
+  for (int q = 0; q < kSortTile / kBlock; ++q) {
+    const long long i = (long long)blockIdx.x * kSortTile + q * kBlock + threadIdx.x;
+    valid[q] = i < n;
+    digit[q] = 0;
+    if (!valid[q]) continue;
     unsigned b = __float_as_uint(t[i] + 0.0f);
     b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
     key[i] = b;
     idx[i] = (int)i;
+    digit[q] = b;
   }
+  if (hist) sort_tile_hist(digit, valid, hist + (size_t)blockIdx.x * 256);
 }
 
 // Cell key of the point at each position of `order` (identity if null): coordinates relative to
@@ -113,36 +123,76 @@ __global__ __launch_bounds__(kBlock) void ds_cell_key_kernel(const int* __restri
 
 // Time order within the cells: a point's place is the number of its cell's points before it in
 // (timestamp, index) order, counted directly (a cell holds a few points: for a sweep of 53,000
-// points one launch of a few us instead of four passes of a sort by time). A cell of more than
-// kMaxRanked points would cost its square: the call then sorts by time.
-constexpr int kMaxRanked = 4096;
+// points one launch of a few us instead of four passes of a sort by time). The block's 256 positions
+// span few cells, whose timestamps go through LDS kRankChunk at a time. A cell costs its square: with
+// 260,000 points in cells of 1,024 the ranks take 108 us and in cells of 4,000 347, the sort by time 88
+// and 66 more for sorting by cell again, so a cell of more than kMaxRanked points sends the call there
+// (cells of 2,000 to 8,192 points: 2.3, 4.1 and 8.0 ms for the filter, most of it the walks).
+constexpr int kMaxRanked = 2048, kRankChunk = 1024;
 __global__ __launch_bounds__(kBlock) void ds_time_rank_kernel(
     const int* __restrict__ val, long long n, const int* __restrict__ start,
     const int* __restrict__ cells, const float* __restrict__ t, int* __restrict__ order,
-    BuildReport* __restrict__ report) {
+    int* __restrict__ unranked, BuildReport* __restrict__ report) {
+  __shared__ float ts[kRankChunk];
+  __shared__ int first, last;
   const int C = *cells;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
+  for (long long b0 = (long long)blockIdx.x * kBlock; b0 < n; b0 += (long long)gridDim.x * kBlock) {
+    const int i = (int)min(b0 + threadIdx.x, n - 1);
     int lo = 0, hi = C;  // start[lo] <= i < start[hi]
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
       if (start[mid] <= i) lo = mid; else hi = mid;
     }
     const int s = start[lo], e = start[lo + 1];
-    const int me = val[i];
-    if (e - s > kMaxRanked) {
+    const bool live = b0 + threadIdx.x < n, deep = e - s > kMaxRanked;
+    if (deep) {
+      *unranked = 1;
       report->deep = 1;
-      order[i] = me;  // the count pass still runs over it
-      continue;
     }
+    const int me = val[i];
     const float ti = t[me];
-    int rank = 0;
-    for (int j = s; j < e; ++j) {  // positions within a cell are in index order
-      const float tj = t[val[j]];
-      rank += tj < ti || (tj == ti && j < i) ? 1 : 0;
+    if (threadIdx.x == 0) {
+      first = INT_MAX;
+      last = 0;
     }
-    order[s + rank] = me;
+    __syncthreads();
+    if (!deep) {
+      atomicMin(&first, s);
+      atomicMax(&last, e);
+    }
+    __syncthreads();
+    const int from = first, to = last;
+    int rank = 0;
+    for (int c0 = from; c0 < to; c0 += kRankChunk) {
+      __syncthreads();  // the chunk before (and the bounds) have been read
+#pragma unroll
+      for (int q = 0; q < kRankChunk / kBlock; ++q) {
+        const int j = c0 + q * kBlock + threadIdx.x;
+        ts[q * kBlock + threadIdx.x] = t[val[min(j, to - 1)]];
+      }
+      __syncthreads();
+      // positions within a cell are in index order
+      const int a = max(s, c0), b = deep ? a : min(e, c0 + kRankChunk);
+#pragma unroll 8
+      for (int j = a; j < b; ++j) {
+        const float tj = ts[j - c0];
+        rank += (int)(tj < ti) | ((int)(tj == ti) & (int)(j < i));
+      }
+    }
+    if (live && !deep) order[s + rank] = me;
+    __syncthreads();
   }
+}
+
+// Which threads the cells of a walk go to: a walk is a chain of dependent loads per cell, and a wave
+// takes as long as all its lanes' gathers together, so cells of many points get waves of their own: every
+// (1 << s)-th thread has one, as many apart as n allows. Packed into the first threads, 260,000 points in
+// cells of 1,024 took 1,449 us to write (now 554), the whole filter 2,414 (now 1,134); two or four times
+// denser than this cost 53,000 points in cells of 64 up to 13 % and gained 260,000 in cells of 128 up to 8 %.
+__device__ inline int walk_shift(long long n, int cells) {
+  int s = 0;
+  while (s < 6 && ((long long)cells << (s + 1)) <= n) ++s;
+  return s;
 }
 
 // One thread per cell walks the cell's points in (time, index) order: the count pass stores the
@@ -151,21 +201,23 @@ __global__ __launch_bounds__(kBlock) void ds_time_rank_kernel(
 template <bool EMIT>
 __global__ __launch_bounds__(kBlock) void ds_walk_kernel(
     const int* __restrict__ val, long long n, const int* __restrict__ start,
-    const int* __restrict__ cells, const float* __restrict__ xyz, const float* __restrict__ t,
-    double thr, int* __restrict__ vcount, const int* __restrict__ voff,
-    const int* __restrict__ total, long long capacity, float* __restrict__ out,
-    float* __restrict__ tout, BuildReport* __restrict__ report) {
+    const int* __restrict__ cells, const int* __restrict__ unranked,
+    const float* __restrict__ xyz, const float* __restrict__ t, double thr,
+    int* __restrict__ vcount, const int* __restrict__ voff, const int* __restrict__ total,
+    long long capacity, float* __restrict__ out, float* __restrict__ tout,
+    BuildReport* __restrict__ report) {
 #pragma clang fp contract(off)
+  if (unranked && *unranked) return;  // a cell has no order yet: the call starts again by time
   const int C = *cells;
   const long long m = EMIT ? *total : 0;
   if (EMIT && blockIdx.x == 0 && threadIdx.x == 0) report->count = (int)m;
   if (EMIT && m > capacity) return;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    if (i >= C) {
-      if (!EMIT) vcount[i] = 0;
-      continue;
-    }
+  const int shift = walk_shift(n, C);  // C << shift <= n
+  for (long long at = (long long)blockIdx.x * blockDim.x + threadIdx.x; at < n;
+       at += (long long)gridDim.x * blockDim.x) {
+    if (!EMIT && at >= C) vcount[at] = 0;
+    const long long i = at >> shift;
+    if (i >= C || (i << shift) != at) continue;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, st = 0.0;
     int cnt = 0, nv = 0;
     const long long o = EMIT ? voff[i] : 0;
@@ -823,7 +875,7 @@ vgicp_status downsample(const float* xyz, const float* t, int64_t n, double res,
   for (int i = 0; i < 5; ++i) ar.need<int>(N);
   ar.need<int>(N + 1);
   ar.need<int>(kRunTiles);
-  ar.need<int>(2);
+  ar.need<int>(3);
   hipError_t e;
   if ((e = ar.get(s))) return hip_fail(e, "device block (downsample)");
   int* kc = ar.take<int>(3 * N);
@@ -839,9 +891,9 @@ vgicp_status downsample(const float* xyz, const float* t, int64_t n, double res,
   int* ranked = ar.take<int>(N);
   int* start = ar.take<int>(N + 1);
   int* tile_counts = ar.take<int>(kRunTiles);
-  int* totals = ar.take<int>(2);  // cells, voxels
+  int* totals = ar.take<int>(3);  // cells, voxels, a cell left unranked
   const bool p2 = pow2_res(res);
-  launch_call_init(nullptr, 0, bounds, report, s);
+  launch_call_init(&totals[2], 1, bounds, report, s);
   ds_cells_kernel<<<std::min(grid_for(n), 128), kBlock, 0, s>>>(xyz, t, n, p2 ? 1 : 0, res, 1.0 / res, kc,
                                                  bounds, report);
   if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
@@ -858,49 +910,43 @@ vgicp_status downsample(const float* xyz, const float* t, int64_t n, double res,
   for (;;) {
     Scratch sc;
     const int* order = nullptr;
+    auto sort = [&](int bits) {
+      return small ? sort_passes(sb, nullptr, 1, n, bits, &report->internal, s)
+                   : radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, bits, &report->internal, s, sc);
+    };
+    int* hist = small ? sb.hist : nullptr;
     if (by_time) {
-      ds_time_key_kernel<<<grid_for(n), kBlock, 0, s>>>(t, n, sb.k, sb.v);
-      if ((e = hipGetLastError()) ||
-          (e = radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, 32, &report->internal, s, sc)))
-        return hip_fail(e, "downsample time sort");
+      ds_time_key_kernel<<<(unsigned)sort_tiles(n), kBlock, 0, s>>>(t, n, sb.k, sb.v, hist);
+      if ((e = hipGetLastError()) || (e = sort(32))) return hip_fail(e, "downsample time sort");
       order = sb.v;
     }
-    const bool passes = small && !by_time;
     ds_cell_key_kernel<<<(unsigned)sort_tiles(n), kBlock, 0, s>>>(
-        kc, n, order, lo[0], lo[1], lo[2], by + bz, bz, sb.kt, sb.vt, passes ? sb.hist : nullptr);
+        kc, n, order, lo[0], lo[1], lo[2], by + bz, bz, sb.kt, sb.vt, hist);
     std::swap(sb.k, sb.kt);
     std::swap(sb.v, sb.vt);
-    e = passes ? sort_passes(sb, nullptr, 1, n, bx + by + bz, &report->internal, s)
-               : radix_sort_pairs(&sb.k, &sb.v, &sb.kt, &sb.vt, n, bx + by + bz,
-                                  &report->internal, s, sc);
-    if (e) return hip_fail(e, "downsample cell sort");
+    if ((e = sort(bx + by + bz))) return hip_fail(e, "downsample cell sort");
     if ((e = run_starts(sb.k, n, start, tile_counts, &totals[0], s)))
       return hip_fail(e, "downsample cells");
     const int* val = sb.v;
+    int* unranked = nullptr;
     if (t && !by_time) {
+      unranked = &totals[2];
       ds_time_rank_kernel<<<grid_for(n), kBlock, 0, s>>>(sb.v, n, start, &totals[0], t, ranked,
-                                                         report);
+                                                         unranked, report);
       val = ranked;
     }
-    ds_walk_kernel<false><<<grid_for(n), kBlock, 0, s>>>(val, n, start, &totals[0], xyz, t, thr,
-                                                         vcnt, nullptr, nullptr, 0, nullptr,
-                                                         nullptr, report);
+    ds_walk_kernel<false><<<grid_for(n), kBlock, 0, s>>>(
+        val, n, start, &totals[0], unranked, xyz, t, thr, vcnt, nullptr, nullptr, 0, nullptr, nullptr,
+        report);
     if ((e = hipGetLastError()) || (e = scan_values(vcnt, voff, n, tile_counts, &totals[1], s)))
       return hip_fail(e, "downsample count");
-    // a cell left unranked has no valid order: nothing is written before that is known
-    if (t && !by_time) {
-      if ((e = hipStreamSynchronize(s))) return hip_fail(e, "downsample count");
-      if (rep->deep) {
-        by_time = true;
-        continue;
-      }
-    }
-    ds_walk_kernel<true><<<grid_for(n), kBlock, 0, s>>>(val, n, start, &totals[0], xyz, t, thr,
-                                                        nullptr, voff, &totals[1], capacity,
+    ds_walk_kernel<true><<<grid_for(n), kBlock, 0, s>>>(val, n, start, &totals[0], unranked, xyz, t,
+                                                        thr, nullptr, voff, &totals[1], capacity,
                                                         xyz_out, t ? t_out : nullptr, report);
     if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
       return hip_fail(e, "downsample emit");
-    break;
+    if (!rep->deep || by_time) break;
+    by_time = true;  // a cell has no order: the walks have counted and written nothing
   }
   if (rep->internal) return fail(VGICP_E_HIP, "internal error in the downsample sort");
   const int64_t m = rep->count;
