@@ -132,6 +132,14 @@ typedef struct {
   int32_t lookahead;
 } vgicp_schedule;
 
+/* ---------------------------------------------------------------------------- memory */
+
+/* The library keeps the device blocks of finished calls and of destroyed maps and batches for the next
+ * ones: idle blocks of at most 256 MiB per device, and at most 16 pinned host blocks of 4 KiB. This
+ * frees the idle ones of every device (hipFree waits for the device); memory in use is not touched, and
+ * other threads may use the library meanwhile. */
+VGICP_API vgicp_status vgicp_release_idle(void);
+
 /* ---------------------------------------------------------------------------- preprocessing */
 
 /* Voxel-grid filter of Sec. III-C: every point goes to the cell floor(p / resolution) per axis

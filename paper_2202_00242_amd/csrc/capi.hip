@@ -201,6 +201,25 @@ HostBlock::~HostBlock() {
   (void)hipHostFree(p);
 }
 
+vgicp_status release_idle() {
+  std::vector<Block> idle;
+  std::vector<void*> host;
+  {
+    std::lock_guard<std::mutex> lk(g_block_mutex);
+    idle.swap(idle_blocks());
+  }
+  {
+    std::lock_guard<std::mutex> lk(g_host_mutex);
+    host.swap(host_blocks());
+  }
+  hipError_t first = hipSuccess;
+  for (const Block& k : idle)
+    if (const hipError_t e = hipFree(k.p); e != hipSuccess && first == hipSuccess) first = e;
+  for (void* p : host)
+    if (const hipError_t e = hipHostFree(p); e != hipSuccess && first == hipSuccess) first = e;
+  return first == hipSuccess ? VGICP_OK : hip_fail(first, "release of idle memory");
+}
+
 vgicp_status flags_to_status(unsigned f) {
   if (f & kFlagNonFinite)
     return fail(VGICP_E_NONFINITE,
@@ -335,6 +354,8 @@ VGICP_API vgicp_status vgicp_sync_status(vgicp_stream stream) {
   }
   return VGICP_OK;
 }
+
+VGICP_API vgicp_status vgicp_release_idle(void) { return release_idle(); }
 
 // ------------------------------------------------------------------------ preprocessing
 

@@ -88,12 +88,14 @@ RelPose make_rel_pose(const double* Tt, const double* Ts, double inv_res);
 
 // Device blocks that outlive a call. A block is handed out to one owner at a time and comes back only
 // when nothing on the device uses it any more (the owners below wait first), so it is safe across
-// streams and threads; idle blocks of a device are kept up to kBlocksKeep bytes, the rest is freed.
+// streams and threads; idle blocks of a device are kept up to kBlocksKeep bytes, the rest is freed
+// (release_idle frees them all).
 // (hipMalloc and hipFree per buffer were half of a sweep's 920 us; a stream-ordered pool still took
 // 18 us per allocation and release.) bytes: asked for, then the block's size.
 constexpr size_t kBlocksKeep = 256u << 20;
 hipError_t block_take(void** p, size_t* bytes);
 void block_give(void* p, size_t bytes, int device);
+vgicp_status release_idle();
 
 // Device memory of one host call that synchronises its stream: one block, cut up by take(). Sizes
 // are added up with need() first; get() takes the block. On every way out the stream is waited for

@@ -98,6 +98,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "vgicp_imu_linearize": [P, P, P, I32, P, P, I32, P, P, P, P, P],
         "vgicp_imu_preintegrate_bias": [P, I64, P, I32, P, D, D, P, P, P, P],
         "vgicp_imu_linearize_bias": [P, P, P, P, P, I32, P, P, P, I32, P, D, D, P, P, P, P],
+        "vgicp_release_idle": [],
         "vgicp_relative_pose": [P, P, P],
         "vgicp_se3_retract": [P, P, P],
         "vgicp_se3_right_jacobian": [P, P],
@@ -747,6 +748,12 @@ def vgicp_linearize_batched(maps, clouds, poses, factors, precision=VGICP_ACC_FP
 
 def vgicp_sync_status(stream=None):
     _check(_lib.vgicp_sync_status(_stream(stream)), "vgicp_sync_status")
+
+
+def vgicp_release_idle():
+    """Frees the memory that the library keeps from finished calls and destroyed maps and batches (at
+    most 256 MiB per device), e.g. to leave it to torch's allocator."""
+    _check(_lib.vgicp_release_idle(), "vgicp_release_idle")
 
 
 def vgicp_relative_pose(T_target, T_source) -> np.ndarray:

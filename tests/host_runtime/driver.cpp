@@ -11,6 +11,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/vgicp.h"
@@ -54,7 +55,7 @@ std::map<const void*, char*> g_symbols;
 size_t g_refuse_above = ~(size_t)0;            // device allocations of more bytes are refused
 size_t g_largest = 0;                          // largest device allocation so far
 std::atomic<int> g_launched{0};                // kernels launched
-int g_synchronised = -1;                       // device of the last device synchronisation
+std::atomic<int> g_synchronised{-1};           // device of the last device synchronisation
 Graph* g_capture = nullptr;
 std::vector<Launch> g_ran;                     // executed launches of batch_kernel
 thread_local int t_device = 0, t_error = kOk;
@@ -70,6 +71,29 @@ int error(int e) {
   t_error = e;
   return e;
 }
+
+// The map build, filter or neighbour search that a thread is in: the block and the pinned report that its
+// first kernel set up. Nobody else may be given them before it ends (done).
+std::map<const void*, std::thread::id> g_owner;
+thread_local const void *t_block = nullptr, *t_report = nullptr;
+
+void own(const void* block, const void* report) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  t_block = block;
+  t_report = report;
+  for (const void* p : {block, report}) g_owner[p] = std::this_thread::get_id();
+}
+
+void still_owned() {
+  std::lock_guard<std::mutex> lk(g_mu);
+  for (const void* p : {t_block, t_report})
+    if (p && g_owner[p] != std::this_thread::get_id()) {
+      std::printf("a block is in two hands\n");
+      std::exit(1);
+    }
+}
+
+void done() { t_block = t_report = nullptr; }
 
 // The allocation that holds p, nullptr when it is not live.
 const Alloc* owner(const void* p) {
@@ -114,6 +138,9 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* shared, void** s) {
 }
 int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
   ++g_launched;
+  if (kernels()[f].find("call_init_kernel") != std::string::npos && *(void**)args[2])
+    own(*(void**)args[2], *(void**)args[3]);
+  still_owned();
   if (kernels()[f].find("12batch_kernel") != std::string::npos) {
     const Launch l = {*(char**)args[2], *(char**)args[6]};
     std::lock_guard<std::mutex> lk(g_mu);
@@ -219,7 +246,10 @@ int hipStreamDestroy(void* s) {
   std::free(s);
   return kOk;
 }
-int hipStreamSynchronize(void*) { return kOk; }
+int hipStreamSynchronize(void*) {
+  still_owned();
+  return kOk;
+}
 int hipStreamWaitEvent(void*, void*, unsigned) { return kOk; }
 int hipStreamBeginCapture(void*, int) {
   g_capture = new Graph;
@@ -416,6 +446,50 @@ void workspace_checks() {
   vgicp_destroy_voxelmap(m);
 }
 
+// Maps, filters, neighbour searches and one-shot batches from eight threads: no block is in two hands,
+// what is kept is bounded, and the release gives all of it back.
+void threads() {
+  const double T[24] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0, 1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0};
+  std::vector<std::thread> all;
+  for (int k = 0; k < 8; ++k)
+    all.emplace_back([k, &T] {
+      vgicp_stream s = some<void>(k + 1);
+      for (int i = 0; i < 40; ++i) {
+        const int64_t n = 1000 + 7919 * ((k + i) % 5);
+        int64_t m = 0;
+        CHECK(vgicp_downsample(some<float>(), nullptr, n, 0.5, 0.1, some<float>(2), nullptr, n, &m, s) ==
+              VGICP_OK);
+        done();
+        CHECK(vgicp_knn(some<float>(), n, 10, 0.0, some<int32_t>(2), s) == VGICP_OK);
+        done();
+        vgicp_voxelmap map = nullptr;
+        CHECK(vgicp_build_voxelmap(nullptr, nullptr, 0, 0.5, s, &map) == VGICP_OK);
+        done();
+        const vgicp_cloud cloud = {some<float>(), some<float>(), n};
+        const vgicp_factor f = {0, 0, 0, 1, 1};
+        CHECK(vgicp_linearize_batched(&map, 1, &cloud, 1, T, 2, &f, 1, VGICP_ACC_FP64, some<double>(2),
+                                      some<double>(3), some<double>(4), some<int64_t>(5), s) == VGICP_OK);
+        done();
+        CHECK(vgicp_destroy_voxelmap(map) == VGICP_OK);
+        done();
+      }
+    });
+  for (auto& t : all) t.join();
+  const vgicp_voxelmap m = empty_map();
+  vgicp_batch_destroy(make_batch(m, {6000000}));  // 240 MB of copies, among others
+  vgicp_batch_destroy(make_batch(m, {4000000}));
+  done();
+  size_t kept = 0;
+  for (const auto& a : g_live) kept += a.second.bytes;
+  CHECK(kept > 0 && kept <= (256u << 20) + (1u << 20));  // and the map
+  CHECK(vgicp_release_idle() == VGICP_OK);
+  CHECK(live_count() == 1 && g_pinned.empty());
+  CHECK(vgicp_destroy_voxelmap(m) == VGICP_OK && vgicp_release_idle() == VGICP_OK);
+  CHECK(live_count() == 0);
+  CHECK(vgicp_release_idle() == VGICP_OK);
+  vgicp_destroy_voxelmap(empty_map());  // and the library takes memory again
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -425,6 +499,7 @@ int main(int argc, char** argv) {
       {"other_device_current", other_device_current},
       {"order_memory", order_memory},
       {"workspace_checks", workspace_checks},
+      {"threads", threads},
   };
   const auto it = tests.find(argc > 1 ? argv[1] : "");
   if (it == tests.end()) return 2;

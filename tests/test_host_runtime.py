@@ -48,3 +48,7 @@ def test_memory_of_ordering_small_clouds_beside_large_ones(driver):
 
 def test_workspace_checks(driver):
     run(driver, "workspace_checks")
+
+
+def test_kept_blocks_of_many_threads_are_bounded_and_released(driver):
+    run(driver, "threads")
