@@ -498,7 +498,7 @@ def vgicp_backward(m: VoxelMap, xyz, cov, T_target, T_source, binary: bool, corr
     """Returns (grad_xi (6|12,) f64, grad_xyz (3, n) f32 or None) as device tensors."""
     if stream is None:  # xi = 0, with torch's workspace
         return _backward_tangent(m, xyz, cov, T_target, T_source, None, None, binary, corr,
-                                 grad_err, precision, want_points, None)
+                                 grad_err, precision, want_points, None, name="vgicp_backward")
     n = _cloud(xyz, cov)
     _dev(corr, torch.int32, (n,), "corr")
     _dev(grad_err, torch.float64, (1,), "grad_err")
@@ -533,7 +533,8 @@ def vgicp_backward_tangent_workspace(m: VoxelMap, xyz, cov, T_target, T_source, 
 
 
 def _backward_tangent(m, xyz, cov, T_target, T_source, xi_target, xi_source, binary, corr,
-                      grad_err, precision, want_points, stream, workspace=None):
+                      grad_err, precision, want_points, stream, workspace=None,
+                      name="vgicp_backward_tangent"):
     n = _cloud(xyz, cov)
     _dev(corr, torch.int32, (n,), "corr")
     _dev(grad_err, torch.float64, (1,), "grad_err")
@@ -551,7 +552,7 @@ def _backward_tangent(m, xyz, cov, T_target, T_source, xi_target, xi_source, bin
         ws = _workspace(n, dev) if workspace is None else _flat(workspace, "workspace")
         fn = _lib.vgicp_backward_tangent_workspace
         args += [_ptr(ws), ws.numel()]
-    _check(fn(*args, _stream(stream)), "vgicp_backward_tangent")
+    _check(fn(*args, _stream(stream)), name)
     return gxi, gp
 
 

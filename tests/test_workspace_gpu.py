@@ -35,3 +35,19 @@ def test_refused_workspaces():
             assert ei.value.status == V.VGICP_E_INVALID_ARG
         form(block[8:8 + size])
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("explicit", [False, True])
+def test_errors_name_the_call(explicit):
+    """A refused call reports itself, on the current stream and on one that is passed."""
+    import paper_2202_00242_amd.vgicp as V
+    x, c = cloud_dev(*tiny.cloud(np.random.default_rng(4), 100))
+    m = V.vgicp_build_voxelmap(x, c, 0.5)
+    T, stream = np.eye(4), torch.cuda.current_stream() if explicit else None
+    corr = V.vgicp_evaluate(m, x, c, T, T, want_corr=True)["corr"]
+    g = dev(np.ones(1))
+    with pytest.raises(V.VGICPError, match="^vgicp_backward: "):
+        V.vgicp_backward(m, x, c, T, T, True, corr, g, V.VGICP_ACC_KAHAN_FP32, stream=stream)
+    with pytest.raises(V.VGICPError, match="^vgicp_backward_tangent: "):
+        V.vgicp_backward_tangent(m, x, c, T, T, None, None, True, corr, g, V.VGICP_ACC_KAHAN_FP32,
+                                 stream=stream)
