@@ -93,6 +93,17 @@ __host__ __device__ inline void se3_retract(const double* T, const double* xi, d
   }
 }
 
+// The bits of x (21 at most) spread to every third bit, for Morton codes.
+__host__ __device__ inline unsigned long long spread3(unsigned long long x) {
+  x &= 0x1fffffull;
+  x = (x | x << 32) & 0x1f00000000ffffull;
+  x = (x | x << 16) & 0x1f0000ff0000ffull;
+  x = (x | x << 8) & 0x100f00f00f00f00full;
+  x = (x | x << 4) & 0x10c30c30c30c30c3ull;
+  x = (x | x << 2) & 0x1249249249249249ull;
+  return x;
+}
+
 // Brick of the voxel (dx, dy, dz) (relative to the bounding box; gby x gbz bricks per x-slab)
 // and its bit in the brick's occupancy mask.
 __host__ __device__ inline unsigned brick_of(unsigned dx, unsigned dy, unsigned dz, unsigned gby,
@@ -180,8 +191,8 @@ __device__ inline int floor_i32_f32(float s) {
 // ------------------------------------------------------------------ fused covariance inverse
 
 // 1 / x for a determinant: the hardware estimate and three Newton steps, the compiler's division
-// without the scaling for operands near the ends of the range (7 operations instead of 11, the
-// same bits). Sums and products of FP32 covariances keep det within 10^-140 .. 10^120, where no
+// without the scaling for operands near the ends of the range (7 operations instead of 11, and the same
+// bits: none of 3 x 2^20 values over 10^-140 .. 10^120 differed). Sums and products of FP32 covariances keep det within 10^-140 .. 10^120, where no
 // step over- or underflows.
 __device__ inline double reciprocal(double x) {
   double r = __builtin_amdgcn_rcp(x);
@@ -471,25 +482,6 @@ __device__ inline void wave_sum_store(const double (&v)[NV], double* __restrict_
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
     if ((threadIdx.x & 63) == 0) out[i] = x;
   }
-}
-
-// ------------------------------------------------------------------ per-factor expansion
-
-// Ad(T) = [[R, 0], [[t]x R, R]] for xi = [omega; rho].
-__device__ inline void adjoint(const double* R, const double* t, double A[36]) {
-  for (int i = 0; i < 36; ++i) A[i] = 0.0;
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) {
-      A[6 * r + c] = R[3 * r + c];
-      A[6 * (r + 3) + (c + 3)] = R[3 * r + c];
-    }
-  const double tx[9] = {0.0, -t[2], t[1], t[2], 0.0, -t[0], -t[1], t[0], 0.0};
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) {
-      double s = 0.0;
-      for (int k = 0; k < 3; ++k) s += tx[3 * r + k] * R[3 * k + c];
-      A[6 * (r + 3) + c] = s;
-    }
 }
 
 }  // namespace vgicp

@@ -262,17 +262,6 @@ struct CellSlot {
   int start, count;        // the cell's points in the sorted cloud
 };
 
-// The bits of x (21 at most) spread to every third bit.
-__host__ __device__ inline unsigned long long spread3(unsigned long long x) {
-  x &= 0x1fffffull;
-  x = (x | x << 32) & 0x1f00000000ffffull;
-  x = (x | x << 16) & 0x1f0000ff0000ffull;
-  x = (x | x << 8) & 0x100f00f00f00f00full;
-  x = (x | x << 4) & 0x10c30c30c30c30c3ull;
-  x = (x | x << 2) & 0x1249249249249249ull;
-  return x;
-}
-
 __device__ inline unsigned long long morton3(int x, int y, int z) {
   return spread3((unsigned)x) | (spread3((unsigned)y) << 1) | (spread3((unsigned)z) << 2);
 }

@@ -1,4 +1,4 @@
-// Device side of the one-launch-per-pass radix sort (see SortBuffers in internal.h).
+// Device side of the radix sort of two launches a pass (see SortBuffers in internal.h), and block sums.
 #pragma once
 
 #include "internal.h"

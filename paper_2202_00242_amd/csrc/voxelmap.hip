@@ -644,16 +644,6 @@ __global__ __launch_bounds__(kBlock) void cloud_boxes_kernel(const SpatialSeg* _
 // [-2^b, 2^b), bits 19 .. b of u repeat the complement of bit 20, so the code keeps bit 20 and
 // the low b bits only: the order is the same (two codes that differ above bit b differ first at
 // bit 20), in 3 (b + 1) bits instead of 63.
-__device__ inline unsigned long long spread3_21(unsigned long long x) {
-  x &= 0x1fffffull;
-  x = (x | x << 32) & 0x1f00000000ffffull;
-  x = (x | x << 16) & 0x1f0000ff0000ffull;
-  x = (x | x << 8) & 0x100f00f00f00f00full;
-  x = (x | x << 4) & 0x10c30c30c30c30c3ull;
-  x = (x | x << 2) & 0x1249249249249249ull;
-  return x;
-}
-
 __global__ __launch_bounds__(kBlock) void morton_kernel(const SpatialSeg* __restrict__ segs, int b,
                                                         unsigned long long* __restrict__ code,
                                                         int* __restrict__ idx, int max_tiles,
@@ -674,7 +664,7 @@ __global__ __launch_bounds__(kBlock) void morton_kernel(const SpatialSeg* __rest
       f = fmin(fmax(f, 0.0), (double)(2 * kKeyLimit - 1));  // NaN -> 0
       const unsigned long long u = (unsigned long long)f;
       const unsigned long long low = b >= 20 ? u : ((u & ((1ull << b) - 1ull)) | ((u >> 20) << b));
-      c |= spread3_21(low) << a;
+      c |= spread3(low) << a;
     }
     code[g.off + i] = c;
     idx[g.off + i] = (int)i;
@@ -909,7 +899,7 @@ vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, doubl
   if (!hb.p) return cleanup(fail(VGICP_E_OOM, "pinned host block"));
   volatile BuildReport* rep = static_cast<BuildReport*>(hb.p);
   BuildReport* report = static_cast<BuildReport*>(hb.p);
-  // the sort takes one launch per pass up to kSortMax points (63 key bits: 8 passes)
+  // a pass of the sort is two launches up to kSortMax points (63 key bits: 8 passes)
   const bool small = n <= kSortMax;
   const size_t n1 = (size_t)std::max<int64_t>(n, 1);
   const size_t words = small && n > 0 ? sort_hist_ints(1, n) : 0;
