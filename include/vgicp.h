@@ -414,6 +414,9 @@ VGICP_API vgicp_status vgicp_backward_tangent_workspace(
  * inlier touches one 24-byte record instead of six planes. The per-factor results are the
  * same sums in another order (deterministic). Call vgicp_batch_refresh after changing the
  * clouds' points or covariances. Synchronises the null stream.
+ * Device memory: 40 bytes per point of the clouds for the copies, under 1 KB per factor, and 232 bytes
+ * for the partial sums of each of the schedule's block / 64 waves of every tile: 0.85 GB for the 159,600
+ * pairs of 400 submaps (10k to 120k points) at the default schedule; larger tiles take less.
  * Calls on one batch share its scratch (relative poses, work queues, partial sums, the LM
  * system) and are ordered: each call's stream first waits for the batch's previous call (an
  * event recorded at the end of every call), so calls issued on different streams run one after
