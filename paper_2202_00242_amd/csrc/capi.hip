@@ -166,6 +166,12 @@ void block_give(void* p, size_t bytes, int device) {
   for (const Block& k : drop) (void)hipFree(k.p);
 }
 
+void block_settle(void* p, size_t bytes, int device, hipError_t waited) {
+  if (waited == hipSuccess) return block_give(p, bytes, device);
+  (void)hipFree(p);
+  (void)hipGetLastError();
+}
+
 namespace {
 std::mutex g_host_mutex;
 std::vector<void*>& host_blocks() {  // not destroyed: calls may run while the process ends
@@ -191,7 +197,7 @@ HostBlock::HostBlock() {
 
 HostBlock::~HostBlock() {
   if (!p) return;
-  {
+  if (idle) {
     std::lock_guard<std::mutex> lk(g_host_mutex);
     if (host_blocks().size() < kHostBlocks) {
       host_blocks().push_back(p);
@@ -1818,13 +1824,13 @@ VGICP_API vgicp_status vgicp_batch_destroy(vgicp_batch batch) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   if (cur != batch->device) (void)hipSetDevice(batch->device);
-  (void)hipDeviceSynchronize();
+  const hipError_t waited = hipDeviceSynchronize();
   batch->drop_graphs();
   if (batch->capture_stream) (void)hipStreamDestroy(batch->capture_stream);
   if (batch->done) (void)hipEventDestroy(batch->done);
-  block_give(batch->arena, batch->arena_bytes, batch->device);
-  block_give(batch->d_sched, batch->sched_cap, batch->device);
-  block_give(batch->d_partials, batch->partials_cap, batch->device);
+  block_settle(batch->arena, batch->arena_bytes, batch->device, waited);
+  block_settle(batch->d_sched, batch->sched_cap, batch->device, waited);
+  block_settle(batch->d_partials, batch->partials_cap, batch->device, waited);
   for (void* p : {(void*)batch->d_gpts, (void*)batch->d_gf, (void*)batch->d_gbptr,
                   (void*)batch->d_gbcontrib, (void*)batch->d_cptr, (void*)batch->d_cfac,
                   (void*)batch->d_cloud_n, (void*)batch->d_cloud_off, (void*)batch->d_gout})

@@ -97,14 +97,34 @@ hipError_t block_take(void** p, size_t* bytes);
 void block_give(void* p, size_t bytes, int device);
 vgicp_status release_idle();
 
+// block_give after a wait: where the wait failed (hipDeviceSynchronize is refused while another thread
+// captures in global mode), work on the block may still run, so it is freed - hipFree waits by itself -
+// and not handed to the next call.
+void block_settle(void* p, size_t bytes, int device, hipError_t waited);
+
+// A pinned host block that a call's kernels write their results to (read after a synchronisation
+// of the stream; copies of a few bytes to pageable memory took 15 to 30 us each). A block belongs to
+// one call at a time; at most kHostBlocks idle ones are kept.
+constexpr size_t kHostBlocks = 16, kHostBlockBytes = 4096;
+struct HostBlock {
+  void* p = nullptr;
+  bool idle = true;  // false: its writers could not be waited for
+  HostBlock();
+  ~HostBlock();
+  HostBlock(const HostBlock&) = delete;
+  HostBlock& operator=(const HostBlock&) = delete;
+};
+
 // Device memory of one host call that synchronises its stream: one block, cut up by take(). Sizes
 // are added up with need() first; get() takes the block. On every way out the stream is waited for
-// before the block goes back. A map or batch keeps its block with keep() and gives it back after a
-// device synchronisation.
+// before the block (and the call's host block, which outlives it) goes back. A map or batch keeps its
+// block with keep() and gives it back after a device synchronisation.
 struct Arena {
   hipStream_t s = nullptr;
+  HostBlock* host = nullptr;
   char* base = nullptr;
   size_t used = 0, size = 0;
+  explicit Arena(HostBlock* h = nullptr) : host(h) {}
   static size_t up(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
   template <typename T>
   void need(size_t count) {
@@ -130,21 +150,10 @@ struct Arena {
     if (!base) return;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    (void)hipStreamSynchronize(s);
-    block_give(base, size, dev);
+    const hipError_t waited = hipStreamSynchronize(s);
+    if (host && waited != hipSuccess) host->idle = false;
+    block_settle(base, size, dev, waited);
   }
-};
-
-// A pinned host block that a call's kernels write their results to (read after a synchronisation
-// of the stream; copies of a few bytes to pageable memory took 15 to 30 us each). A block belongs to
-// one call at a time; at most kHostBlocks idle ones are kept.
-constexpr size_t kHostBlocks = 16, kHostBlockBytes = 4096;
-struct HostBlock {
-  void* p = nullptr;
-  HostBlock();
-  ~HostBlock();
-  HostBlock(const HostBlock&) = delete;
-  HostBlock& operator=(const HostBlock&) = delete;
 };
 
 // What the map build, the filter and the neighbour search read back. Error words are plain stores

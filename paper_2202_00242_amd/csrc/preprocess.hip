@@ -855,7 +855,7 @@ vgicp_status downsample(const float* xyz, const float* t, int64_t n, double res,
   volatile BuildReport* rep = report;
   const bool small = n <= kSortMax;
   const size_t words = small ? sort_hist_ints(1, n) : 0, N = (size_t)n;
-  Arena ar;
+  Arena ar(&hb);
   ar.need<int>(3 * N);
   ar.need<int>(8);
   ar.need<int>(words);
@@ -953,7 +953,7 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
   volatile BuildReport* rep = report;
   const bool small = n <= kSortMax;
   const size_t words = small ? sort_hist_ints(1, n) : 0, N = (size_t)n;
-  Arena ar;
+  Arena ar(&hb);
   ar.need<int>(8);
   ar.need<int>(words);
   ar.need<unsigned long long>(N);
@@ -1028,7 +1028,7 @@ vgicp_status knn(const float* xyz, int64_t n, int k, double cell, int32_t* nbr, 
     at[L] = slots_total;
     slots_total += cap;
   }
-  Arena at_ar;
+  Arena at_ar(&hb);
   Scratch sc;
   at_ar.need<CellSlot>(slots_total);
   if ((e = at_ar.get(s))) return hip_fail(e, "device block (knn)");

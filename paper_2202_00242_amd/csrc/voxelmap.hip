@@ -778,7 +778,7 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
   BuildReport* rep = static_cast<BuildReport*>(hb.p);
   const int S = (int)segs.size();
   std::vector<float> boxes(6 * C, 0.0f);
-  Arena a0;
+  Arena a0(&hb);
   a0.need<SpatialSeg>((size_t)S);
   a0.need<float>((size_t)S * kBoxBlocks * 8);
   a0.need<int>((size_t)S);
@@ -837,7 +837,7 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
     const int bits = b >= 20 ? 63 : 3 * (b + 1);
     const long long tiles = sort_tiles(max_n);
     const size_t words = big ? 0 : sort_hist_ints(m, max_n);
-    Arena ar;
+    Arena ar(&hb);
     Scratch sc;
     ar.need<unsigned long long>((size_t)pts);
     ar.need<unsigned long long>((size_t)pts);
@@ -903,7 +903,7 @@ vgicp_status build_voxelmap(const float* xyz, const float* cov, int64_t n, doubl
   const bool small = n <= kSortMax;
   const size_t n1 = (size_t)std::max<int64_t>(n, 1);
   const size_t words = small && n > 0 ? sort_hist_ints(1, n) : 0;
-  Arena ar;
+  Arena ar(&hb);
   Scratch sc;
   ar.need<int>(3 * n1);
   ar.need<int>(8);
@@ -1057,8 +1057,8 @@ void destroy_voxelmap(vgicp_voxelmap m) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   if (cur != m->device) (void)hipSetDevice(m->device);
-  (void)hipDeviceSynchronize();
-  if (m->arena) block_give(m->arena, m->arena_bytes, m->device);
+  const hipError_t waited = hipDeviceSynchronize();
+  if (m->arena) block_settle(m->arena, m->arena_bytes, m->device, waited);
   if (cur != m->device) (void)hipSetDevice(cur);
   delete m;
 }

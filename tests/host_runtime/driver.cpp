@@ -56,6 +56,7 @@ size_t g_refuse_above = ~(size_t)0;            // device allocations of more byt
 size_t g_largest = 0;                          // largest device allocation so far
 std::atomic<int> g_launched{0};                // kernels launched
 std::atomic<int> g_synchronised{-1};           // device of the last device synchronisation
+bool g_refuse_waits = false;                   // synchronisations fail (another thread captures, say)
 Graph* g_capture = nullptr;
 std::vector<Launch> g_ran;                     // executed launches of batch_kernel
 thread_local int t_device = 0, t_error = kOk;
@@ -158,6 +159,7 @@ int hipSetDevice(int d) {
   return kOk;
 }
 int hipDeviceSynchronize() {
+  if (g_refuse_waits) return error(kInvalid);
   g_synchronised = t_device;
   return kOk;
 }
@@ -247,6 +249,7 @@ int hipStreamDestroy(void* s) {
   return kOk;
 }
 int hipStreamSynchronize(void*) {
+  if (g_refuse_waits) return error(kInvalid);
   still_owned();
   return kOk;
 }
@@ -446,6 +449,30 @@ void workspace_checks() {
   vgicp_destroy_voxelmap(m);
 }
 
+// Memory whose users could not be waited for is freed (the runtime's free waits by itself), not kept
+// for the next call.
+void refused_waits() {
+  vgicp_voxelmap m = empty_map();
+  vgicp_batch b = make_batch(m, {1000, 2000});
+  CHECK(vgicp_release_idle() == VGICP_OK);
+  const size_t pinned = g_pinned.size();
+  CHECK(pinned == 0);
+  g_refuse_waits = true;
+  int64_t n = 0;
+  CHECK(vgicp_downsample(some<float>(), nullptr, 5000, 0.5, 0.1, some<float>(2), nullptr, 5000, &n,
+                         nullptr) == VGICP_E_HIP);
+  vgicp_voxelmap other = nullptr;
+  CHECK(vgicp_build_voxelmap(nullptr, nullptr, 0, 0.5, nullptr, &other) == VGICP_E_HIP && !other);
+  CHECK(vgicp_knn(some<float>(), 5000, 10, 0.0, some<int32_t>(2), nullptr) == VGICP_E_HIP);
+  CHECK(vgicp_batch_refresh(b, nullptr) == VGICP_E_HIP);
+  CHECK(vgicp_batch_destroy(b) == VGICP_OK);
+  CHECK(vgicp_destroy_voxelmap(m) == VGICP_OK);
+  g_refuse_waits = false;
+  // nothing is left that a next call could be given
+  CHECK(live_count() == 0 && g_pinned.empty());
+  vgicp_destroy_voxelmap(empty_map());
+}
+
 // Maps, filters, neighbour searches and one-shot batches from eight threads: no block is in two hands,
 // what is kept is bounded, and the release gives all of it back.
 void threads() {
@@ -499,6 +526,7 @@ int main(int argc, char** argv) {
       {"other_device_current", other_device_current},
       {"order_memory", order_memory},
       {"workspace_checks", workspace_checks},
+      {"refused_waits", refused_waits},
       {"threads", threads},
   };
   const auto it = tests.find(argc > 1 ? argv[1] : "");

@@ -52,3 +52,7 @@ def test_workspace_checks(driver):
 
 def test_kept_blocks_of_many_threads_are_bounded_and_released(driver):
     run(driver, "threads")
+
+
+def test_memory_that_was_not_waited_for_is_not_kept(driver):
+    run(driver, "refused_waits")
