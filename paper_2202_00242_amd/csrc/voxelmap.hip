@@ -837,6 +837,8 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
     const int bits = b >= 20 ? 63 : 3 * (b + 1);
     const long long tiles = sort_tiles(max_n);
     const size_t words = big ? 0 : sort_hist_ints(m, max_n);
+    std::vector<SortSeg> ss;  // read by a copy until the stream is waited for, at the latest by the block
+    for (int i = 0; i < m; ++i) ss.push_back({segs[first + i].off, segs[first + i].n, 0});
     Arena ar(&hb);
     Scratch sc;
     ar.need<unsigned long long>((size_t)pts);
@@ -853,8 +855,6 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
     sb.vt = ar.take<int>((size_t)pts);
     sb.hist = ar.take<int>(words);
     SortSeg* d_ss = ar.take<SortSeg>((size_t)m);
-    std::vector<SortSeg> ss;
-    for (int i = 0; i < m; ++i) ss.push_back({segs[first + i].off, segs[first + i].n, 0});
     if ((e = hipMemcpyAsync(d_segs + first, segs.data() + first, (size_t)m * sizeof(SpatialSeg),
                             hipMemcpyHostToDevice, s)) ||
         (e = hipMemcpyAsync(d_ss, ss.data(), ss.size() * sizeof(SortSeg), hipMemcpyHostToDevice,
@@ -870,7 +870,6 @@ vgicp_status spatial_copies(std::vector<SpatialJob>& jobs, float* d_boxes, hipSt
     gather_clouds_kernel<<<dim3((unsigned)std::min<long long>((max_n + 255) / 256, 4096),
                                 (unsigned)m),
                            kBlock, 0, s>>>(d_segs + first, sb.v, &rep->internal);
-    // the host vectors above are read by the copies until here
     if ((e = hipGetLastError()) || (e = hipStreamSynchronize(s)))
       return hip_fail(e, "cloud order");
     first += m;

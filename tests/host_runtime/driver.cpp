@@ -46,6 +46,11 @@ struct Config {
 struct Graph {
   std::vector<Launch> launches;
 };
+struct Copy {  // an asynchronous copy that runs at the next wait
+  void* to;
+  const void* from;
+  std::vector<char> then;  // what was there when it was asked for
+};
 
 constexpr int kOk = 0, kInvalid = 1, kOutOfMemory = 2;
 std::mutex g_mu;
@@ -53,10 +58,13 @@ std::map<char*, Alloc> g_live;                 // device memory
 std::map<char*, size_t> g_pinned;
 std::map<const void*, char*> g_symbols;
 size_t g_refuse_above = ~(size_t)0;            // device allocations of more bytes are refused
+size_t g_refuse_exactly = 0;                    // and those of this size
 size_t g_largest = 0;                          // largest device allocation so far
 std::atomic<int> g_launched{0};                // kernels launched
 std::atomic<int> g_synchronised{-1};           // device of the last device synchronisation
 bool g_refuse_waits = false;                   // synchronisations fail (another thread captures, say)
+bool g_defer = false;                          // asynchronous copies run at the next wait
+std::vector<Copy> g_copies;
 Graph* g_capture = nullptr;
 std::vector<Launch> g_ran;                     // executed launches of batch_kernel
 thread_local int t_device = 0, t_error = kOk;
@@ -179,7 +187,7 @@ int hipGetSymbolAddress(void** p, const void* s) {
 }
 
 int hipMalloc(void** p, size_t n) {
-  if (n > g_refuse_above) return error(kOutOfMemory);
+  if (n > g_refuse_above || n == g_refuse_exactly) return error(kOutOfMemory);
   char* q = (char*)std::calloc(1, n ? n : 1);
   std::lock_guard<std::mutex> lk(g_mu);
   g_live[q] = {n, t_device};
@@ -217,7 +225,11 @@ int hipMemcpy(void* d, const void* s, size_t n, int) {
   std::memcpy(d, s, n);
   return kOk;
 }
-int hipMemcpyAsync(void* d, const void* s, size_t n, int k, void*) { return hipMemcpy(d, s, n, k); }
+int hipMemcpyAsync(void* d, const void* s, size_t n, int k, void*) {
+  if (!g_defer) return hipMemcpy(d, s, n, k);
+  g_copies.push_back({d, s, std::vector<char>((const char*)s, (const char*)s + n)});
+  return kOk;
+}
 int hipMemset(void* d, int v, size_t n) {
   std::memset(d, v, n);
   return kOk;
@@ -250,6 +262,14 @@ int hipStreamDestroy(void* s) {
 }
 int hipStreamSynchronize(void*) {
   if (g_refuse_waits) return error(kInvalid);
+  for (const Copy& c : g_copies) {
+    if (std::memcmp(c.from, c.then.data(), c.then.size()) != 0) {
+      std::printf("the source of a copy changed before it was waited for\n");
+      std::exit(1);
+    }
+    std::memcpy(c.to, c.from, c.then.size());
+  }
+  g_copies.clear();
   still_owned();
   return kOk;
 }
@@ -449,6 +469,21 @@ void workspace_checks() {
   vgicp_destroy_voxelmap(m);
 }
 
+// A call that ends early leaves no copy behind that reads memory of its own.
+void copies_of_a_refused_call() {
+  const vgicp_voxelmap m = empty_map();
+  const vgicp_cloud cloud = {some<float>(), some<float>(), (1 << 18) + 5};
+  const vgicp_factor f = {0, 0, 0, 1, 1};
+  vgicp_batch b = nullptr;
+  g_defer = true;
+  g_refuse_exactly = 256 * 129 * sizeof(int);  // the digit counts of the long sort
+  CHECK(vgicp_batch_create(&m, 1, &cloud, 1, &f, 1, 2, &b) == VGICP_E_OOM && !b);
+  g_refuse_exactly = 0;
+  CHECK(hipStreamSynchronize(nullptr) == kOk);
+  CHECK(vgicp_batch_create(&m, 1, &cloud, 1, &f, 1, 2, &b) == VGICP_OK);
+  CHECK(vgicp_batch_destroy(b) == VGICP_OK && vgicp_destroy_voxelmap(m) == VGICP_OK);
+}
+
 // Memory whose users could not be waited for is freed (the runtime's free waits by itself), not kept
 // for the next call.
 void refused_waits() {
@@ -526,6 +561,7 @@ int main(int argc, char** argv) {
       {"other_device_current", other_device_current},
       {"order_memory", order_memory},
       {"workspace_checks", workspace_checks},
+      {"copies_of_a_refused_call", copies_of_a_refused_call},
       {"refused_waits", refused_waits},
       {"threads", threads},
   };

@@ -56,3 +56,7 @@ def test_kept_blocks_of_many_threads_are_bounded_and_released(driver):
 
 def test_memory_that_was_not_waited_for_is_not_kept(driver):
     run(driver, "refused_waits")
+
+
+def test_copies_of_a_refused_call_are_over_when_it_returns(driver):
+    run(driver, "copies_of_a_refused_call")
