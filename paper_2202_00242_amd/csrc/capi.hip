@@ -908,6 +908,12 @@ bool valid_schedule(const vgicp_schedule& s) {
          s.blocks_per_cu <= 16 && (s.lookahead == 2 || s.lookahead == 4 || s.lookahead == 8);
 }
 
+// Blocks of 256 threads that a schedule asks for.
+int schedule_grid(vgicp_batch b, const vgicp_schedule& s) {
+  const int blocks = device_cu_count(b->device) * s.blocks_per_cu * (s.block / 256);
+  return ((blocks + kNumXcd - 1) / kNumXcd) * kNumXcd;
+}
+
 // Splits every factor into tiles and orders the work: factors are grouped by source cloud (its
 // positions and covariances, the larger part of a factor's traffic, then stay in one XCD's L2 while
 // its factors run; grouped by target map the global batch took 1,318 us instead of 1,269 and the
@@ -1011,9 +1017,7 @@ vgicp_status apply_schedule(vgicp_batch b, const vgicp_schedule& sc) {
   b->d_seg = reinterpret_cast<int*>(b->d_sched + o_seg);
   b->d_items = reinterpret_cast<WorkItem*>(b->d_sched + o_items);
   b->total_tiles = (int)total;
-  const int cus = device_cu_count(b->device);
-  const int blocks = cus * sc.blocks_per_cu * (sc.block / 256);
-  b->grid = ((blocks + kNumXcd - 1) / kNumXcd) * kNumXcd;
+  b->grid = schedule_grid(b, sc);
   b->sched = sc;
   return VGICP_OK;
 }
@@ -1770,18 +1774,28 @@ vgicp_status autotune(vgicp_batch batch, const double* poses, vgicp_precision pr
                    times.back());
     return times[times.size() / 2];
   };
-  // stage 1: every candidate, median of 3; stage 2: the six fastest again, median of 31
+  // stage 1: every candidate (of at most 90) once, median of 3; stage 2: the six fastest again, median of 31
   const int blocks[] = {256, 512};
   const int per_lane[] = {8, 16, 32};
   const int bpcs[] = {1, 2, 3, 4, 8};
   const int looks[] = {2, 4, 8};
   std::vector<std::pair<float, vgicp_schedule>> ranked;
+  // candidates whose grids come to the same one are the same launch: the first of them is timed
+  std::set<std::array<int, 4>> seen;
+  auto first_of_its_launch = [&](const vgicp_schedule& sc) {
+    int64_t tiles = 0;
+    for (const FactorView& f : batch->hf) tiles += (f.n + sc.tile - 1) / sc.tile;
+    if (tiles >= (1LL << 31) / kPartialStride) return true;  // refused when it is applied
+    const int grid = batch_grid(schedule_grid(batch, sc), (int)tiles, sc.block,
+                                std::max(device_cu_count(batch->device), kNumXcd), (int)precision);
+    return seen.insert({sc.block, sc.tile, sc.lookahead, grid}).second;
+  };
   for (int blk : blocks)
     for (int pl : per_lane)
       for (int bpc : bpcs)
         for (int la : looks) {
           vgicp_schedule sc{blk, blk * pl, bpc, la};
-          if (!valid_schedule(sc)) continue;
+          if (!valid_schedule(sc) || !first_of_its_launch(sc)) continue;
           const float t = time_schedule(sc, 3, 1);
           if (t >= 0.0f) ranked.push_back({t, sc});
         }

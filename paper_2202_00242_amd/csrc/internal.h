@@ -308,6 +308,8 @@ struct BatchLaunch {
   int64_t* inliers;
 };
 void launch_batched(const BatchLaunch& L, hipStream_t s);
+// Blocks that a schedule's grid comes to for a batch of this many tiles.
+int batch_grid(int grid, int total_tiles, int block, int cus, int precision);
 
 // Batched backward (kernels.hip): the batch kernel in its gradient mode (the queue of inliers
 // carries the gradient terms), then per factor, per pose and per source point sums.

@@ -991,13 +991,12 @@ constexpr float kStaticShare = 0.3f;
 
 // Waves per SIMD the registers are kept to: 4 (128 registers) where the lane sums are 28 floats, 3
 // where they are 56 words.
-template <int PREC>
-constexpr int waves_for() {
-  return PREC == kAccKahan || PREC == kMathFp64 ? 3 : 4;
+constexpr int waves_for(int precision) {
+  return precision == kAccKahan || precision == kMathFp64 ? 3 : 4;
 }
 
 template <int PREC, bool LIN, bool GRAD = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for<PREC>()))) void
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for(PREC)))) void
 batch_kernel(const FactorView* __restrict__ F, const RelPose* __restrict__ rel,
              const WorkItem* __restrict__ items, const int* __restrict__ seg,
              unsigned long long* __restrict__ heads, BatchCut cut,
@@ -1356,14 +1355,9 @@ BatchCut cut_of(const BatchLaunch& L) {
   return {L.tile, 64 * L.lookahead, L.block / 64, L.block == 512 ? 3 : 2};
 }
 
-// The schedule's grid, but no more blocks than fit the chip together: a wave of a later round would
-// start on its dealt items when everyone else is done (global batch, 6 blocks per CU instead of 4:
-// 1,371 us instead of 1,242).
 template <int PREC>
 int resident(const BatchLaunch& L) {
-  const int need = (L.total_tiles * (L.block / 64) + 3) / 4;  // a wave item per wave at least
-  const int most = std::min(L.grid, L.cus * waves_for<PREC>());
-  return std::max((std::min(need, most) + kNumXcd - 1) / kNumXcd, 1) * kNumXcd;
+  return batch_grid(L.grid, L.total_tiles, L.block, L.cus, PREC);
 }
 
 template <int PREC, bool LIN>
@@ -1387,6 +1381,15 @@ void launch_batch_count(const BatchLaunch& L, hipStream_t s) {
 }
 
 }  // namespace
+
+// The schedule's grid, but no more blocks than fit the chip together: a wave of a later round would
+// start on its dealt items when everyone else is done (global batch, 6 blocks per CU instead of 4:
+// 1,371 us instead of 1,242).
+int batch_grid(int grid, int total_tiles, int block, int cus, int precision) {
+  const int need = (total_tiles * (block / 64) + 3) / 4;  // a wave item per wave at least
+  const int most = std::min(grid, cus * waves_for(precision));
+  return std::max((std::min(need, most) + kNumXcd - 1) / kNumXcd, 1) * kNumXcd;
+}
 
 void launch_plain(const MapView& m, const RelPose& T, const float* xyz, const float* cov,
                   int64_t n, int binary, int precision, bool linearize, double* partials,

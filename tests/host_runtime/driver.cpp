@@ -3,6 +3,7 @@
 // device memory in host memory, kernels that do nothing and refusals on demand. What it checks is the
 // library's host code: who owns which block of memory, on which device, and what is left after a
 // refused allocation. Usage: driver <test>; prints "<test> ok".
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <cstdio>
@@ -484,6 +485,36 @@ void copies_of_a_refused_call() {
   CHECK(vgicp_batch_destroy(b) == VGICP_OK && vgicp_destroy_voxelmap(m) == VGICP_OK);
 }
 
+// The autotuner times no launch twice in its first stage: with the grid capped at the resident blocks
+// (256 CUs here, 4 blocks of 4 waves, 3 for the forms with wide sums) several blocks-per-CU values are one.
+void tuned_once() {
+  const vgicp_voxelmap m = empty_map();
+  const vgicp_batch b = make_batch(m, std::vector<int64_t>(64, 1000000));
+  const char* path = std::getenv("VGICP_AUTOTUNE_LOG");
+  for (int precision = 0; precision < 4; ++precision) {
+    std::remove(path);
+    vgicp_schedule chosen;
+    CHECK(vgicp_batch_autotune(b, some<double>(), (vgicp_precision)precision, nullptr, &chosen, nullptr) ==
+          VGICP_OK);
+    const int most = precision == VGICP_ACC_KAHAN_FP32 || precision == VGICP_MATH_FP64 ? 3 : 4;
+    std::map<std::vector<int>, int> launches;
+    std::FILE* f = std::fopen(path, "r");
+    CHECK(f);
+    char line[256];
+    while (std::fgets(line, sizeof line, f)) {
+      int stage, block, tile, per_cu, look;
+      if (std::sscanf(line, "%d %d %d %d %d", &stage, &block, &tile, &per_cu, &look) != 5 || stage != 1)
+        continue;
+      const std::vector<int> launch = {block, tile, look, std::min(per_cu * block / 256, most)};
+      CHECK(++launches[launch] == 1);
+    }
+    std::fclose(f);
+    CHECK(launches.size() == (most == 4 ? 54u : 45u));  // 2 x 3 x 3 cuts, 4 + 2 grids (3 + 2)
+  }
+  vgicp_batch_destroy(b);
+  vgicp_destroy_voxelmap(m);
+}
+
 // Memory whose users could not be waited for is freed (the runtime's free waits by itself), not kept
 // for the next call.
 void refused_waits() {
@@ -562,6 +593,7 @@ int main(int argc, char** argv) {
       {"order_memory", order_memory},
       {"workspace_checks", workspace_checks},
       {"copies_of_a_refused_call", copies_of_a_refused_call},
+      {"tuned_once", tuned_once},
       {"refused_waits", refused_waits},
       {"threads", threads},
   };

@@ -25,8 +25,9 @@ def driver(tmp_path_factory):
     return exe
 
 
-def run(driver, name):
-    r = subprocess.run([driver, name], capture_output=True, text=True, timeout=120)
+def run(driver, name, **env):
+    r = subprocess.run([driver, name], capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, **env))
     assert r.returncode == 0 and f"{name} ok" in r.stdout, (r.returncode, r.stdout + r.stderr)
 
 
@@ -60,3 +61,7 @@ def test_memory_that_was_not_waited_for_is_not_kept(driver):
 
 def test_copies_of_a_refused_call_are_over_when_it_returns(driver):
     run(driver, "copies_of_a_refused_call")
+
+
+def test_autotune_times_each_launch_once(driver, tmp_path):
+    run(driver, "tuned_once", VGICP_AUTOTUNE_LOG=str(tmp_path / "log"))
